@@ -789,7 +789,7 @@ int32_t validate_values(smx_ctx c)
     HIP_TRY(c, c->d_check.ensure(2));
     HIP_TRY(c, hipMemsetAsync(c->d_check.p, 0, 2 * sizeof(double), c->stream));
     HIP_TRY(c, launch_check_values(c->stream, c->nnzb, c->d_valoff.p, c->d_brow.p, c->d_bcol.p,
-                                   c->d_mirror.p, c->d_k.p, c->d_check.p));
+                                   c->d_mirror.p, c->d_k.p, c->nvals, c->d_check.p));
     double h[2] = {0, 0};
     HIP_TRY(c, hipMemcpyAsync(h, c->d_check.p, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));

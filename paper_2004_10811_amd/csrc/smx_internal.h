@@ -270,7 +270,7 @@ hipError_t launch_own_trace(hipStream_t st, int g0, int ngroups, const GroupDesc
 
 hipError_t launch_check_values(hipStream_t st, int64_t nblocks, const int64_t *valoff,
                                const int32_t *blk_rows, const int32_t *blk_cols,
-                               const int64_t *mirror, const double *kvals, double *out2);
+                               const int64_t *mirror, const double *kvals, int64_t nvals, double *out2);
 
 // ---- batched symmetric eigensolver (finite temperature, Algorithm 1) --------
 // Largest submatrix dimension of the eigensolver path (its workgroups keep

@@ -611,21 +611,28 @@ void reduce_kernel(int64_t n, const double *__restrict__ pe, const double *__res
 }
 
 // Validation of K's values: max|K_IJ - K_JI^T| and max|K| (NaN/Inf -> +Inf).
+// Bound by HBM (K is read once; the mirrored block mostly comes from a cache).
+// A fixed grid walks the stored blocks, L lanes per block, and every workgroup
+// ends with one atomic pair: one pair per stored block serialised on the two
+// result words (about 20 ns each: 6.2 ms for water1024's 330,000 blocks, 27 ms
+// for the 1.2 million one-element blocks of the split water256e, against
+// 0.10 ms and 0.04 ms this way).  Maxima do not depend on the order.
+template <int L>
 __global__ __launch_bounds__(256)
 void check_values_kernel(int64_t nblocks, const int64_t *__restrict__ valoff,
                          const int32_t *__restrict__ brow, const int32_t *__restrict__ bcol,
                          const int64_t *__restrict__ mirror, const double *__restrict__ kv,
                          unsigned long long *__restrict__ out2)
 {
-    const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
+    __shared__ double sm[2][4];
+    const int sub = threadIdx.x & (L - 1);
     double asym = 0.0, amax = 0.0;
-    if (p < nblocks) {
+    for (int64_t p = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L; p < nblocks; p += (int64_t)gridDim.x * (256 / L)) {
         const int bi = brow[p], bj = bcol[p];
         const int64_t q = mirror[p];
         const double *a = kv + valoff[p];
         const double *b = kv + valoff[q];          // block (J, I): bj x bi
-        for (int t = lane; t < bi * bj; t += 64) {
+        for (int t = sub; t < bi * bj; t += L) {
             const int rr = t % bi, cc = t / bi;
             const double x = a[t];
             const double y = b[cc + (int64_t)rr * bj];
@@ -638,9 +645,14 @@ void check_values_kernel(int64_t nblocks, const int64_t *__restrict__ valoff,
     }
     asym = wave_max(asym);
     amax = wave_max(amax);
-    if (lane == 0 && p < nblocks) {
-        atomic_max_nonneg(out2 + 0, asym);
-        atomic_max_nonneg(out2 + 1, amax);
+    if ((threadIdx.x & 63) == 0) {
+        sm[0][threadIdx.x >> 6] = asym;
+        sm[1][threadIdx.x >> 6] = amax;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const double *s = sm[threadIdx.x];
+        atomic_max_nonneg(out2 + threadIdx.x, fmax(fmax(s[0], s[1]), fmax(s[2], s[3])));
     }
 }
 
@@ -877,13 +889,25 @@ hipError_t launch_reduce(hipStream_t st, int64_t n, const double *part_e, const 
 
 hipError_t launch_check_values(hipStream_t st, int64_t nblocks, const int64_t *valoff,
                                const int32_t *blk_rows, const int32_t *blk_cols,
-                               const int64_t *mirror, const double *kvals, double *out2)
+                               const int64_t *mirror, const double *kvals, int64_t nvals, double *out2)
 {
     if (nblocks <= 0) return hipSuccess;
-    const int64_t grid = (nblocks + 3) / 4;
-    hipLaunchKernelGGL(check_values_kernel, dim3((unsigned)grid), dim3(256), 0, st, nblocks, valoff,
-                       blk_rows, blk_cols, mirror, kvals,
-                       reinterpret_cast<unsigned long long *>(out2));
+    // Lanes per block by the mean block: more lanes than elements idle (the
+    // one-element blocks of the split water256e: 0.42 ms with 64 lanes, 0.04 ms
+    // with one), and a wave that spans several blocks has more of the dependent
+    // index loads in flight (water1024, mean 47 elements: 0.13 ms with 64 lanes,
+    // 0.10 ms with 8); from 512 elements on, 64 lanes have eight loads each.
+    // Four workgroups per CU.
+    unsigned long long *o = reinterpret_cast<unsigned long long *>(out2);
+    const auto go = [&](auto kernel, int lanes) {
+        const int64_t grid = std::min<int64_t>((nblocks * lanes + 255) / 256, 1024);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, nblocks, valoff, blk_rows, blk_cols, mirror,
+                           kvals, o);
+    };
+    const int64_t mean = nvals / nblocks;
+    if (mean >= 512) go(check_values_kernel<64>, 64);
+    else if (mean >= 4) go(check_values_kernel<8>, 8);
+    else go(check_values_kernel<1>, 1);
     return hipGetLastError();
 }
 
