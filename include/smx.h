@@ -612,7 +612,8 @@ int32_t smx_get_launch_profile(smx_ctx ctx, int32_t cap, float *ms, double *algo
  * tile (2 x 16 x 16 x n_pad per live 16 x 16 block of a 256 x 256 tile),
  * times the word products per algorithmic product (3 for SMX_FP16_2W, 6 for
  * SMX_BF16_3W, else 1), padding included, for every group the launch works
- * on; kind 12 (vector units only) repeats its algorithmic flops.  Divided by
+ * on (the FP64 products are counted in the same 64 x 64 tiles, of which they
+ * skip the 32 x 32 parts beyond the matrix or above the diagonal); kind 12 (vector units only) repeats its algorithmic flops.  Divided by
  * the launch time and the matrix-core peak of the format this is the
  * fraction of the matrix cores the launch kept busy.  Writes min(cap, count)
  * entries (issued_flops may be NULL) and the launch count to *count.

@@ -105,6 +105,10 @@ struct Plan {
     std::vector<int32_t> own_list;    // own columns of every group (submatrix column indices)
     std::vector<double> wtiles;       // live 64 x 64 wave tiles of one product, per group
     std::vector<TileDesc> tiles_full; // every tile (general products of the adjoint), XCD-ordered
+    // lower tiles of the FP64 products and their edge (also that of tiles_full); per wave like tile_beg
+    int32_t edge_d = kTile;
+    std::vector<TileDesc> tiles_d;
+    std::vector<int64_t> tiles_d_beg;
     std::vector<int64_t> cptr;        // per stored block: its contributions from the groups (adjoint)
     std::vector<int4> contrib;        // (group, row offset, column offset, 0), ascending group per block
     // waves: consecutive group ranges [wave_g[w], wave_g[w+1]) whose slabs share one arena;
@@ -138,7 +142,7 @@ struct Plan {
 // context's own buffers, or places in the static scratch array.
 struct DevView {
     const GroupDesc *gd = nullptr;
-    const TileDesc *tiles = nullptr, *tiles_s = nullptr, *tiles_b = nullptr;
+    const TileDesc *tiles = nullptr, *tiles_s = nullptr, *tiles_b = nullptr, *tiles_d = nullptr;
     const TileDesc *tiles_sx = nullptr;     // per-XCD lists of the persistent word products (context buffers only)
     const int32_t *xbeg = nullptr;
     const int2 *chunks = nullptr;
@@ -205,7 +209,7 @@ struct smx_context {
     DevBuf<int32_t> d_brow, d_bcol;
     // device: plan
     DevBuf<GroupDesc> d_gd;
-    DevBuf<TileDesc> d_tiles, d_tiles_s, d_tiles_b, d_tiles_sx;
+    DevBuf<TileDesc> d_tiles, d_tiles_s, d_tiles_b, d_tiles_sx, d_tiles_d;
     DevBuf<int32_t> d_xbeg, d_tq;           // per-XCD list offsets, counters of the persistent word products
     DevBuf<int2> d_chunks;
     DevBuf<RowInfo> d_rinfo;
@@ -498,6 +502,22 @@ int64_t group_bytes(const GroupDesc &d)
     return kArenaBytesPerElem * (int64_t)d.npad * d.npad + (2 * kMaxPolishMixed + 1) * 8 * (int64_t)d.npad * d.m_own;
 }
 
+// Tile edge of the FP64 products (bitwise the same results).  Edge 64 once its
+// tiles fill the chip: four workgroups on each of the 256 CUs are 1024 tiles.
+// With fewer, edge 32 spreads the same products over more waves.  Square per
+// launch, edge 32 / 64: 36 tiles of 64 (12 groups of n ~ 90) 6.3 / 11.0 us, 240
+// (16 of 271) 17.0 / 20.3, 920 (40 of 374) 55 / 61, 2476 (60 of 518) 187 / 191,
+// 3025 (40 of 724) 320 / 293, 3600 (100 of 503) 284 / 272.
+int32_t f64_edge(const Plan &P)
+{
+    int64_t tiles64 = 0;
+    for (const GroupDesc &d : P.gd) {
+        const int64_t nt = (d.npad + 63) / 64;
+        tiles64 += nt * (nt + 1) / 2;
+    }
+    return tiles64 <= 1536 ? 32 : 64;
+}
+
 // Split the groups into consecutive waves of at most `budget` bytes each
 // (balanced: about total / ceil(total / budget) per wave), assign the
 // wave-relative slab offsets, and build each wave's launch lists.
@@ -537,6 +557,9 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     P.tiles_b.clear();
     P.tiles_s_beg.assign(1, 0);
     P.tiles_b_beg.assign(1, 0);
+    P.edge_d = f64_edge(P);
+    P.tiles_d.clear();
+    P.tiles_d_beg.assign(1, 0);
     P.tiles_sx.clear();
     P.sx_wbeg.assign(1, 0);
     P.xbeg.clear();
@@ -548,7 +571,7 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     size_t ch = 0;
     for (int32_t w = 0; w < nw; w++) {
         int64_t e = 0, t = 0;
-        std::vector<TileDesc> tl, ts, tb;
+        std::vector<TileDesc> tl, ts, tb, td;
         for (int32_t g = P.wave_g[w]; g < P.wave_g[w + 1]; g++) {
             GroupDesc &d = P.gd[g];
             d.off = e;
@@ -558,6 +581,9 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
             const int32_t nt = (d.npad + kTile - 1) / kTile;
             for (int32_t ti = 0; ti < nt; ti++)
                 for (int32_t tj = 0; tj <= ti; tj++) tl.push_back(TileDesc{g, (ti << 16) | tj});
+            const int32_t ntd = (d.npad + P.edge_d - 1) / P.edge_d;
+            for (int32_t ti = 0; ti < ntd; ti++)
+                for (int32_t tj = 0; tj <= ti; tj++) td.push_back(TileDesc{g, (ti << 16) | tj});
             if (P.big[g]) {
                 const int32_t nt2 = (d.npad + kTile2 - 1) / kTile2;
                 for (int32_t ti = 0; ti < nt2; ti++)
@@ -584,6 +610,7 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
             xcd_order(P, P.wave_g[w], P.wave_g[w + 1], tl);
             if (!ts.empty()) xcd_order(P, P.wave_g[w], P.wave_g[w + 1], ts);
             if (!tb.empty()) xcd_order(P, P.wave_g[w], P.wave_g[w + 1], tb);
+            xcd_order(P, P.wave_g[w], P.wave_g[w + 1], td);
         }
         P.tiles.insert(P.tiles.end(), tl.begin(), tl.end());
         P.tile_beg.push_back((int64_t)P.tiles.size());
@@ -591,13 +618,15 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
         P.tiles_s_beg.push_back((int64_t)P.tiles_s.size());
         P.tiles_b.insert(P.tiles_b.end(), tb.begin(), tb.end());
         P.tiles_b_beg.push_back((int64_t)P.tiles_b.size());
+        P.tiles_d.insert(P.tiles_d.end(), td.begin(), td.end());
+        P.tiles_d_beg.push_back((int64_t)P.tiles_d.size());
         while (ch < P.chunks.size() && P.chunks[ch].x < P.wave_g[w + 1]) ch++;
         P.chunk_beg.push_back((int64_t)ch);
     }
     if (nw == 1) {
         // every tile (general products of the adjoint), XCD-ordered
         for (int32_t g = 0; g < ng; g++) {
-            const int32_t nt = (P.gd[g].npad + kTile - 1) / kTile;
+            const int32_t nt = (P.gd[g].npad + P.edge_d - 1) / P.edge_d;
             for (int32_t ti = 0; ti < nt; ti++)
                 for (int32_t tj = 0; tj < nt; tj++) P.tiles_full.push_back(TileDesc{g, (ti << 16) | tj});
         }
@@ -631,6 +660,24 @@ int32_t check_plan(smx_ctx c, const Plan &P)
             const int ti = t.y >> 16, tj = t.y & 0xffff;
             if (tj > ti || ti * kTile >= d.npad) return fail(c, SMX_E_INVALID, "internal: tile index");
         }
+        // lower tiles of the FP64 products: every tile of every group of the wave
+        if ((int32_t)P.tiles_d_beg.size() != nw + 1 || P.tiles_d_beg[nw] != (int64_t)P.tiles_d.size() ||
+            (P.edge_d != 32 && P.edge_d != 64))
+            return fail(c, SMX_E_INVALID, "internal: FP64 tile tables");
+        int64_t nd = 0;
+        for (int64_t q = P.tiles_d_beg[w]; q < P.tiles_d_beg[w + 1]; q++) {
+            const TileDesc &t = P.tiles_d[(size_t)q];
+            if (t.x == -1) continue;
+            if (t.x < P.wave_g[w] || t.x >= P.wave_g[w + 1]) return fail(c, SMX_E_INVALID, "internal: FP64 tile group");
+            const int ti = t.y >> 16, tj = t.y & 0xffff;
+            if (tj > ti || ti * P.edge_d >= P.gd[t.x].npad) return fail(c, SMX_E_INVALID, "internal: FP64 tile index");
+            nd++;
+        }
+        for (int32_t g = P.wave_g[w]; g < P.wave_g[w + 1]; g++) {
+            const int64_t nt = (P.gd[g].npad + P.edge_d - 1) / P.edge_d;
+            nd -= nt * (nt + 1) / 2;
+        }
+        if (nd != 0) return fail(c, SMX_E_INVALID, "internal: FP64 tile count");
         // size-bucket lists: every group of the wave in exactly one of them,
         // with its full set of lower tiles of that shape
         if ((int32_t)P.tiles_s_beg.size() != nw + 1 || (int32_t)P.tiles_b_beg.size() != nw + 1 ||
@@ -676,7 +723,7 @@ int32_t check_plan(smx_ctx c, const Plan &P)
         if (t.x < 0 || t.x >= P.ngroups) return fail(c, SMX_E_INVALID, "internal: tile group");
         const GroupDesc &d = P.gd[t.x];
         const int ti = t.y >> 16, tj = t.y & 0xffff;
-        if (ti * kTile >= d.npad || tj * kTile >= d.npad) return fail(c, SMX_E_INVALID, "internal: tile index");
+        if (ti * P.edge_d >= d.npad || tj * P.edge_d >= d.npad) return fail(c, SMX_E_INVALID, "internal: tile index");
     }
     for (const GroupDesc &d : P.gd) {
         if (d.npad % 16 || d.npad < d.n || d.off < 0 || d.off + (int64_t)d.npad * d.npad > P.work_elems)
@@ -733,7 +780,8 @@ int32_t ensure_plan(smx_ctx c)
         int64_t tiles_est = 0;
         for (const GroupDesc &d : P.gd) {
             const int64_t nt = (d.npad + kTile - 1) / kTile;
-            tiles_est += nt * nt;
+            const int64_t ntd = (d.npad + 63) / 64;     // more than 1536 such tiles, or the estimate is small anyway
+            tiles_est += nt * nt + ntd * ntd;
         }
         const int64_t tables = (int64_t)(vbytes(P.gd) + vbytes(P.chunks) + vbytes(P.rinfo) + vbytes(P.bmap) +
                                          vbytes(P.boffs) + vbytes(P.scat) + vbytes(P.own_list)) +
@@ -761,6 +809,7 @@ int32_t ensure_plan(smx_ctx c)
     HIP_TRY(c, upload(c->d_tiles_sx, P.tiles_sx, c->stream));
     HIP_TRY(c, upload(c->d_xbeg, P.xbeg, c->stream));
     HIP_TRY(c, upload(c->d_tiles_full, P.tiles_full, c->stream));
+    HIP_TRY(c, upload(c->d_tiles_d, P.tiles_d, c->stream));
     HIP_TRY(c, upload(c->d_plist, P.plist, c->stream));
     c->contrib_ready = false;
     HIP_TRY(c, upload(c->d_chunks, P.chunks, c->stream));
@@ -986,6 +1035,7 @@ int32_t smx_destroy(smx_ctx c)
     c->d_bcol.release();
     c->d_gd.release();
     c->d_tiles.release();
+    c->d_tiles_d.release();
     c->d_tiles_s.release();
     c->d_tiles_sx.release();
     c->d_xbeg.release();
@@ -1453,7 +1503,8 @@ bool plan_tables_valid(const Plan &P, int64_t nnzb, int32_t big_tile, std::strin
         }
         return true;
     };
-    if (!tiles_ok(P.tiles, kTile, "tiles") || !tiles_ok(P.tiles_s, kTile, "128-tiles") ||
+    if (!tiles_ok(P.tiles, kTile, "tiles") || !tiles_ok(P.tiles_d, P.edge_d, "FP64 tiles") ||
+        !tiles_ok(P.tiles_s, kTile, "128-tiles") ||
         !tiles_ok(P.tiles_b, big_tile, "256-tiles"))
         return false;
     for (const int2 &ch : P.chunks)
@@ -1524,6 +1575,7 @@ DevView ctx_view(smx_ctx c)
     v.tiles = c->d_tiles.p;
     v.tiles_s = c->d_tiles_s.p;
     v.tiles_b = c->d_tiles_b.p;
+    v.tiles_d = c->d_tiles_d.p;
     v.tiles_sx = c->d_tiles_sx.p;
     v.xbeg = c->d_xbeg.p;
     v.chunks = c->d_chunks.p;
@@ -1658,6 +1710,8 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const int32_t g0 = P.wave_g[wave], wng = P.wave_g[wave + 1] - g0;
         const int ntiles = (int)(P.tile_beg[wave + 1] - P.tile_beg[wave]);
         const TileDesc *tl = V.tiles + P.tile_beg[wave];
+        const int ntd = (int)(P.tiles_d_beg[wave + 1] - P.tiles_d_beg[wave]);
+        const TileDesc *tld = V.tiles_d + P.tiles_d_beg[wave];
         // one- and two-word products: the size buckets (128 x 128 and 256 x 256 tiles)
         const bool buckets = mixed && fmt != 2 && nw <= 2;
         const int nts = (int)(P.tiles_s_beg[wave + 1] - P.tiles_s_beg[wave]);
@@ -1693,21 +1747,21 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
             // (W = (15 I - 10 T + 3 T^2) / 8), update X W.
             if (!mixed) {
                 if (!pade) {
-                    e = run(0, [&] { return launch_ns_f64(s, 0, ntiles, tl, V.gd, xb[k & 1], xb[k & 1], wslab, it, k,
+                    e = run(0, [&] { return launch_ns_f64(s, 0, P.edge_d, ntd, tld, V.gd, xb[k & 1], xb[k & 1], wslab, it, k,
                                                           c->tol, c->max_iter, 0); });
                 } else {
                     double *tt = xb[(k + 1) & 1];
-                    e = run(0, [&] { return launch_ns_f64(s, 5, ntiles, tl, V.gd, xb[k & 1], xb[k & 1], tt, it, k,
+                    e = run(0, [&] { return launch_ns_f64(s, 5, P.edge_d, ntd, tld, V.gd, xb[k & 1], xb[k & 1], tt, it, k,
                                                           c->tol, c->max_iter, 0); });
                     if (e == hipSuccess)
-                        e = run(11, [&] { return launch_ns_f64(s, 6, ntiles, tl, V.gd, tt, tt, wslab, it, k, c->tol,
+                        e = run(11, [&] { return launch_ns_f64(s, 6, P.edge_d, ntd, tld, V.gd, tt, tt, wslab, it, k, c->tol,
                                                                c->max_iter, 0); });
                 }
                 if (e == hipSuccess)
-                    e = run(1, [&] { return launch_ns_f64(s, 1, ntiles, tl, V.gd, xb[k & 1], wslab, xb[(k + 1) & 1],
+                    e = run(1, [&] { return launch_ns_f64(s, 1, P.edge_d, ntd, tld, V.gd, xb[k & 1], wslab, xb[(k + 1) & 1],
                                                           it, k, c->tol, c->max_iter, 0); });
                 if (e == hipSuccess && tangent)
-                    e = run(6, [&] { return launch_ns_f64(s, 2, ntiles, tl, V.gd, tb[k & 1], wslab, tb[(k + 1) & 1],
+                    e = run(6, [&] { return launch_ns_f64(s, 2, P.edge_d, ntd, tld, V.gd, tb[k & 1], wslab, tb[(k + 1) & 1],
                                                           it, k, c->tol, c->max_iter, 0); });
             } else {
                 // one launch per size bucket and product (one bucket of all
@@ -1963,7 +2017,7 @@ int32_t eig_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView &
 // context memory allocated by earlier calls.
 struct StaticLayout {
     int64_t gd = 0, tiles = 0, chunks = 0, rinfo = 0, bmap = 0, boffs = 0, scat = 0, own = 0, plist = 0;
-    int64_t tiles_s = 0, tiles_b = 0;
+    int64_t tiles_s = 0, tiles_b = 0, tiles_d = 0;
     int64_t scale = 0, resid = 0, done = 0, kfinal = 0, flags = 0, ndone = 0, tdiag = 0, tau_hist = 0;
     int64_t pe = 0, pn = 0, arena = 0, pool = 0, end = 0;
 };
@@ -1985,6 +2039,7 @@ StaticLayout static_layout(smx_ctx c, const Plan &P, int32_t stride)
     L.tiles = take(vbytes(P.tiles));
     L.tiles_s = take(vbytes(P.tiles_s));
     L.tiles_b = take(vbytes(P.tiles_b));
+    L.tiles_d = take(vbytes(P.tiles_d));
     L.chunks = take(vbytes(P.chunks));
     L.rinfo = take(vbytes(P.rinfo));
     L.bmap = take(vbytes(P.bmap));
@@ -2105,6 +2160,7 @@ int32_t smx_evaluate_static(smx_ctx c)
             HIP_TRY(c, upload_to(base, L.tiles, P.tiles, st));
             HIP_TRY(c, upload_to(base, L.tiles_s, P.tiles_s, st));
             HIP_TRY(c, upload_to(base, L.tiles_b, P.tiles_b, st));
+            HIP_TRY(c, upload_to(base, L.tiles_d, P.tiles_d, st));
             HIP_TRY(c, upload_to(base, L.chunks, P.chunks, st));
             HIP_TRY(c, upload_to(base, L.rinfo, P.rinfo, st));
             HIP_TRY(c, upload_to(base, L.bmap, P.bmap, st));
@@ -2121,6 +2177,7 @@ int32_t smx_evaluate_static(smx_ctx c)
     V.tiles = reinterpret_cast<const TileDesc *>(base + L.tiles);
     V.tiles_s = reinterpret_cast<const TileDesc *>(base + L.tiles_s);
     V.tiles_b = reinterpret_cast<const TileDesc *>(base + L.tiles_b);
+    V.tiles_d = reinterpret_cast<const TileDesc *>(base + L.tiles_d);
     V.chunks = reinterpret_cast<const int2 *>(base + L.chunks);
     V.rinfo = reinterpret_cast<const RowInfo *>(base + L.rinfo);
     V.bmap = reinterpret_cast<const int32_t *>(base + L.bmap);
@@ -2360,7 +2417,7 @@ int32_t smx_get_stats(smx_ctx c, smx_stats *out)
     s.time_total_ms = ms;
     double ws = 0;
     for (size_t b : {c->d_k.bytes(), c->d_d.bytes(), c->d_arena.bytes(), c->d_tpool.bytes(), c->d_tx0.bytes(), c->d_tx1.bytes(), c->d_adj.bytes(), c->d_bmap.bytes(),
-                     c->d_rinfo.bytes(), c->d_scat.bytes(), c->d_resid.bytes(), c->d_tiles.bytes(),
+                     c->d_rinfo.bytes(), c->d_scat.bytes(), c->d_resid.bytes(), c->d_tiles.bytes(), c->d_tiles_d.bytes(),
                      c->d_tiles_full.bytes(), c->d_plist.bytes(), c->ws_ptr ? c->ws_bytes : (size_t)0})
         ws += (double)b;
     s.workspace_bytes = ws;
@@ -3012,8 +3069,8 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     it.tau_hist = c->d_tau_hist.p;
     it.resid_stride = c->last_stride;
     const int scratch_slot = c->last_max_iter + 1;    // residual slot the adjoint squares may use
-    const int nt = (int)P.tiles.size(), ntf = (int)P.tiles_full.size();
-    const TileDesc *tl = c->d_tiles.p, *tf = c->d_tiles_full.p;
+    const int nt = (int)P.tiles_d.size(), ntf = (int)P.tiles_full.size();
+    const TileDesc *tl = c->d_tiles_d.p, *tf = c->d_tiles_full.p;
 
     // seed: Xbar_K = sym(-1/2 dL/dD at the own-column stored positions)
     HIP_TRY(c, hipMemsetAsync(xb, 0, sizeof(double) * (size_t)E, st));
@@ -3040,8 +3097,8 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     HIP_TRY(c, hipMemcpyAsync(cp(0), seg[0], sizeof(double) * (size_t)E, hipMemcpyDeviceToDevice, st));
     auto fwd_step = [&](int k, const double *x, double *xnext) -> int32_t {
         it.kact = k;
-        HIP_TRY(c, launch_ns_f64(st, 0, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-        HIP_TRY(c, launch_ns_f64(st, 1, nt, tl, c->d_gd.p, x, wb, xnext, it, scratch_slot, 0.0, c->last_max_iter, 1));
+        HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
+        HIP_TRY(c, launch_ns_f64(st, 1, P.edge_d, nt, tl, c->d_gd.p, x, wb, xnext, it, scratch_slot, 0.0, c->last_max_iter, 1));
         return SMX_OK;
     };
     const int32_t mlast = (kmax > 0) ? (kmax - 1) / kSeg : 0;
@@ -3063,10 +3120,10 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
         for (int32_t k = khi; k >= m * kSeg; k--) {
             const double *x = seg[k - m * kSeg];
             it.kact = k;
-            HIP_TRY(c, launch_ns_f64(st, 0, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 4, ntf, tf, c->d_gd.p, xb, wb, zb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 4, ntf, tf, c->d_gd.p, xb, x, yb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 3, nt, tl, c->d_gd.p, x, yb, xb, it, scratch_slot, 0.0, c->last_max_iter, 1,
+            HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
+            HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, ntf, tf, c->d_gd.p, xb, wb, zb, it, scratch_slot, 0.0, c->last_max_iter, 1));
+            HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, ntf, tf, c->d_gd.p, xb, x, yb, it, scratch_slot, 0.0, c->last_max_iter, 1));
+            HIP_TRY(c, launch_ns_f64(st, 3, P.edge_d, nt, tl, c->d_gd.p, x, yb, xb, it, scratch_slot, 0.0, c->last_max_iter, 1,
                                      zb));
         }
     }

@@ -132,7 +132,8 @@ hipError_t launch_gather(hipStream_t st, int nchunks, const int2 *chunks, const 
 //         and b general; every tile of the group is listed.
 // mode 5 (Pade square): T = a^2 X X stored, residual as mode 0.
 // mode 6 (Pade combine): out = (15 I - 10 x + 3 x x) / 8 with x = b = T.
-hipError_t launch_ns_f64(hipStream_t st, int mode, int ntiles, const TileDesc *tiles,
+// edge: tile edge of the list (32 or 64).
+hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
                          const GroupDesc *groups, const double *x, const double *b, double *out,
                          const IterState &it, int k, double tol, int max_iter, int polish,
                          const double *aux = nullptr);

@@ -16,16 +16,29 @@
 //
 // Every iterate is a polynomial in the symmetric A_g, so X, T and W are
 // symmetric and X W = W X.  Each workgroup therefore computes one
-// lower-triangle 128 x 128 tile and writes it twice (tile and mirror); both
-// operands are read as columns (A(i, k) = X(k, i)), which keeps every global
-// load contiguous along k.
+// lower-triangle tile and writes it twice (tile and mirror); both operands are
+// read as columns (A(i, k) = X(k, i)), which keeps every global load
+// contiguous along k.
 //
-// Workgroup: 256 threads = 4 waves in a 2 x 2 arrangement, each wave owns a
-// 64 x 64 sub-tile = 4 x 4 blocks of v_mfma_f64_16x16x4_f64.  K is staged
-// through LDS in steps of 16 with double buffering.  Inside a 16-step the
-// k index handed to the matrix core is permuted (lane group q, sub-step t ->
-// k = 4q + t) so each lane's four operand values are contiguous in LDS; the
-// same permutation is applied to both operands, so the sum is unchanged.
+// Workgroup: 256 threads = 4 waves in a 2 x 2 arrangement, each wave owns
+// WB x WB blocks of v_mfma_f64_16x16x4_f64, so a tile has an edge of 32 WB.
+// K is staged through LDS in steps of 16 with double buffering; the loads run
+// two steps ahead in two register sets.  Inside a 16-step the k index handed to
+// the matrix core is permuted (lane group q, sub-step t -> k = 4q + t) so each
+// lane's four operand values are contiguous in LDS; the same permutation is
+// applied to both operands, so the sum is unchanged.  The order of the sum does
+// not depend on the tile edge: results are bitwise the same.
+//
+// What bounds it: the FP64 matrix pipe (one product occupies it for 64 cycles).
+// Edge 64 puts four workgroups on a CU, whose waves fill each other's barrier
+// and epilogue times, and its waves skip the padding and the upper half of the
+// diagonal in 32 x 32 pieces.  water1024 (n_g 602-1055), square / update per
+// launch: edge 128, two workgroups per CU and loads under a column condition
+// (the compiler waited for them before the products) 11.7 / 10.9 ms; edge 96
+// 10.9 / 10.4; edge 64 10.1 / 9.6 with loads one step ahead, 9.9 / 9.4 two
+// steps ahead, which is 0.9 of the matrix pipe at 2.4 GHz; edge 32 11.8 / 11.3
+// (one block per wave: each operand value read from LDS feeds one product);
+// edge 64 with K steps of 32 12.2 / 11.0 (two workgroups per CU).
 #include "smx_internal.h"
 
 namespace smx {
@@ -35,7 +48,6 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = kTile;      // 128
 constexpr int BK = 16;
 constexpr int SK = BK + 2;     // LDS row stride in doubles (breaks bank aliasing)
 
@@ -45,13 +57,15 @@ __device__ inline double wave_max(double v)
     return v;
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256, 2)
+template <int MODE, int WB>
+__global__ __launch_bounds__(256, 4)
 void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
                    const double *__restrict__ xin, const double *__restrict__ bin,
                    double *__restrict__ out, IterState it, int k, double tol, int max_iter, int polish,
                    const double *__restrict__ aux)
 {
+    constexpr int BM = 32 * WB;        // tile edge: 2 x 2 waves of WB x WB blocks of 16 x 16
+    constexpr int WE = 16 * WB;        // edge of a wave's part of the tile
     __shared__ double As[2][BM][SK];
     __shared__ double Bs[2][BM][SK];
 
@@ -96,74 +110,87 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     const int wr = wave >> 1, wc = wave & 1;
 
     // global -> LDS staging: a K step is 16 k = 128 B per tile column, i.e. eight
-    // 16-B chunks.  Chunk q*256 + tid (q = 0..3) is column 32 q + tid/8, part
-    // tid%8: eight consecutive lanes read one full cache line.
+    // 16-B chunks.  Chunk q*256 + tid (q < WB) is column 32 q + tid/8, part
+    // tid%8: eight consecutive lanes read one full cache line.  Every lane
+    // loads (columns beyond ld read column ld - 1, whose products reach only
+    // outputs that are not stored): under a branch the compiler waits for the
+    // loads where the paths join, before the products they should overlap.
     const int part = tid & 7;
     const int col8 = tid >> 3;
-    const double *pa = xin + gd.off + (int64_t)(ti * BM + col8) * ld + part * 2;
-    const double *pb = bin + gd.off + (int64_t)(tj * BM + col8) * ld + part * 2;
-    const int64_t col_stride = (int64_t)32 * ld;
+    const double *pa[WB], *pb[WB];
+#pragma unroll
+    for (int q = 0; q < WB; q++) {
+        pa[q] = xin + gd.off + (int64_t)min(ti * BM + 32 * q + col8, ld - 1) * ld + part * 2;
+        pb[q] = bin + gd.off + (int64_t)min(tj * BM + 32 * q + col8, ld - 1) * ld + part * 2;
+    }
 
-    // waves whose 64 x 64 sub-tile lies wholly in the padding, or strictly
+    // waves whose part of the tile lies wholly in the padding, or strictly
     // above the diagonal of a diagonal tile (never stored), skip the math
-    const int row_w = ti * BM + wr * 64, col_w = tj * BM + wc * 64;
+    const int row_w = ti * BM + wr * WE, col_w = tj * BM + wc * WE;
     const bool wave_live = (row_w < ld) && (col_w < ld) && (MODE == 4 || !(ti == tj && wr < wc));
 
-    d4 acc[4][4];
+    d4 acc[WB][WB];
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+    for (int i = 0; i < WB; i++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < WB; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
-    d2 ra[4], rb[4];
-    const d2 z2 = {0.0, 0.0};
-    auto gload = [&](int k0) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            ra[q] = (ti * BM + 32 * q + col8 < ld) ? *reinterpret_cast<const d2 *>(pa + q * col_stride + k0) : z2;
-            rb[q] = (tj * BM + 32 * q + col8 < ld) ? *reinterpret_cast<const d2 *>(pb + q * col_stride + k0) : z2;
-        }
-    };
-    auto sstore = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            *reinterpret_cast<d2 *>(&As[buf][32 * q + col8][part * 2]) = ra[q];
-            *reinterpret_cast<d2 *>(&Bs[buf][32 * q + col8][part * 2]) = rb[q];
-        }
-    };
-
+    d2 r0[2 * WB], r1[2 * WB];         // two K steps in flight
     const int nk = ld / BK;
-    gload(0);
-    sstore(0);
-    __syncthreads();
-
+    auto gload = [&](int kt, d2 (&r)[2 * WB]) {
+        const int kk = min(kt, nk - 1) * BK;
+#pragma unroll
+        for (int q = 0; q < WB; q++) {
+            r[q] = *reinterpret_cast<const d2 *>(pa[q] + kk);
+            r[WB + q] = *reinterpret_cast<const d2 *>(pb[q] + kk);
+        }
+    };
+    auto sstore = [&](int buf, const d2 (&r)[2 * WB]) {
+#pragma unroll
+        for (int q = 0; q < WB; q++) {
+            *reinterpret_cast<d2 *>(&As[buf][32 * q + col8][part * 2]) = r[q];
+            *reinterpret_cast<d2 *>(&Bs[buf][32 * q + col8][part * 2]) = r[WB + q];
+        }
+    };
     const int li = lane & 15;
     const int lq = (lane >> 4) * 4;
-    for (int kt = 0; kt < nk; kt++) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) gload((kt + 1) * BK);
-        if (wave_live) {
-            d4 av[4], bv[4];
+    auto products = [&](int buf) {
+        if (!wave_live) return;
+        d4 av[WB], bv[WB];
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const double *sa = &As[buf][wr * 64 + i * 16 + li][lq];
-                const double *sb = &Bs[buf][wc * 64 + i * 16 + li][lq];
-                const d2 a0 = *reinterpret_cast<const d2 *>(sa);
-                const d2 a1 = *reinterpret_cast<const d2 *>(sa + 2);
-                const d2 b0 = *reinterpret_cast<const d2 *>(sb);
-                const d2 b1 = *reinterpret_cast<const d2 *>(sb + 2);
-                av[i] = d4{a0.x, a0.y, a1.x, a1.y};
-                bv[i] = d4{b0.x, b0.y, b1.x, b1.y};
-            }
-#pragma unroll
-            for (int t = 0; t < 4; t++)
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-#pragma unroll
-                    for (int j = 0; j < 4; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][t], bv[j][t], acc[i][j], 0, 0, 0);
+        for (int i = 0; i < WB; i++) {
+            const double *sa = &As[buf][wr * WE + i * 16 + li][lq];
+            const double *sb = &Bs[buf][wc * WE + i * 16 + li][lq];
+            const d2 a0 = *reinterpret_cast<const d2 *>(sa);
+            const d2 a1 = *reinterpret_cast<const d2 *>(sa + 2);
+            const d2 b0 = *reinterpret_cast<const d2 *>(sb);
+            const d2 b1 = *reinterpret_cast<const d2 *>(sb + 2);
+            av[i] = d4{a0.x, a0.y, a1.x, a1.y};
+            bv[i] = d4{b0.x, b0.y, b1.x, b1.y};
         }
-        if (kt + 1 < nk) sstore(buf ^ 1);
+#pragma unroll
+        for (int t = 0; t < 4; t++)
+#pragma unroll
+            for (int i = 0; i < WB; i++)
+#pragma unroll
+                for (int j = 0; j < WB; j++)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[i][t], bv[j][t], acc[i][j], 0, 0, 0);
+    };
+    // step kt: the loads of step kt + 2 go out, the products of step kt run from
+    // LDS, and step kt + 1 (loaded one step earlier) is stored for the next
+    gload(0, r0);
+    gload(1, r1);
+    sstore(0, r0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {
+        gload(kt + 2, r0);
+        products(0);
+        sstore(1, r1);
+        __syncthreads();
+        if (kt + 1 >= nk) break;
+        gload(kt + 3, r1);
+        products(1);
+        sstore(0, r0);
         __syncthreads();
     }
 
@@ -182,9 +209,9 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     const bool pad_fix = (k == 0 && !polish && reads_x0);
     double rmax = 0.0;
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
+    for (int i = 0; i < WB; i++) {
 #pragma unroll
-        for (int j = 0; j < 4; j++) {
+        for (int j = 0; j < WB; j++) {
             const int c = col_w + j * 16 + li;
 #pragma unroll
             for (int v = 0; v < 4; v++) {
@@ -240,13 +267,15 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
 
 }  // namespace
 
-hipError_t launch_ns_f64(hipStream_t st, int mode, int ntiles, const TileDesc *tiles,
-                         const GroupDesc *groups, const double *x, const double *b, double *out,
-                         const IterState &it, int k, double tol, int max_iter, int polish, const double *aux)
+namespace {
+
+template <int WB>
+hipError_t launch_wb(hipStream_t st, int mode, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+                     const double *x, const double *b, double *out, const IterState &it, int k, double tol,
+                     int max_iter, int polish, const double *aux)
 {
-    if (ntiles <= 0) return hipSuccess;
 #define SMX_NS_LAUNCH(M)                                                                                    \
-    hipLaunchKernelGGL(ns_f64_kernel<M>, dim3(ntiles), dim3(256), 0, st, tiles, groups, x, b, out, it, k, tol, \
+    hipLaunchKernelGGL((ns_f64_kernel<M, WB>), dim3(ntiles), dim3(256), 0, st, tiles, groups, x, b, out, it, k, tol, \
                        max_iter, polish, aux)
     switch (mode) {
     case 0: SMX_NS_LAUNCH(0); break;
@@ -260,6 +289,20 @@ hipError_t launch_ns_f64(hipStream_t st, int mode, int ntiles, const TileDesc *t
     }
 #undef SMX_NS_LAUNCH
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
+                         const GroupDesc *groups, const double *x, const double *b, double *out,
+                         const IterState &it, int k, double tol, int max_iter, int polish, const double *aux)
+{
+    if (ntiles <= 0) return hipSuccess;
+    switch (edge) {
+    case 32: return launch_wb<1>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, aux);
+    case 64: return launch_wb<2>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, aux);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace smx
