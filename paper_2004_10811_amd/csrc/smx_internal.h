@@ -126,17 +126,16 @@ hipError_t launch_gather(hipStream_t st, int nchunks, const int2 *chunks, const 
 // polish != 0: unconditional step on every group (a = 1, no skipping, no
 // stopping); the square's residual goes to slot k of the residual history.
 // With it.kfix set, a group stops exactly at step kfix[g] (frozen iteration).
-// mode 3 (adjoint step, lower tiles): acc = X Y; out = Xb is updated in place to
-//         -1.5 Xb + Z + Z^T - 0.5 acc with Z = aux (= Xb W).
-// mode 4 (full tiles, plain product): out = x b with x symmetric (read by columns)
-//         and b general; every tile of the group is listed.
+// mode 3 (tangent of the square): out = -0.5 (x b + x2 b2), with x = b2 = X, b = x2 = Xd;
+// mode 4 (tangent of the update): out = x b + x2 b2, with x = Xd, b = W, x2 = X, b2 = Wd.
+// (All operands symmetric; the sums of the two products are symmetric too.)
 // mode 5 (Pade square): T = a^2 X X stored, residual as mode 0.
 // mode 6 (Pade combine): out = (15 I - 10 x + 3 x x) / 8 with x = b = T.
 // edge: tile edge of the list (32 or 64).
 hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
                          const GroupDesc *groups, const double *x, const double *b, double *out,
                          const IterState &it, int k, double tol, int max_iter, int polish,
-                         const double *aux = nullptr);
+                         const double *x2 = nullptr, const double *b2 = nullptr);
 
 // ---- adjoint helpers ------------------------------------------------------
 // xb (zeroed) at the own-column stored positions: -1/2 (gE K + gN I_diag + gD).
@@ -149,13 +148,15 @@ hipError_t launch_symmetrize(hipStream_t st, int ngroups, int max_npad, const Gr
 hipError_t launch_scale_slab(hipStream_t st, int ngroups, int max_npad, const GroupDesc *groups,
                              const unsigned long long *scale_bits, double *x);
 // dK[p] = ge D[p] + sum over the contributions (g, oi, oj) of block p of Xb_g[oi.., oj..] / s_g,
-// in list order; part[g] = -sum_i Xb_g[i, i] / s_g (the mu derivative).
+// in list order; part[g] = -sum_i Xb_g[i, i] / s_g (the mu derivative).  Xb_g is in xb0 or xb1
+// by the parity of kfix[g].
 hipError_t launch_gather_t(hipStream_t st, int64_t nblocks, const int64_t *cptr, const int4 *contrib,
                            const int64_t *valoff, const int32_t *brow, const int32_t *bcol,
-                           const GroupDesc *groups, const unsigned long long *scale_bits, const double *xb,
-                           const double *dvals, double ge, double *dk);
+                           const GroupDesc *groups, const unsigned long long *scale_bits, const int32_t *kfix,
+                           const double *xb0, const double *xb1, const double *dvals, double ge, double *dk);
 hipError_t launch_diag_part(hipStream_t st, int ngroups, const GroupDesc *groups,
-                            const unsigned long long *scale_bits, const double *xb, double *part);
+                            const unsigned long long *scale_bits, const int32_t *kfix, const double *xb0,
+                            const double *xb1, double *part);
 
 // Word storage of the reduced-precision iterates (nw 16-bit words per value):
 // group g's words start at element nw * off of an operand buffer; inside them

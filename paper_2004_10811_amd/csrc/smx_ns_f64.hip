@@ -13,6 +13,10 @@
 //   mode 5 ("Pade square"):  T = a^2 X_k X_k and its residual, as mode 0, T stored;
 //   mode 6 ("Pade combine"): W = (15 I - 10 T + 3 T T) / 8 (T read at the output position);
 //   mode 1 ("update") as above.
+// The derivative of a Newton-Schulz step in a symmetric direction Xd takes two
+// products of two operand pairs each, one pair's K range after the other's:
+//   mode 3 ("square tangent"): Wd = -0.5 (X Xd + Xd X);
+//   mode 4 ("update tangent"): Xd_{k+1} = Xd W + X Wd.
 //
 // Every iterate is a polynomial in the symmetric A_g, so X, T and W are
 // symmetric and X W = W X.  Each workgroup therefore computes one
@@ -62,7 +66,7 @@ __global__ __launch_bounds__(256, 4)
 void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
                    const double *__restrict__ xin, const double *__restrict__ bin,
                    double *__restrict__ out, IterState it, int k, double tol, int max_iter, int polish,
-                   const double *__restrict__ aux)
+                   const double *__restrict__ x2, const double *__restrict__ b2)
 {
     constexpr int BM = 32 * WB;        // tile edge: 2 x 2 waves of WB x WB blocks of 16 x 16
     constexpr int WE = 16 * WB;        // edge of a wave's part of the tile
@@ -127,7 +131,7 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     // waves whose part of the tile lies wholly in the padding, or strictly
     // above the diagonal of a diagonal tile (never stored), skip the math
     const int row_w = ti * BM + wr * WE, col_w = tj * BM + wc * WE;
-    const bool wave_live = (row_w < ld) && (col_w < ld) && (MODE == 4 || !(ti == tj && wr < wc));
+    const bool wave_live = (row_w < ld) && (col_w < ld) && !(ti == tj && wr < wc);
 
     d4 acc[WB][WB];
 #pragma unroll
@@ -136,13 +140,19 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
         for (int j = 0; j < WB; j++) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
     d2 r0[2 * WB], r1[2 * WB];         // two K steps in flight
-    const int nk = ld / BK;
+    constexpr bool dual = MODE == 3 || MODE == 4;    // a second operand pair follows the first
+    const int nk1 = ld / BK, nk = dual ? 2 * nk1 : nk1;
     auto gload = [&](int kt, d2 (&r)[2 * WB]) {
-        const int kk = min(kt, nk - 1) * BK;
+        kt = min(kt, nk - 1);
+        int64_t ka = (int64_t)kt * BK, kb = ka;
+        if (dual && kt >= nk1) {
+            ka += (x2 - xin) - ld;
+            kb += (b2 - bin) - ld;
+        }
 #pragma unroll
         for (int q = 0; q < WB; q++) {
-            r[q] = *reinterpret_cast<const d2 *>(pa[q] + kk);
-            r[WB + q] = *reinterpret_cast<const d2 *>(pb[q] + kk);
+            r[q] = *reinterpret_cast<const d2 *>(pa[q] + ka);
+            r[WB + q] = *reinterpret_cast<const d2 *>(pb[q] + kb);
         }
     };
     auto sstore = [&](int buf, const d2 (&r)[2 * WB]) {
@@ -236,19 +246,11 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
                     // tangent: 3 Xd W - 3 Xd (Xd and W commute, so the product is symmetric)
                     val = (r < ld && c < ld) ? 3.0 * acc[i][j][v] - 3.0 * xin[gd.off + r + (int64_t)c * ld] : 0.0;
                 } else if (MODE == 3) {
-                    // adjoint step: Xb_k = -1.5 Xb + Z + Z^T - 0.5 X (Xb X), Z = Xb W
-                    val = 0.0;
-                    if (r < ld && c < ld && r >= c)
-                        val = -1.5 * og[r + (int64_t)c * ld] + aux[gd.off + r + (int64_t)c * ld] +
-                              aux[gd.off + c + (int64_t)r * ld] - 0.5 * acc[i][j][v];
+                    val = -0.5 * acc[i][j][v];
                 } else {
                     val = acc[i][j][v];
                 }
                 if (pad_fix && (r >= n || c >= n)) val = (r == c) ? 1.0 : 0.0;
-                if (MODE == 4) {
-                    if (r < ld && c < ld) og[r + (int64_t)c * ld] = val;
-                    continue;
-                }
                 if (r < ld && c < ld && r >= c) {
                     og[r + (int64_t)c * ld] = val;
                     if (r > c) og[c + (int64_t)r * ld] = val;
@@ -272,11 +274,11 @@ namespace {
 template <int WB>
 hipError_t launch_wb(hipStream_t st, int mode, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
                      const double *x, const double *b, double *out, const IterState &it, int k, double tol,
-                     int max_iter, int polish, const double *aux)
+                     int max_iter, int polish, const double *x2, const double *b2)
 {
 #define SMX_NS_LAUNCH(M)                                                                                    \
     hipLaunchKernelGGL((ns_f64_kernel<M, WB>), dim3(ntiles), dim3(256), 0, st, tiles, groups, x, b, out, it, k, tol, \
-                       max_iter, polish, aux)
+                       max_iter, polish, x2, b2)
     switch (mode) {
     case 0: SMX_NS_LAUNCH(0); break;
     case 1: SMX_NS_LAUNCH(1); break;
@@ -295,12 +297,13 @@ hipError_t launch_wb(hipStream_t st, int mode, int ntiles, const TileDesc *tiles
 
 hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
                          const GroupDesc *groups, const double *x, const double *b, double *out,
-                         const IterState &it, int k, double tol, int max_iter, int polish, const double *aux)
+                         const IterState &it, int k, double tol, int max_iter, int polish, const double *x2,
+                         const double *b2)
 {
     if (ntiles <= 0) return hipSuccess;
     switch (edge) {
-    case 32: return launch_wb<1>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, aux);
-    case 64: return launch_wb<2>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, aux);
+    case 32: return launch_wb<1>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
+    case 64: return launch_wb<2>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
     default: return hipErrorInvalidValue;
     }
 }
