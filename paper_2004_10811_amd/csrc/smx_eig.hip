@@ -27,6 +27,8 @@ namespace smx {
 
 namespace {
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 // lanes of the reduction workgroups: two waves per SIMD, so that the
 // compiler may hold 256 registers and keep eight loads per lane in flight in
 // the row dots of A_s v (at 1024 lanes and 128 registers it issued them one
@@ -86,24 +88,233 @@ __device__ inline double row_dot(const double *__restrict__ row, int ld, const d
 constexpr int kPanel = 16;
 constexpr int kTrailCols = 64;      // columns of V and W rows staged per trailing-update pass
 
+// Sum over the 64 lanes of each of 16 values: lane l returns the sum of
+// val[l % 16].  Each of the first four exchanges halves the values a lane
+// carries, so the whole takes 17 exchanges instead of 6 for every value.
+__device__ inline double lane_sums16(const double (&val)[16], int lane)
+{
+    double a[8], b[4], c[2], d;
+#pragma unroll
+    for (int u = 0; u < 8; u++) {
+        const bool hi = lane & 8;
+        a[u] = (hi ? val[u + 8] : val[u]) + __shfl_xor(hi ? val[u] : val[u + 8], 8, 64);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const bool hi = lane & 4;
+        b[u] = (hi ? a[u + 4] : a[u]) + __shfl_xor(hi ? a[u] : a[u + 4], 4, 64);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+        const bool hi = lane & 2;
+        c[u] = (hi ? b[u + 2] : b[u]) + __shfl_xor(hi ? b[u] : b[u + 2], 2, 64);
+    }
+    {
+        const bool hi = lane & 1;
+        d = (hi ? c[1] : c[0]) + __shfl_xor(hi ? c[0] : c[1], 1, 64);
+    }
+    d += __shfl_xor(d, 16, 64);
+    d += __shfl_xor(d, 32, 64);
+    return d;
+}
+
+// A_s v from the lower triangle alone, rows and columns k0 .. n - 1 (vs is
+// zero outside [k0, n)): an element a_ij (i > j) adds a v_j to row i and a v_i
+// to row j.  A wave takes strips of 16 columns and runs down each in pieces of
+// 64 rows; the column sums stay in registers until the strip's end, the row
+// sums go to the wave's own acc[wave][.], which starts at zero (the caller adds
+// the waves' sums in order).  Strips go to the waves back and forth, so that
+// each wave gets about the same number of pieces.  A piece's 16 loads are in
+// flight while the previous piece is worked on (two register sets in turn,
+// loads unconditional: rows and columns beyond n read the last one).
+template <int NR>
+__device__ inline void sym_mv(const double *__restrict__ A, int ld, int n, int k0, const double *vs,
+                              double (*acc)[NR], int lane, int wave)
+{
+    constexpr int NWV = kEigBlock / 64;
+    const int nch = (n + 63) / 64, nst = (n + 15) / 16;
+    int round = 0, s = k0 / 16 + wave, c = s >> 2;
+    if (s >= nst) return;
+    auto load = [&](int ss, int cc, double (&r)[16]) {
+        const unsigned row = (unsigned)min(64 * cc + lane, n - 1);
+#pragma unroll
+        for (int u = 0; u < 16; u++) r[u] = (A + (int64_t)min(16 * ss + u, n - 1) * ld)[row];
+    };
+    double vj[16], col[16];
+    auto begin = [&](int ss) {
+#pragma unroll
+        for (int u = 0; u < 16; u++) {
+            vj[u] = vs[16 * ss + u];
+            col[u] = 0.0;
+        }
+    };
+    // one piece; `last`: no piece follows.  Returns false after the last one.
+    auto step = [&](const double (&cur)[16], double (&nxt)[16]) -> bool {
+        int s2 = s, c2 = c + 1, round2 = round;
+        if (c2 >= nch) {                               // next strip of this wave
+            round2++;
+            s2 = k0 / 16 + round2 * NWV + ((round2 & 1) ? NWV - 1 - wave : wave);
+            if (s2 >= nst && !(round2 & 1)) s2 = nst;
+            c2 = s2 >> 2;
+        }
+        const bool last = s2 >= nst;
+        load(last ? s : s2, last ? c : c2, nxt);
+        const int i = 64 * c + lane;
+        const double vi = vs[i];
+        double y0 = 0.0, y1 = 0.0;
+        if (c > (s >> 2)) {
+#pragma unroll
+            for (int u = 0; u < 16; u += 2) {
+                y0 += cur[u] * vj[u];
+                y1 += cur[u + 1] * vj[u + 1];
+                col[u] += cur[u] * vi;
+                col[u + 1] += cur[u + 1] * vi;
+            }
+        } else {                                       // the piece meets the diagonal
+#pragma unroll
+            for (int u = 0; u < 16; u++) {
+                const int j = 16 * s + u;
+                y0 += i >= j ? cur[u] * vj[u] : 0.0;
+                col[u] += i > j ? cur[u] * vi : 0.0;
+            }
+        }
+        acc[wave][i] += y0 + y1;
+        if (s2 != s || last) {
+            const double sum = lane_sums16(col, lane);
+            if (lane < 16) acc[wave][16 * s + lane] += sum;
+            if (!last) begin(s2);
+        }
+        s = s2;
+        c = c2;
+        round = round2;
+        return !last;
+    };
+    double ra[16], rb[16];
+    load(s, c, ra);
+    begin(s);
+    for (;;) {
+        if (!step(ra, rb)) break;
+        if (!step(rb, ra)) break;
+    }
+}
+
+// Trailing update of a panel, lower triangle from row and column k1 on:
+// A_ij -= sum_q V_iq W_jq + W_iq V_jq, a product of n x 32 blocks [V W] [W V]^T
+// on v_mfma_f64_16x16x4_f64.  The matrix core's row index is the matrix column
+// and its column index the matrix row, so that 16 lanes hold 16 consecutive
+// rows of a column.  Pieces of 64 rows x 16 columns, chunk of rows by chunk; the
+// waves take a chunk's column strips in turn.  nb < 16 (the last panel): the
+// missing columns of V and W count as zero.
+__device__ inline void sym_rank32(double *__restrict__ A, const double *__restrict__ V, const double *__restrict__ W,
+                                  int ld, int n, int k1, int nb, int lane, int wave)
+{
+    constexpr int NWV = kEigBlock / 64;
+    const int li = lane & 15, lq = lane >> 4;
+    const int nch = (n - k1 + 63) / 64;
+    // lane (li, lq), t: column 4 t + lq of [V W] (vw) or [W V] at row r
+    auto frag = [&](const double *__restrict__ F, const double *__restrict__ S, int r, double (&f)[8]) {
+        const int rr = min(r, n - 1);
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+            const int q = (4 * t + lq) & 15;
+            const double v = (t < 4 ? F : S)[rr + (int64_t)min(q, nb - 1) * ld];
+            f[t] = q < nb ? v : 0.0;
+        }
+    };
+    for (int c = 0; c < nch; c++) {
+        const int r0 = k1 + 64 * c;
+        const int ns = min(4 * c + 4, (n - k1 + 15) / 16);     // strips up to the diagonal
+        if (wave >= ns) continue;
+        double q[4][8];
+#pragma unroll
+        for (int b = 0; b < 4; b++) frag(V, W, r0 + 16 * b + li, q[b]);
+        for (int s = wave; s < ns; s += NWV) {
+            double p[8], x[4][4];
+            const int j0 = k1 + 16 * s;
+#pragma unroll
+            for (int b = 0; b < 4; b++)
+#pragma unroll
+                for (int v = 0; v < 4; v++)
+                    x[b][v] = A[min(r0 + 16 * b + li, n - 1) + (int64_t)min(j0 + lq + 4 * v, n - 1) * ld];
+            frag(W, V, j0 + li, p);
+            f64x4 d[4];
+#pragma unroll
+            for (int b = 0; b < 4; b++) d[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int t = 0; t < 8; t++)
+#pragma unroll
+                for (int b = 0; b < 4; b++)
+                    d[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[t], q[b][t], d[b], 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < 4; b++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int i = r0 + 16 * b + li, j = j0 + lq + 4 * v;
+                    if (i < n && j <= i) A[i + (int64_t)j * ld] = x[b][v] - d[b][v];
+                }
+        }
+    }
+}
+
+// sum_q V_iq a_q + W_iq b_q over q < j in order, eight columns of both loaded
+// at a time (columns beyond j read column 0 and count as zero: j >= 1).
+__device__ inline double panel_row(const double *__restrict__ V, const double *__restrict__ W, int ld, int i, int j,
+                                   const double *a, const double *b, double s)
+{
+    for (int q0 = 0; q0 < j; q0 += 8) {
+        double v[8], w[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int64_t o = (int64_t)(q0 + u < j ? q0 + u : 0) * ld;
+            v[u] = V[i + o];
+            w[u] = W[i + o];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (q0 + u < j) s -= v[u] * a[q0 + u] + w[u] * b[q0 + u];
+    }
+    return s;
+}
+
+constexpr int kHalfMaxN = 1280;     // largest n whose eight per-wave sums fit the LDS beside the rest
+
+// HALF: the trailing block is read and kept up to date in its lower triangle
+// only, n <= kHalfMaxN; otherwise in full, larger n.  A launch covers all groups
+// and returns at once from those of the other kind.
+//
+// What bounds it: HBM.  With one group per CU the trailing blocks (5.8 MB each
+// at n = 850) stay in no cache, and A_s v reads them once per step.  water256 at
+// kT = 0.01 (n 700-1053), whole reduction: 130 ms reading the full block, 87 ms
+// from the triangle with the column sums reduced over the lanes for every
+// piece, 72 ms with the column sums kept down a strip, the trailing update on
+// the matrix cores (on the vector units it was bound by its LDS reads of V and
+// W) and the panel's rows and dot products loaded eight at a time.  Of a group
+// of n = 799, A_s v then takes 30 of 47 ms at 23 GB/s per CU, 5.8 TB/s over the
+// chip.  32 groups of n ~ 330 (latency): 10.3, 11.9, 8.7 ms.
+template <bool HALF>
 __global__ __launch_bounds__(kEigBlock)
 void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__restrict__ abase,
                     double *__restrict__ wbase, EigVecs ev)
 {
-    __shared__ double vs[kEigMaxN];
-    __shared__ double ws[kEigMaxN];
+    constexpr int NR = HALF ? kHalfMaxN : kEigMaxN;
+    __shared__ double vs[NR + 64];                    // v; zero outside it
+    __shared__ double ws[NR];
     __shared__ double red[kEigBlock / 64];
     __shared__ double rowk[2 * kPanel];               // V[k, t], W[k, t] of the panel's earlier steps
     __shared__ double dots[2 * kPanel];               // W[:, t]^T v, V[:, t]^T v
-    __shared__ double vwc[kTrailCols][2 * kPanel];    // V[c, t], W[c, t] of a run of trailing columns
-    __shared__ double psum[kEigBlock];                // column-part sums of A_s v
+    __shared__ double vwc[HALF ? 1 : kTrailCols][2 * kPanel];    // V[c, t], W[c, t] of a run of trailing columns
+    __shared__ double psum[HALF ? 1 : kEigBlock];     // column-part sums of A_s v
+    __shared__ double acc[HALF ? kEigBlock / 64 : 1][HALF ? NR : 1];   // the waves' sums of A_s v
     const int g = g0 + blockIdx.x;
     const GroupDesc gd = groups[g];
     const int n = gd.n, ld = gd.npad, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double *A = abase + gd.off;
     double *W = wbase + gd.off;                       // W[:, t] at W + t * ld (kPanel <= 32 <= n_pad)
     double *d = ev.d + gd.rinfo_off, *e = ev.e + gd.rinfo_off, *tau = ev.tau + gd.rinfo_off;
+    if ((n <= kHalfMaxN) != HALF) return;
+    for (int i = tid; i < NR + 64; i += kEigBlock) vs[i] = 0.0;
+    __syncthreads();
     for (int kp = 0; kp + 2 < n; kp += kPanel) {
         const int nb = min(kPanel, n - 2 - kp);
         const double *V = A + (int64_t)kp * ld;       // V[:, t] = A[:, kp + t] below its subdiagonal
@@ -118,12 +329,7 @@ void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__rest
             }
             __syncthreads();
             if (j > 0)
-                for (int i = k + tid; i < n; i += kEigBlock) {
-                    double s = col[i];
-                    for (int q = 0; q < j; q++)
-                        s -= V[i + (int64_t)q * ld] * rowk[kPanel + q] + W[i + (int64_t)q * ld] * rowk[q];
-                    col[i] = s;
-                }
+                for (int i = k + tid; i < n; i += kEigBlock) col[i] = panel_row(V, W, ld, i, j, rowk + kPanel, rowk, col[i]);
             __syncthreads();
             const double x0 = col[k + 1];             // read by every lane before the barrier in
             double part = 0.0;                        // block_sum; lane 0 overwrites it with v_0 below
@@ -145,16 +351,30 @@ void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__rest
                 d[k] = col[k];
                 e[k] = beta;
                 tau[k] = tk;
+                vs[k] = 0.0;                          // sym_mv reads whole 64-row chunks
+            }
+            if constexpr (HALF) {
+                for (int i = ((k + 1) & ~63) + tid; i < ((n + 63) & ~63); i += kEigBlock)
+#pragma unroll
+                    for (int w = 0; w < kEigBlock / 64; w++) acc[w][i] = 0.0;
             }
             __syncthreads();
             double *wj = W + (int64_t)j * ld;
             any = any || tk != 0.0;                   // the same in every lane
             if (tk != 0.0) {
-                // W[:, q]^T v and V[:, q]^T v over rows k + 1 .., one wave per product
+                // W[:, q]^T v and V[:, q]^T v over rows k + 1 .., one wave per product,
+                // eight loads in flight (rows beyond n read row n - 1, where v is zero)
                 for (int q = wave; q < 2 * j; q += kEigBlock / 64) {
                     const double *src = q < j ? W + (int64_t)q * ld : V + (int64_t)(q - j) * ld;
                     double s = 0.0;
-                    for (int i = k + 1 + lane; i < n; i += 64) s += src[i] * vs[i];
+                    for (int i0 = k + 1 + lane; i0 < n; i0 += 512) {
+                        double r[8];
+#pragma unroll
+                        for (int u = 0; u < 8; u++) r[u] = src[min(i0 + 64 * u, n - 1)];
+#pragma unroll
+                        for (int u = 0; u < 8; u++)
+                            if (i0 + 64 * u < n) s += r[u] * vs[i0 + 64 * u];
+                    }
                     s = wave_sum0(s);
                     if (lane == 0) dots[q] = s;
                 }
@@ -165,7 +385,16 @@ void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__rest
                 // kEigBlock / (rows rounded up to 64) parts so every lane streams,
                 // and the parts' sums are added in order
                 const int R = n - k - 1;
-                if (R <= kEigBlock) {
+                if constexpr (HALF) {
+                    sym_mv<NR>(A, ld, n, k + 1, vs, acc, lane, wave);
+                    __syncthreads();
+                    for (int i = k + 1 + tid; i < n; i += kEigBlock) {
+                        double s = 0.0;
+#pragma unroll
+                        for (int w = 0; w < kEigBlock / 64; w++) s += acc[w][i];
+                        ws[i] = tk * panel_row(V, W, ld, i, j, dots, dots + j, s);
+                    }
+                } else if (R <= kEigBlock) {
                     const int RS = (R + 63) & ~63, P = kEigBlock / RS;
                     const int sl = tid % RS, part = tid / RS;
                     if (part < P) {
@@ -182,16 +411,12 @@ void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__rest
                         double s = 0.0;
                         for (int pp = 0; pp < P; pp++) s += psum[pp * RS + sl2];
                         const int i = k + 1 + sl2;
-                        for (int q = 0; q < j; q++)
-                            s -= V[i + (int64_t)q * ld] * dots[q] + W[i + (int64_t)q * ld] * dots[j + q];
-                        ws[i] = tk * s;
+                        ws[i] = tk * panel_row(V, W, ld, i, j, dots, dots + j, s);
                     }
                 } else {
                     for (int i = k + 1 + tid; i < n; i += kEigBlock) {
                         double s = row_dot(A + i, ld, vs, k + 1, n);
-                        for (int q = 0; q < j; q++)
-                            s -= V[i + (int64_t)q * ld] * dots[q] + W[i + (int64_t)q * ld] * dots[j + q];
-                        ws[i] = tk * s;
+                        ws[i] = tk * panel_row(V, W, ld, i, j, dots, dots + j, s);
                     }
                 }
                 __syncthreads();
@@ -206,7 +431,8 @@ void tridiag_kernel(const GroupDesc *__restrict__ groups, int g0, double *__rest
         }
         // trailing block (rows and columns from k1 on): A -= V W^T + W V^T over the panel
         const int k1 = kp + nb;
-        for (int c0 = k1; any && c0 < n; c0 += kTrailCols) {
+        if (HALF && any) sym_rank32(A, V, W, ld, n, k1, nb, lane, wave);
+        for (int c0 = k1; !HALF && any && c0 < n; c0 += kTrailCols) {
             const int ncol = min(kTrailCols, n - c0);
             __syncthreads();
             for (int u = tid; u < kTrailCols * 2 * kPanel; u += kEigBlock) {
@@ -764,13 +990,18 @@ void n_reduce_kernel(int ng, int nmu, const double *__restrict__ part, double *_
 
 }  // namespace
 
-hipError_t launch_eig_tridiag(hipStream_t st, int g0, int ngroups, const GroupDesc *groups, double *a,
+hipError_t launch_eig_tridiag(hipStream_t st, int g0, int ngroups, int max_npad, const GroupDesc *groups, double *a,
                               double *wpanel, const EigVecs &ev)
 {
     if (ngroups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(tridiag_kernel, dim3((unsigned)ngroups), dim3(kEigBlock), 0, st, groups, g0, a, wpanel, ev);
+    hipLaunchKernelGGL(tridiag_kernel<true>, dim3((unsigned)ngroups), dim3(kEigBlock), 0, st, groups, g0, a, wpanel, ev);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (max_npad > kHalfMaxN) {
+        hipLaunchKernelGGL(tridiag_kernel<false>, dim3((unsigned)ngroups), dim3(kEigBlock), 0, st, groups, g0, a, wpanel, ev);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(split_kernel, dim3((unsigned)((ngroups + 63) / 64)), dim3(64), 0, st, groups, g0, ngroups, ev);
     return hipGetLastError();
 }
