@@ -1879,7 +1879,8 @@ EigVecs eig_vecs(smx_ctx c)
 
 // Decompose the groups of one wave at the context's mu: gather A_g - mu I
 // into slab 0 (and its Gershgorin norm), tridiagonalise (reflectors stay in
-// slab 0), eigenvalues and eigenvectors of T (slab 1, slab 2 as scratch),
+// slab 0), eigenvalues and eigenvectors of T (slab 1, slab 2 as scratch, then
+// the reflectors' triangular factors, which stay there),
 // Y = Q^T E (thin block 0), C = S^T Y (thin block 1) with the weights and the
 // unshifted eigenvalues.
 int32_t eig_decompose_wave(smx_ctx c, const Plan &P, const DevView &V, double *arena, double *pool, int32_t wave,
@@ -1913,7 +1914,8 @@ int32_t eig_decompose_wave(smx_ctx c, const Plan &P, const DevView &V, double *a
     }
     HIP_TRY(c, launch_eig_values_vectors(st, g0, wng, P.max_npad, V.gd, ev, s, scr));
     HIP_TRY(c, launch_eig_own_select(st, g0, wng, P.max_npad, P.max_own, V.gd, V.own, y));
-    HIP_TRY(c, launch_eig_reflect(st, 1, g0, wng, P.max_own, V.gd, a, ev, y));
+    HIP_TRY(c, launch_eig_wy(st, g0, wng, P.max_npad, V.gd, a, ev, scr));      // the vectors' scratch is free again
+    HIP_TRY(c, launch_eig_reflect(st, 1, g0, wng, P.max_npad, P.max_own, V.gd, a, scr, y));
     HIP_TRY(c, launch_eig_thin(st, 0, g0, wng, P.max_npad, P.max_own, V.gd, ev, s, y, cb, c->mu, 0.0, c->kT, V.scale));
     return SMX_OK;
 }
@@ -1931,7 +1933,7 @@ int32_t eig_apply_wave(smx_ctx c, const Plan &P, const DevView &V, double *arena
     double *cb = pool + P.thin_elems, *z = pool + 2 * P.thin_elems;
     const EigVecs ev = eig_vecs(c);
     HIP_TRY(c, launch_eig_thin(st, 1, g0, wng, P.max_npad, P.max_own, V.gd, ev, s, cb, z, c->mu, dmu, c->kT, V.scale));
-    HIP_TRY(c, launch_eig_reflect(st, 0, g0, wng, P.max_own, V.gd, a, ev, z));
+    HIP_TRY(c, launch_eig_reflect(st, 0, g0, wng, P.max_npad, P.max_own, V.gd, a, arena + 2 * E, z));
     IterState it{};
     it.scale_bits = V.scale;
     it.kfinal = V.kfinal;

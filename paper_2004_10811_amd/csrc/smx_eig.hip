@@ -34,7 +34,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // the row dots of A_s v (at 1024 lanes and 128 registers it issued them one
 // at a time)
 constexpr int kEigBlock = 512;
-constexpr int kReflBlock = 512;     // lanes of the reflector workgroups (two waves per SIMD: 256 registers)
+constexpr int kReflBlock = 512;     // lanes of the reflector workgroups
 
 // Sum over a kEigBlock-lane workgroup in a fixed order (lanes by a xor tree, lane
 // 0's value per wave, then the waves in order); every lane gets the same bits.
@@ -755,106 +755,195 @@ void own_select_kernel(const GroupDesc *__restrict__ groups, const int32_t *__re
     }
 }
 
-// The reflectors applied to a thin block: forward (H_0 first: Y <- Q^T Y) or
-// backward (H_{n-3} first: Y <- Q Y).  One 512-lane workgroup per group and
-// chunk of 8 columns keeps its part of the block in registers (rows tid +
-// 512 q); per reflector the 8 dot products are reduced in a fixed order (xor
-// trees inside the waves, then the 8 waves in order), then every lane updates
-// its rows.
-constexpr int kReflCols = 8;
-template <bool FORWARD>
+// The reflectors applied to a thin block, 16 at a time in compact WY form:
+// H_a ... H_{a+15} = I - V T V^T with T upper triangular, T_ii = tau_i and
+// T_ri = -tau_i sum_{r <= p < i} T_rp (V^T V)_pi.  Y <- Q^T Y takes the blocks in
+// order, Y <- Y - V T^T (V^T Y); Y <- Q Y in reverse, Y <- Y - V T (V^T Y).
+//
+// One reflector at a time is a serial chain of n steps, each a reduction over
+// the workgroup (water256: 10 ms a pass); a block of 16 is three products on the
+// matrix cores and one reduction (1.07 ms a pass, and 0.26 ms for all T).
+constexpr int kWy = 16;
+
+// Column k0 + q of the reflectors at `row` (V is zero above row k0 + q + 1).
+__device__ inline double v_mask(double x, int row, int q, int k0, int n)
+{
+    return (row > k0 + q && row < n && k0 + q < n - 2) ? x : 0.0;
+}
+
+// T of the block of reflectors k0 .. k0 + 15 of every group, one workgroup each,
+// to twy (at the group's slab, block b at 256 b, T_rc at 16 r + c).
+__global__ __launch_bounds__(256)
+void wy_t_kernel(const GroupDesc *__restrict__ groups, int g0, const double *__restrict__ abase, EigVecs ev,
+                 double *__restrict__ twy)
+{
+    __shared__ double gs[4][16][17];
+    const GroupDesc gd = groups[g0 + blockIdx.y];
+    const int n = gd.n, ld = gd.npad, k0 = blockIdx.x * kWy;
+    if (k0 + 2 >= n) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int li = lane & 15, lq = lane >> 4;
+    const double *vc = abase + gd.off + (int64_t)min(k0 + li, n - 1) * ld;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int r0 = (k0 & ~15) + 16 * wave; r0 < n; r0 += 64) {
+        double v[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) v[t] = v_mask(vc[r0 + 4 * lq + t], r0 + 4 * lq + t, li, k0, n);
+#pragma unroll
+        for (int t = 0; t < 4; t++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], v[t], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; v++) gs[wave][lq + 4 * v][li] = acc[v];
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+        gs[0][r][c] = ((gs[0][r][c] + gs[1][r][c]) + gs[2][r][c]) + gs[3][r][c];
+    }
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        const int r = threadIdx.x;
+        const double *tau = ev.tau + gd.rinfo_off;
+        double tr[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const double ti = k0 + i < n - 2 ? tau[k0 + i] : 0.0;
+            double s = 0.0;
+#pragma unroll
+            for (int p = 0; p < i; p++) s += (p >= r ? tr[p] : 0.0) * gs[0][p][i];
+            tr[i] = i < r ? 0.0 : (i == r ? ti : -ti * s);
+        }
+        double *to = twy + gd.off + (int64_t)blockIdx.x * (kWy * kWy) + 16 * r;
+#pragma unroll
+        for (int i = 0; i < 16; i++) to[i] = tr[i];
+    }
+}
+
+// One 512-lane workgroup per group and block of 16 columns keeps the columns in
+// registers: wave w holds the 16-row tiles w, w + 8, ... (NT of them), lane
+// (li, lq) = (l % 16, l / 16) rows 4 lq + t, t < 4, of column li.  That is the
+// layout of a right operand of V^T Y (with the sum index permuted, k = 4 lq + t
+// in both operands), and of the output of V (T V^T Y) when its row m stands for
+// row 4 (m % 4) + m / 4 of the tile, so the block never changes its layout.
+// NT = 0: any n, the columns stay in memory, where each lane reads and writes
+// its own elements.
+template <bool FORWARD, int NT>
 __global__ __launch_bounds__(kReflBlock)
 void reflect_kernel(const GroupDesc *__restrict__ groups, int g0, const double *__restrict__ abase,
-                    EigVecs ev, double *__restrict__ y)
+                    const double *__restrict__ twy, double *__restrict__ y)
 {
-    constexpr int R = kEigMaxN / kReflBlock;
     constexpr int NWV = kReflBlock / 64;
-    __shared__ double red[NWV][kReflCols];
+    __shared__ double us[NWV][16][17];
+    __shared__ double ts[16][17];
     const GroupDesc gd = groups[g0 + blockIdx.y];
-    const int c0 = blockIdx.x * kReflCols;
+    const int c0 = blockIdx.x * 16;
     if (c0 >= gd.m_own) return;
-    const int nc = min(kReflCols, gd.m_own - c0);
-    const int n = gd.n, ld = gd.npad, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = gd.n, ld = gd.npad, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lq = lane >> 4;
+    const int nt = (n + 15) / 16;                      // row tiles (n_pad is a multiple of 32)
     const double *A = abase + gd.off;
-    const double *tau = ev.tau + gd.rinfo_off;
-    double *yb = y + gd.thin_off + (int64_t)c0 * ld;
-    double yr[R][kReflCols];
+    const double *T = twy + gd.off;
+    double *yc = y + gd.thin_off + (int64_t)min(c0 + li, gd.m_own - 1) * ld;
+    const bool mine = c0 + li < gd.m_own;
+    const int nq = NT > 0 ? NT : (nt + NWV - 1) / NWV;
+    auto tile_in = [&](int q) {
+        f64x4 f;
+        const int r = 16 * (wave + NWV * q) + 4 * lq;
 #pragma unroll
-    for (int q = 0; q < R; q++) {
-        const int i = tid + kReflBlock * q;
-#pragma unroll
-        for (int c = 0; c < kReflCols; c++) yr[q][c] = (i < n && c < nc) ? yb[i + (int64_t)c * ld] : 0.0;
-    }
-    // The next step's reflector and tau are loaded while this step's dot
-    // products are reduced (the reflectors do not change); two register sets
-    // take turns, so that no step waits on a memory round trip before its
-    // products (the barriers of a step wait for LDS accesses, not for these
-    // loads).  Every lane loads, rows beyond n reading row n - 1, so that the
-    // loads sit outside any branch; rows outside the reflector are masked to
-    // zero where they are used.
-    auto load_v = [&](int step, double (&dst)[R], double &tdst) {
-        const int k = FORWARD ? step : n - 3 - step;
-        const double *v = A + (int64_t)k * ld;
-        tdst = tau[k];
-#pragma unroll
-        for (int q = 0; q < R; q++) dst[q] = v[min(tid + kReflBlock * q, n - 1)];
+        for (int t = 0; t < 4; t++) {
+            const double v = yc[min(r + t, n - 1)];
+            f[t] = (mine && r + t < n) ? v : 0.0;
+        }
+        return f;
     };
-    auto apply = [&](int step, const double (&vl)[R], double t) {
-        if (t == 0.0) return;
-        const int k = FORWARD ? step : n - 3 - step;
-        double vr[R];
+    auto tile_out = [&](int q, const f64x4 &f) {
+        const int r = 16 * (wave + NWV * q) + 4 * lq;
 #pragma unroll
-        for (int q = 0; q < R; q++) {
-            const int i = tid + kReflBlock * q;
-            vr[q] = (i > k && i < n) ? vl[q] : 0.0;
-        }
-        double part[kReflCols];
-#pragma unroll
-        for (int c = 0; c < kReflCols; c++) part[c] = 0.0;
-#pragma unroll
-        for (int q = 0; q < R; q++)
-#pragma unroll
-            for (int c = 0; c < kReflCols; c++) part[c] += vr[q] * yr[q][c];
-#pragma unroll
-        for (int c = 0; c < kReflCols; c++) {
-            double s = part[c];
-            for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-            if (lane == 0) red[wave][c] = s;
-        }
-        __syncthreads();
-        double sv[kReflCols];
-#pragma unroll
-        for (int c = 0; c < kReflCols; c++) {
-            double s = 0.0;
-            for (int w = 0; w < NWV; w++) s += red[w][c];
-            sv[c] = t * s;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; q++)
-#pragma unroll
-            for (int c = 0; c < kReflCols; c++) yr[q][c] -= sv[c] * vr[q];
+        for (int t = 0; t < 4; t++)
+            if (mine && r + t < ld) yc[r + t] = r + t < n ? f[t] : 0.0;
     };
-    const int nsteps = n - 2;
-    double va[R], vb[R], ta = 0.0, tb = 0.0;
-    if (nsteps > 0) load_v(0, va, ta);
-    // (the loads are unconditional, the last step's reflector read again at
-    // the end: loads issued under a branch made the compiler wait for every
-    // outstanding load where the paths join)
-    for (int st = 0; st < nsteps; st += 2) {
-        load_v(min(st + 1, nsteps - 1), vb, tb);
-        apply(st, va, ta);
-        if (st + 1 >= nsteps) break;
-        load_v(min(st + 2, nsteps - 1), va, ta);
-        apply(st + 1, vb, tb);
-    }
+    f64x4 yr[NT > 0 ? NT : 1];
+    if constexpr (NT > 0) {
 #pragma unroll
-    for (int q = 0; q < R; q++) {
-        const int i = tid + kReflBlock * q;
-#pragma unroll
-        for (int c = 0; c < kReflCols; c++)
-            if (i < ld && c < nc) yb[i + (int64_t)c * ld] = i < n ? yr[q][c] : 0.0;
+        for (int q = 0; q < NT; q++) yr[q] = tile_in(q);
     }
+    const int nb = (n - 2 + kWy - 1) / kWy;
+    for (int s = 0; s < nb; s++) {
+        const int b = FORWARD ? s : nb - 1 - s, k0 = b * kWy;
+        const int tb = k0 >> 4;                        // first tile with rows of the block
+        if (tid < 256) ts[tid >> 4][tid & 15] = T[(int64_t)b * (kWy * kWy) + tid];
+        // U = V^T Y over this wave's tiles
+        f64x4 u = {0.0, 0.0, 0.0, 0.0};
+        const double *vc = A + (int64_t)min(k0 + li, n - 1) * ld;
+        auto dot_tile = [&](int q, const f64x4 &f) {
+            const int tile = wave + NWV * q, r = 16 * tile + 4 * lq;
+            if (tile >= nt || tile < tb) return;
+            double v[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) v[t] = v_mask(vc[r + t], r + t, li, k0, n);
+#pragma unroll
+            for (int t = 0; t < 4; t++) u = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], f[t], u, 0, 0, 0);
+        };
+        if constexpr (NT > 0) {
+#pragma unroll
+            for (int q = 0; q < NT; q++) dot_tile(q, yr[q]);
+        } else {
+            for (int q = 0; q < nq; q++) dot_tile(q, tile_in(q));
+        }
+#pragma unroll
+        for (int v = 0; v < 4; v++) us[wave][lq + 4 * v][li] = u[v];
+        __syncthreads();
+        // U summed over the waves in order, as the right operand of T U (T^T U)
+        double ub[4], ta[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            double a = 0.0;
+#pragma unroll
+            for (int w = 0; w < NWV; w++) a += us[w][4 * t + lq][li];
+            ub[t] = a;
+            ta[t] = FORWARD ? ts[4 * t + lq][li] : ts[li][4 * t + lq];
+        }
+        f64x4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < 4; t++) x = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[t], ub[t], x, 0, 0, 0);
+        // lane (li, lq) holds rows lq + 4 v of X: the right operand of V X with
+        // the sum index k = lq + 4 t in sub-step t
+        auto update_tile = [&](int q, f64x4 &f) {
+            const int tile = wave + NWV * q, r = 16 * tile + 4 * (li & 3) + (li >> 2);
+            if (tile >= nt || tile < tb) return;
+            double v[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const int qc = 4 * t + lq;
+                v[t] = -v_mask(A[r + (int64_t)min(k0 + qc, n - 1) * ld], r, qc, k0, n);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; t++) f = __builtin_amdgcn_mfma_f64_16x16x4f64(v[t], x[t], f, 0, 0, 0);
+        };
+        if constexpr (NT > 0) {
+#pragma unroll
+            for (int q = 0; q < NT; q++) update_tile(q, yr[q]);
+        } else {
+            for (int q = 0; q < nq; q++) {
+                f64x4 f = tile_in(q);
+                update_tile(q, f);
+                tile_out(q, f);
+            }
+        }
+        __syncthreads();                               // us and ts are free again
+    }
+    // rows from n on as zero: in the last tiles here, in those beyond them below
+    if constexpr (NT > 0) {
+#pragma unroll
+        for (int q = 0; q < NT; q++) tile_out(q, yr[q]);
+    } else {
+        for (int q = 0; q < nq; q++) tile_out(q, tile_in(q));
+    }
+    for (int r = 16 * nt + 4 * (tid >> 4); r < ld; r += 128)
+        if (c0 + li < gd.m_own) {
+#pragma unroll
+            for (int t = 0; t < 4; t++) yc[r + t] = 0.0;
+        }
 }
 
 // g(lambda) = 1 - 2 f(lambda): tanh(lambda / 2kT) for kT > 0; at T = 0 the
@@ -1031,15 +1120,35 @@ hipError_t launch_eig_own_select(hipStream_t st, int g0, int ngroups, int max_np
     return hipGetLastError();
 }
 
-hipError_t launch_eig_reflect(hipStream_t st, int forward, int g0, int ngroups, int max_own, const GroupDesc *groups,
-                              const double *a, const EigVecs &ev, double *y)
+hipError_t launch_eig_wy(hipStream_t st, int g0, int ngroups, int max_npad, const GroupDesc *groups, const double *a,
+                         const EigVecs &ev, double *twy)
+{
+    if (ngroups <= 0 || max_npad <= 2) return hipSuccess;
+    const dim3 grid((unsigned)((max_npad + kWy - 1) / kWy), (unsigned)ngroups);
+    hipLaunchKernelGGL(wy_t_kernel, grid, dim3(256), 0, st, groups, g0, a, ev, twy);
+    return hipGetLastError();
+}
+
+hipError_t launch_eig_reflect(hipStream_t st, int forward, int g0, int ngroups, int max_npad, int max_own,
+                              const GroupDesc *groups, const double *a, const double *twy, double *y)
 {
     if (ngroups <= 0 || max_own <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((max_own + kReflCols - 1) / kReflCols), (unsigned)ngroups);
-    if (forward)
-        hipLaunchKernelGGL(reflect_kernel<true>, grid, dim3(kReflBlock), 0, st, groups, g0, a, ev, y);
-    else
-        hipLaunchKernelGGL(reflect_kernel<false>, grid, dim3(kReflBlock), 0, st, groups, g0, a, ev, y);
+    const dim3 grid((unsigned)((max_own + 15) / 16), (unsigned)ngroups);
+    // tiles per wave held in registers: 8 are 1024 rows, 12 are 1536 (24 for all
+    // kEigMaxN rows would spill most of them)
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kReflBlock), 0, st, groups, g0, a, twy, y);
+    };
+    if (max_npad <= 1024) {
+        if (forward) go(reflect_kernel<true, 8>);
+        else go(reflect_kernel<false, 8>);
+    } else if (max_npad <= 1536) {
+        if (forward) go(reflect_kernel<true, 12>);
+        else go(reflect_kernel<false, 12>);
+    } else {
+        if (forward) go(reflect_kernel<true, 0>);
+        else go(reflect_kernel<false, 0>);
+    }
     return hipGetLastError();
 }
 

@@ -303,9 +303,13 @@ hipError_t launch_eig_values_vectors(hipStream_t st, int g0, int ngroups, int ma
 // y = the own-column selector (n_pad x m_own blocks at thin_off).
 hipError_t launch_eig_own_select(hipStream_t st, int g0, int ngroups, int max_npad, int max_own,
                                  const GroupDesc *groups, const int32_t *own_list, double *y);
-// y <- Q^T y (forward != 0) or Q y, with Q from the reflectors in a.
-hipError_t launch_eig_reflect(hipStream_t st, int forward, int g0, int ngroups, int max_own, const GroupDesc *groups,
-                              const double *a, const EigVecs &ev, double *y);
+// The triangular factors of the reflectors in a, 16 of them to a block
+// (n_pad x 16 values at each group's place of the slab twy).
+hipError_t launch_eig_wy(hipStream_t st, int g0, int ngroups, int max_npad, const GroupDesc *groups, const double *a,
+                         const EigVecs &ev, double *twy);
+// y <- Q^T y (forward != 0) or Q y, with Q from the reflectors in a and their factors twy.
+hipError_t launch_eig_reflect(hipStream_t st, int forward, int g0, int ngroups, int max_npad, int max_own,
+                              const GroupDesc *groups, const double *a, const double *twy, double *y);
 // mode 0: out = S^T in, with weights and lam_abs = lam + mu0;
 // mode 1: out = S diag(g(lam - dmu)) in, g = tanh(x / 2kT) (signum at T = 0).
 hipError_t launch_eig_thin(hipStream_t st, int mode, int g0, int ngroups, int max_npad, int max_own,
