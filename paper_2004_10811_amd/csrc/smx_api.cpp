@@ -104,7 +104,7 @@ struct Plan {
     std::vector<ScatterDesc> scat;
     std::vector<int32_t> own_list;    // own columns of every group (submatrix column indices)
     std::vector<double> wtiles;       // live 64 x 64 wave tiles of one product, per group
-    // lower tiles of the FP64 products and their edge; per wave like tile_beg
+    // lower tiles of the FP64 and FP32 products and their edge; per wave like tile_beg
     int32_t edge_d = kTile;
     std::vector<TileDesc> tiles_d;
     std::vector<int64_t> tiles_d_beg;
@@ -500,7 +500,7 @@ int64_t group_bytes(const GroupDesc &d)
     return kArenaBytesPerElem * (int64_t)d.npad * d.npad + (2 * kMaxPolishMixed + 1) * 8 * (int64_t)d.npad * d.m_own;
 }
 
-// Tile edge of the FP64 products (bitwise the same results).  Edge 64 once its
+// Tile edge of the FP64 and FP32 products (bitwise the same results).  Edge 64 once its
 // tiles fill the chip: four workgroups on each of the 256 CUs are 1024 tiles.
 // With fewer, edge 32 spreads the same products over more waves.  Square per
 // launch, edge 32 / 64: 36 tiles of 64 (12 groups of n ~ 90) 6.3 / 11.0 us, 240
@@ -1762,6 +1762,9 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                     if (b.big)
                         r = run(kind256, [&] { return launch_ns_words256(s, fmt, nw, mode, b.n, b.tl, V.gd, x, y, o, it,
                                                                          k, c->switch_tol, kmax); });
+                    else if (fmt == 2)
+                        r = run(kind128, [&] { return launch_ns_f32(s, mode, P.edge_d, ntd, tld, V.gd, x, y, o, it, k,
+                                                                    c->switch_tol, kmax); });
                     else if (persistent && mode <= 1)
                         r = run(kind128, [&] {
                             return launch_ns_words_persistent(s, fmt, nw, mode, pers_nwg, V.tiles_sx + P.sx_wbeg[wave],

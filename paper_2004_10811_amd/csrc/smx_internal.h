@@ -180,8 +180,7 @@ hipError_t launch_ns_words_persistent(hipStream_t st, int fmt, int nw, int mode,
 // Workgroups of the persistent word products one CU holds at once.
 int words_persistent_blocks_per_cu(int fmt, int nw);
 
-// Reduced-precision bulk products (fmt 0 = FP16, 1 = BF16; nw words per value;
-// fmt 2 = one FP32 value per element, column-major like the FP64 slabs).
+// Reduced-precision bulk products (fmt 0 = FP16, 1 = BF16; nw words per value).
 // mode 0: Newton-Schulz square (W = 1.5 I - 0.5 X^2, residual, 1 - T_ii);
 // mode 1: update X_{k+1} = X W after the bulk stopping rule;
 // mode 2: Pade square (T = X^2 stored, residual, 1 - T_ii);
@@ -192,6 +191,11 @@ int words_persistent_blocks_per_cu(int fmt, int nw);
 hipError_t launch_ns_words(hipStream_t st, int fmt, int nw, int mode, int variant, int ntiles, const TileDesc *tiles,
                            const GroupDesc *groups, const unsigned short *x, const unsigned short *b,
                            unsigned short *out, const IterState &it, int k, double switch_tol, int kmax);
+// The same for FP32 values (one per element, column-major like the FP64 slabs), on
+// the lower tiles of the FP64 products (edge 32 or 64).
+hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+                         const unsigned short *x, const unsigned short *b, unsigned short *out, const IterState &it,
+                         int k, double switch_tol, int kmax);
 // The same products on 256 x 256 output tiles (tiles list (group, tile row
 // << 16 | tile column) in units of 256; fmt 0 / 1 with nw = 1 or 2 only).
 // Results are bitwise those of the 128 x 128 tiles.

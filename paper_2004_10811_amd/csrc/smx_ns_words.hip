@@ -934,25 +934,28 @@ void ns_words256_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__r
 }
 
 // FP32 products (v_mfma_f32_16x16x4_f32, FP32 accumulation): the iterate is
-// held as one FP32 value per element.  Same tiling, symmetry use, LDS loads
-// (32 k = 128 B per column and step, chunks swizzled over eight positions),
-// stopping rule and epilogue as the word products.
-__device__ inline int swz8(int col) { return (col ^ (col >> 3)) & 7; }
-
-__host__ __device__ constexpr int f32_lds_bytes()
-{
-    return (2 * BM * BK * 4) > (BM * CSTH * 4) ? (2 * BM * BK * 4) : (BM * CSTH * 4);
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256, 2)
+// held as one FP32 value per element.  Stopping rule as the word products;
+// tiles, operand stream and stores as the FP64 products: 2 x 2 waves of WB x WB
+// blocks of 16 x 16 (edge 32 WB), lower tiles and their mirror, K steps of 32 (a
+// 128-B line per column) through double-buffered LDS with the loads two steps
+// ahead in two register sets.  Lane group lg holds k = 16 h + 4 lg + (0..3) of
+// each half h of a step, and product j takes component j: the order of the sum
+// is the same for every edge.
+//
+// What bounds it: the FP32 matrix pipe (32 cycles a product).  water256 in 384
+// k-means groups (n up to ~1300), square / update per launch: 128 x 128 tiles, one
+// LDS stage, epilogue through LDS 1.79 / 1.68 ms; edge 64 1.59 / 1.51 ms.
+template <int MODE, int WB>
+__global__ __launch_bounds__(256, 4)
 void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
                    const float *__restrict__ xin, const float *__restrict__ bin,
                    float *__restrict__ out, IterState it, int k, double switch_tol, int kmax)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[f32_lds_bytes()];
-    float *Ls = reinterpret_cast<float *>(smem);                     // [2 operands][BM][BK]
-    float *Cs = reinterpret_cast<float *>(smem);                     // staging after the K loop
+    constexpr int TE = 32 * WB;         // tile edge
+    constexpr int WE = 16 * WB;         // edge of a wave's part of the tile
+    constexpr int SF = BK + 4;          // LDS column stride in floats (breaks bank aliasing)
+    __shared__ float As[2][TE][SF];
+    __shared__ float Bs[2][TE][SF];
 
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
@@ -973,147 +976,115 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     const int li = lane & 15;
     const int lg = lane >> 4;
 
-    // Loads: one wave instruction fills 1 KB of LDS = 8 columns x 128 B (32
-    // floats); lane l fills slot l % 8 of column (wave + 4 q) * 8 + l / 8 with
-    // chunk (slot ^ swz8(column)) of that column.  Columns beyond ld read any
-    // valid address instead (their products only reach discarded outputs).
-    constexpr int PH = BM * BK;         // floats per operand region
-    const float *srcA[4], *srcB[4];
-    int kcoff[4];
+    // Chunk q*256 + tid (q < WB) of a K step is column 32 q + tid/8, 16-B part
+    // tid%8.  Every lane loads (columns beyond ld read column ld - 1, whose
+    // products reach only outputs that are not stored).
+    const int part = (tid & 7) * 4, col8 = tid >> 3;
+    const float *pa[WB], *pb[WB];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int cl = (wave + 4 * q) * 8 + lane / 8;
-        kcoff[q] = ((lane % 8) ^ swz8(cl)) * 4;
-        srcA[q] = xin + gd.off + (int64_t)(ti * BM + cl < ld ? ti * BM + cl : 0) * ld;
-        srcB[q] = bin + gd.off + (int64_t)(tj * BM + cl < ld ? tj * BM + cl : 0) * ld;
+    for (int q = 0; q < WB; q++) {
+        pa[q] = xin + gd.off + (int64_t)min(ti * TE + 32 * q + col8, ld - 1) * ld + part;
+        pb[q] = bin + gd.off + (int64_t)min(tj * TE + 32 * q + col8, ld - 1) * ld + part;
     }
-
-    const int row_w = ti * BM + wr * 64, col_w = tj * BM + wc * 64;
+    const int row_w = ti * TE + wr * WE, col_w = tj * TE + wc * WE;
     const bool wave_live = (row_w < ld) && (col_w < ld) && !(ti == tj && wr < wc);
 
-    f4 acc[4][4];
+    f4 acc[WB][WB];
 #pragma unroll
-    for (int i = 0; i < 4; i++)
+    for (int i = 0; i < WB; i++)
 #pragma unroll
-        for (int j = 0; j < 4; j++) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < WB; j++) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
     const int nk = ld / BK;             // ld is a multiple of 32
-    for (int kt = 0; kt < nk; kt++) {
-        const int k0 = kt * BK;
+    f4 r0[2 * WB], r1[2 * WB];
+    auto gload = [&](int kt, f4 (&r)[2 * WB]) {
+        const int kk = min(kt, nk - 1) * BK;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            float *dA = Ls + 0 * PH + (wave + 4 * q) * 8 * BK;
-            float *dB = Ls + 1 * PH + (wave + 4 * q) * 8 * BK;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(srcA[q] + k0 + kcoff[q]),
-                                             (__attribute__((address_space(3))) void *)dA, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(srcB[q] + k0 + kcoff[q]),
-                                             (__attribute__((address_space(3))) void *)dB, 16, 0, 0);
+        for (int q = 0; q < WB; q++) {
+            r[q] = *reinterpret_cast<const f4 *>(pa[q] + kk);
+            r[WB + q] = *reinterpret_cast<const f4 *>(pb[q] + kk);
         }
-        wait_vm0();
-        lds_barrier();                  // every wave's loads of this step are in LDS
-        if (wave_live) {
-            // two halves of 16 k; lane group lg holds k = 16 h + 4 lg + (0..3), and
-            // product j takes component j: the same permutation of k on both sides
+    };
+    auto sstore = [&](int buf, const f4 (&r)[2 * WB]) {
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                f4 bv[4];
+        for (int q = 0; q < WB; q++) {
+            *reinterpret_cast<f4 *>(&As[buf][32 * q + col8][part]) = r[q];
+            *reinterpret_cast<f4 *>(&Bs[buf][32 * q + col8][part]) = r[WB + q];
+        }
+    };
+    auto products = [&](int buf) {
+        if (!wave_live) return;
 #pragma unroll
-                for (int jj = 0; jj < 4; jj++) {
-                    const int cb = wc * 64 + jj * 16 + li;
-                    bv[jj] = *reinterpret_cast<const f4 *>(Ls + 1 * PH + cb * BK + (((h * 4 + lg) ^ swz8(cb)) * 4));
-                }
+        for (int h = 0; h < 2; h++) {
+            f4 av[WB], bv[WB];
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int ca = wr * 64 + i * 16 + li;
-                    const f4 av = *reinterpret_cast<const f4 *>(Ls + 0 * PH + ca * BK + (((h * 4 + lg) ^ swz8(ca)) * 4));
-#pragma unroll
-                    for (int j = 0; j < 4; j++)
-#pragma unroll
-                        for (int jj = 0; jj < 4; jj++)
-                            acc[i][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], bv[jj][j], acc[i][jj], 0, 0, 0);
-                }
+            for (int i = 0; i < WB; i++) {
+                av[i] = *reinterpret_cast<const f4 *>(&As[buf][wr * WE + i * 16 + li][16 * h + 4 * lg]);
+                bv[i] = *reinterpret_cast<const f4 *>(&Bs[buf][wc * WE + i * 16 + li][16 * h + 4 * lg]);
             }
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+#pragma unroll
+                for (int i = 0; i < WB; i++)
+#pragma unroll
+                    for (int j = 0; j < WB; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][t], bv[j][t], acc[i][j], 0, 0, 0);
         }
-        lds_barrier();                  // every wave is done reading before the next loads land
+    };
+    gload(0, r0);
+    gload(1, r1);
+    sstore(0, r0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {
+        gload(kt + 2, r0);
+        products(0);
+        sstore(1, r1);
+        __syncthreads();
+        if (kt + 1 >= nk) break;
+        gload(kt + 3, r1);
+        products(1);
+        sstore(0, r0);
+        __syncthreads();
     }
+    if (!wave_live) return;
 
-    // ---- epilogue, in two rounds over the column halves h of the tile (the
-    // waves with wc == h hold them).  Lane l, register v of block (i, j) holds
-    // row 16 i + 4 (l / 16) + v and column 16 j + l % 16 of the wave's tile.
+    // Lane l, register v of block (i, j) holds row 16 i + 4 (l / 16) + v and
+    // column 16 j + l % 16 of the wave's part: four consecutive rows of a column
+    // in one store, and their mirror in four (16 lanes to a 64-B run).  n_pad is
+    // a multiple of 32, so a block lies wholly inside or outside the matrix.
     const int n = gd.n;
-    const bool diag = (ti == tj);
     float *og = out + gd.off;
     float rmax = 0.f;
-    for (int h = 0; h < 2; h++) {
-        if (wave_live && wc == h) {
 #pragma unroll
-            for (int i = 0; i < 4; i++)
+    for (int i = 0; i < WB; i++)
 #pragma unroll
-                for (int j = 0; j < 4; j++)
-                    *reinterpret_cast<f4 *>(&Cs[(j * 16 + li) * CST + wr * 64 + i * 16 + lg * 4]) = acc[i][j];
-        }
-        __syncthreads();
-        // the tile's own positions: unit (column cl of the half, 8-row chunk rc);
-        // 8-row chunks above the diagonal of a diagonal tile are the mirror's
-#pragma unroll 2
-        for (int q = 0; q < 4; q++) {
-            const int u = tid + 256 * q;
-            const int rc = u & 15, cl = u >> 4;
-            const int c = tj * BM + h * 64 + cl, r0 = ti * BM + rc * 8;
-            if (c >= ld || r0 >= ld) continue;
-            if (diag && r0 + 7 < c) continue;
-            float v[8];
-            load8(&Cs[cl * CST + rc * 8], rc & 4, v);
+        for (int j = 0; j < WB; j++) {
+            const int c = col_w + j * 16 + li, ra = row_w + i * 16 + 4 * lg;
+            if (row_w + i * 16 >= ld || col_w + j * 16 >= ld) continue;
+            f4 val;
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const int r = r0 + e;
-                const float t = v[e];
+            for (int v = 0; v < 4; v++) {
+                const int r = ra + v;
+                const float t = acc[i][j][v];
                 if ((MODE == 0 || MODE == 2) && r < n && c < n && r >= c) {
                     float d = fabsf(t - (r == c ? 1.f : 0.f));
                     if (!(d <= 3.4e38f)) d = __builtin_huge_valf();
                     rmax = fmaxf(rmax, d);
                     if (r == c) it.tdiag[gd.rinfo_off + r] = 1.0 - (double)t;
                 }
-                v[e] = out_value<MODE>(t, MODE == 3 ? xin[gd.off + r + (int64_t)c * ld] : 0.f, r, c);
+                val[v] = out_value<MODE>(t, MODE == 3 ? xin[gd.off + r + (int64_t)c * ld] : 0.f, r, c);
             }
-            *reinterpret_cast<f4 *>(og + r0 + (int64_t)c * ld) = f4{v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<f4 *>(og + r0 + 4 + (int64_t)c * ld) = f4{v[4], v[5], v[6], v[7]};
-        }
-        __syncthreads();                // Cs reads done; direct stores precede the mirror's
-        if (wave_live && wc == h) {
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int j = 0; j < 4; j++)
-#pragma unroll
-                    for (int v = 0; v < 4; v++)
-                        Cs[(wr * 64 + i * 16 + lg * 4 + v) * CSTH + j * 16 + li] = acc[i][j][v];
-        }
-        __syncthreads();
-        // mirror: tile element (rl, cl) goes to (cl, rl) of the matrix; unit (tile
-        // row rl, 8-column chunk cc); in a diagonal tile only positions above
-        // the diagonal
-#pragma unroll 2
-        for (int q = 0; q < 4; q++) {
-            const int u = tid + 256 * q;
-            const int cc = u & 7, rl = u >> 3;
-            const int r = ti * BM + rl, c0 = tj * BM + h * 64 + cc * 8;
-            if (r >= ld || c0 >= ld) continue;
-            if (diag && c0 >= r) continue;
-            float v[8];
-            load8(&Cs[rl * CSTH + cc * 8], cc & 4, v);
-#pragma unroll
-            for (int e = 0; e < 8; e++) v[e] = out_value<MODE>(v[e], MODE == 3 ? xin[gd.off + c0 + e + (int64_t)r * ld] : 0.f, r, c0 + e);
-            if (!diag || c0 + 8 <= r) {
-                *reinterpret_cast<f4 *>(og + c0 + (int64_t)r * ld) = f4{v[0], v[1], v[2], v[3]};
-                *reinterpret_cast<f4 *>(og + c0 + 4 + (int64_t)r * ld) = f4{v[4], v[5], v[6], v[7]};
+            if (ra >= c) {
+                *reinterpret_cast<f4 *>(og + ra + (int64_t)c * ld) = val;
             } else {
-                for (int e = 0; c0 + e < r; e++) og[c0 + e + (int64_t)r * ld] = v[e];
+#pragma unroll
+                for (int v = 0; v < 4; v++)
+                    if (ra + v >= c) og[ra + v + (int64_t)c * ld] = val[v];
             }
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+                if (ra + v > c) og[c + (int64_t)(ra + v) * ld] = val[v];
         }
-        __syncthreads();
-    }
-
     if (MODE == 0 || MODE == 2) {
         double rm = (double)rmax;
         rm = wave_max(rm);
@@ -1121,7 +1092,6 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
             atomicMax(it.resid_bits + (int64_t)g * it.resid_stride + k, (unsigned long long)__double_as_longlong(rm));
     }
 }
-
 
 // X_0 = a A_g, a = 1/s_g (the Gershgorin prescaling, bounds from the row-sum
 // pass), gathered straight into the word storage: one thread per row of a
@@ -1243,26 +1213,35 @@ hipError_t launch_ns_words(hipStream_t st, int fmt, int nw, int mode, int varian
                            unsigned short *out, const IterState &it, int k, double switch_tol, int kmax)
 {
     if (ntiles <= 0) return hipSuccess;
-    if (fmt == 2) {
-        const float *xf = reinterpret_cast<const float *>(x), *bf = reinterpret_cast<const float *>(b);
-        float *of = reinterpret_cast<float *>(out);
-#define SMX_F32(M) hipLaunchKernelGGL(ns_f32_kernel<M>, dim3(ntiles), dim3(256), 0, st, tiles, groups, xf, bf, of, it, \
-                                      k, switch_tol, kmax)
-        switch (mode) {
-        case 0: SMX_F32(0); break;
-        case 1: SMX_F32(1); break;
-        case 2: SMX_F32(2); break;
-        case 3: SMX_F32(3); break;
-        default: return hipErrorInvalidValue;
-        }
-#undef SMX_F32
-        return hipGetLastError();
-    }
     if (fmt == 0 && nw == 1) return launch_words_t<0, 1>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     if (fmt == 0 && nw == 2) return launch_words_t<0, 2>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     if (fmt == 1 && nw == 1) return launch_words_t<1, 1>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     if (fmt == 1 && nw == 3) return launch_words_t<1, 3>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+                         const unsigned short *x, const unsigned short *b, unsigned short *out, const IterState &it,
+                         int k, double switch_tol, int kmax)
+{
+    if (ntiles <= 0) return hipSuccess;
+    const float *xf = reinterpret_cast<const float *>(x), *bf = reinterpret_cast<const float *>(b);
+    float *of = reinterpret_cast<float *>(out);
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(256), 0, st, tiles, groups, xf, bf, of, it, k, switch_tol, kmax);
+        return hipGetLastError();
+    };
+    if ((edge != 32 && edge != 64) || mode < 0 || mode > 3) return hipErrorInvalidValue;
+    switch (mode + (edge == 64 ? 4 : 0)) {
+    case 0: return go(ns_f32_kernel<0, 1>);
+    case 1: return go(ns_f32_kernel<1, 1>);
+    case 2: return go(ns_f32_kernel<2, 1>);
+    case 3: return go(ns_f32_kernel<3, 1>);
+    case 4: return go(ns_f32_kernel<0, 2>);
+    case 5: return go(ns_f32_kernel<1, 2>);
+    case 6: return go(ns_f32_kernel<2, 2>);
+    default: return go(ns_f32_kernel<3, 2>);
+    }
 }
 
 hipError_t launch_ns_words_persistent(hipStream_t st, int fmt, int nw, int mode, int nwg, const TileDesc *tiles_x,
