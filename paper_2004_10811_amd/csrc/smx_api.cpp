@@ -108,6 +108,7 @@ struct Plan {
     int32_t edge_d = kTile;
     std::vector<TileDesc> tiles_d;
     std::vector<int64_t> tiles_d_beg;
+    bool by_cols = false;              // gather in pieces of 16 columns (gather_by_cols)
     std::vector<int64_t> cptr;        // per stored block: its contributions from the groups (adjoint)
     std::vector<int4> contrib;        // (group, row offset, column offset, 0), ascending group per block
     // waves: consecutive group ranges [wave_g[w], wave_g[w+1]) whose slabs share one arena;
@@ -516,6 +517,27 @@ int32_t f64_edge(const Plan &P)
     return tiles64 <= 1536 ? 32 : 64;
 }
 
+// Whether an evaluation gathers A_g in pieces of 64 rows x 16 columns and takes
+// the bound (and the words) in further passes over A_g, or walks each row's
+// block columns in one pass (bitwise the same).  A row's walk is a chain of three
+// dependent loads per block column; few rows leave it exposed, and blocks of a
+// few columns make it long.  Gather to words, one walk / pieces: 16 groups of
+// n ~ 270 0.148 / 0.032 ms, 40 of 724 (three words) 0.29 / 0.15, the 5888 of
+// ~ 200 of a split problem (one-element blocks) 5.2 / 2.7; FP64 100 of 503 (27
+// million elements) 0.116 / 0.103.  Many rows of larger blocks are bound by
+// memory, where the further passes cost more: 256 groups of 855 (194 million
+// elements) 0.89 / 1.27, 1024 of 847 2.7 / 5.1.
+bool gather_by_cols(const Plan &P)
+{
+    int64_t elems = 0, rows = 0, blocks = 0;
+    for (const GroupDesc &d : P.gd) {
+        elems += (int64_t)d.npad * d.npad;
+        rows += d.n;
+        blocks += d.m;
+    }
+    return elems <= (int64_t)64 << 20 || rows < 4 * blocks;
+}
+
 // Split the groups into consecutive waves of at most `budget` bytes each
 // (balanced: about total / ceil(total / budget) per wave), assign the
 // wave-relative slab offsets, and build each wave's launch lists.
@@ -555,6 +577,7 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     P.tiles_s_beg.assign(1, 0);
     P.tiles_b_beg.assign(1, 0);
     P.edge_d = f64_edge(P);
+    P.by_cols = gather_by_cols(P);
     P.tiles_d.clear();
     P.tiles_d_beg.assign(1, 0);
     P.tiles_sx.clear();
@@ -1578,6 +1601,18 @@ DevView ctx_view(smx_ctx c)
     return v;
 }
 
+// A_g = K_sub - mu I of the chunks' groups into their places of x0, and the
+// bounds s_g (atomic max into scale, which starts at zero).
+hipError_t gather_slab(smx_ctx c, const Plan &P, const DevView &V, int nch, const int2 *chs, double *x0,
+                       unsigned long long *scale)
+{
+    if (P.by_cols)
+        return launch_gather_cols(c->stream, nch, chs, P.max_npad, V.gd, V.rinfo, V.bmap, c->d_valoff.p, c->d_k.p,
+                                  c->mu, x0, scale);
+    return launch_gather(c->stream, nch, chs, V.gd, V.rinfo, V.bmap, V.boffs, c->d_valoff.p, c->d_k.p, c->mu, x0,
+                         scale);
+}
+
 // Enqueue one evaluation on the context's stream.  `arena` holds the largest
 // wave's three slabs (or the words of three iterates from byte 8E), `pool`
 // the own-column blocks of the polish (2 n_polish + 1 of them).  With
@@ -1704,8 +1739,11 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const int nch = (int)(P.chunk_beg[wave + 1] - P.chunk_beg[wave]);
         const int2 *chs = V.chunks + P.chunk_beg[wave];
         if (!mixed) {
-            HIP_TRY(c, launch_gather(st, nch, chs, V.gd, V.rinfo, V.bmap, V.boffs, c->d_valoff.p,
-                                     c->d_k.p, c->mu, xb[0], gather_scale));
+            HIP_TRY(c, gather_slab(c, P, V, nch, chs, xb[0], gather_scale));
+        } else if (P.by_cols) {
+            // A_g in the FP64 slab, which the bulk leaves free, then its words
+            HIP_TRY(c, gather_slab(c, P, V, nch, chs, xb[0], gather_scale));
+            HIP_TRY(c, launch_words_from_f64(st, fmt, nw, nch, chs, P.max_npad, V.gd, xb[0], it.scale_bits, wb[0]));
         } else {
             // bounds first, then X_0 straight into the words (no FP64 copy of A_g)
             HIP_TRY(c, launch_gather_bound(st, nch, chs, V.gd, V.rinfo, V.bmap, V.boffs,
@@ -1896,8 +1934,7 @@ int32_t eig_decompose_wave(smx_ctx c, const Plan &P, const DevView &V, double *a
     double *y = pool, *cb = pool + P.thin_elems;
     const EigVecs ev = eig_vecs(c);
     const int nch = (int)(P.chunk_beg[wave + 1] - P.chunk_beg[wave]);
-    HIP_TRY(c, launch_gather(st, nch, V.chunks + P.chunk_beg[wave], V.gd, V.rinfo, V.bmap, V.boffs, c->d_valoff.p,
-                             c->d_k.p, c->mu, a, V.scale));
+    HIP_TRY(c, gather_slab(c, P, V, nch, V.chunks + P.chunk_beg[wave], a, V.scale));
     if (after_gather) HIP_TRY(c, hipEventRecord(after_gather, st));
     {
         // the Householder reduction dominates the path: timed like the product launches

@@ -118,6 +118,12 @@ hipError_t launch_gather(hipStream_t st, int nchunks, const int2 *chunks, const 
                          const int64_t *valoff, const double *kvals, double mu, double *x0,
                          unsigned long long *scale_bits);
 
+// The same (A_g and the bounds, bitwise) in two passes that spread over the
+// columns too: A_g by pieces of 64 rows x 16 columns, then the row sums.
+hipError_t launch_gather_cols(hipStream_t st, int nchunks, const int2 *chunks, int max_npad, const GroupDesc *groups,
+                              const RowInfo *rinfo, const int32_t *bmap, const int64_t *valoff, const double *kvals,
+                              double mu, double *x0, unsigned long long *scale_bits);
+
 // mode 0: T = a^2 X X, records max|T - I| for step k, writes W = 1.5 I - 0.5 T.
 // mode 1: if the step-k residual meets the stopping rule the group is finished
 //         at X_k; otherwise X_{k+1} = a X W.   a = 1/s_g at k = 0, else 1.
@@ -205,6 +211,10 @@ constexpr size_t kGuardElems = 8192;
 hipError_t launch_ns_words256(hipStream_t st, int fmt, int nw, int mode, int ntiles, const TileDesc *tiles,
                               const GroupDesc *groups, const unsigned short *x, const unsigned short *b,
                               unsigned short *out, const IterState &it, int k, double switch_tol, int kmax);
+// The same X_0 words (or FP32 values) from an FP64 copy of A_g (launch_gather_cols).
+hipError_t launch_words_from_f64(hipStream_t st, int fmt, int nw, int nchunks, const int2 *chunks, int max_npad,
+                                 const GroupDesc *groups, const double *a,
+                                 const unsigned long long *scale_bits, unsigned short *dst);
 // Group-walking launchers take the first group g0 and the count ngroups (a wave).
 // Gershgorin bounds only (atomic max of the row sums into scale_bits), no
 // writes of A_g; then X_0 = A_g / s_g gathered straight into the word storage

@@ -64,6 +64,74 @@ void gather_shift_kernel(const int2 *__restrict__ chunks, const GroupDesc *__res
     if ((threadIdx.x & 63) == 0) atomic_max_nonneg(scale_bits + ch.x, m);
 }
 
+// The gather in pieces of 64 rows x 16 columns, one wave each (four waves of a
+// workgroup take the 256 rows of a chunk, blockIdx.y the columns), with no bound:
+// a value takes three dependent loads (the stored block's position, its offset,
+// the value), and the sixteen columns go through each stage together.
+__global__ __launch_bounds__(256)
+void gather_cols_kernel(const int2 *__restrict__ chunks, const GroupDesc *__restrict__ groups,
+                        const RowInfo *__restrict__ rinfo, const int32_t *__restrict__ bmap,
+                        const int64_t *__restrict__ valoff, const double *__restrict__ kvals, double mu,
+                        double *__restrict__ x0)
+{
+    constexpr int NB = 16;
+    const int2 ch = chunks[blockIdx.x];
+    const GroupDesc gd = groups[ch.x];
+    const int r = ch.y + (int)threadIdx.x, c0 = NB * (int)blockIdx.y;
+    const int npad = gd.npad, n = gd.n;
+    if (r >= npad || c0 >= npad) return;              // n_pad is a multiple of 32
+    const RowInfo *ci = rinfo + gd.rinfo_off;         // rows and columns share the table
+    const bool real = r < n;
+    const RowInfo ri = ci[real ? r : 0];
+    const int rr = ri.y & 0xffff, br = ri.y >> 16;
+    const int32_t *map_row = bmap + gd.map_off + ri.x;
+    RowInfo col[NB];
+    int32_t pos[NB];
+    int64_t off[NB];
+    double v[NB];
+#pragma unroll
+    for (int u = 0; u < NB; u++) col[u] = ci[min(c0 + u, n - 1)];
+#pragma unroll
+    for (int u = 0; u < NB; u++) pos[u] = map_row[(int64_t)gd.m * col[u].x];
+#pragma unroll
+    for (int u = 0; u < NB; u++) off[u] = valoff[max(pos[u], 0)] + rr + (int64_t)(col[u].y & 0xffff) * br;
+#pragma unroll
+    for (int u = 0; u < NB; u++) v[u] = kvals[pos[u] >= 0 ? off[u] : 0];
+    double *xg = x0 + gd.off + r;
+#pragma unroll
+    for (int u = 0; u < NB; u++) {
+        const int c = c0 + u;
+        double x = (real && c < n && pos[u] >= 0) ? v[u] : 0.0;
+        if (r == c) x = real ? x - mu : 1.0;          // padding: the identity
+        xg[(int64_t)c * npad] = x;
+    }
+}
+
+// Row sums of |A_g| in column order (the order of gather_row: the same bits)
+// into the bound s_g, one lane per row, 32 columns in flight.
+__global__ __launch_bounds__(64)
+void row_bound_kernel(const int2 *__restrict__ chunks, const GroupDesc *__restrict__ groups,
+                      const double *__restrict__ x0, unsigned long long *__restrict__ scale_bits)
+{
+    constexpr int NB = 32;
+    const int2 ch = chunks[blockIdx.x >> 2];
+    const GroupDesc gd = groups[ch.x];
+    const int r = ch.y + 64 * (int)(blockIdx.x & 3) + (int)threadIdx.x, n = gd.n;
+    if (r - (int)threadIdx.x >= n) return;            // whole wave beyond the matrix
+    const double *row = x0 + gd.off + min(r, n - 1);
+    double s = 0.0;
+    for (int c0 = 0; c0 < n; c0 += NB) {
+        double v[NB];
+#pragma unroll
+        for (int u = 0; u < NB; u++) v[u] = row[(int64_t)min(c0 + u, n - 1) * gd.npad];
+#pragma unroll
+        for (int u = 0; u < NB; u++)
+            if (c0 + u < n) s += fabs(v[u]);
+    }
+    s = wave_max(s);                                  // lanes beyond n repeat row n - 1
+    if (threadIdx.x == 0) atomic_max_nonneg(scale_bits + ch.x, s);
+}
+
 // ---------------------------------------------------------------------------
 // Scatter (Sec. III-A step 3): for every stored block (I, J) of an own
 // column J of group g, D_IJ = (delta_IJ I - S_g[I rows, J cols]) / 2.  The
@@ -717,6 +785,19 @@ hipError_t launch_gather(hipStream_t st, int nchunks, const int2 *chunks, const 
     if (nchunks <= 0) return hipSuccess;
     hipLaunchKernelGGL(gather_shift_kernel<true>, dim3(nchunks), dim3(256), 0, st, chunks, groups,
                        rinfo, bmap, boffs, valoff, kvals, mu, x0, scale_bits);
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_cols(hipStream_t st, int nchunks, const int2 *chunks, int max_npad, const GroupDesc *groups,
+                              const RowInfo *rinfo, const int32_t *bmap, const int64_t *valoff, const double *kvals,
+                              double mu, double *x0, unsigned long long *scale_bits)
+{
+    if (nchunks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(gather_cols_kernel, dim3(nchunks, (unsigned)((max_npad + 15) / 16)), dim3(256), 0, st, chunks,
+                       groups, rinfo, bmap, valoff, kvals, mu, x0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(row_bound_kernel, dim3(4 * nchunks), dim3(64), 0, st, chunks, groups, x0, scale_bits);
     return hipGetLastError();
 }
 

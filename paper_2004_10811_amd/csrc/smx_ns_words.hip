@@ -1151,6 +1151,42 @@ void gather_f32_kernel(const int2 *__restrict__ chunks, const GroupDesc *__restr
     for (int c = gd.n; c < ld; c++) d[r + (int64_t)c * ld] = (r == c) ? 1.0f : 0.0f;   // the identity, not prescaled
 }
 
+// X_0 = a A_g into the word storage (FMT 2: FP32 values) from an FP64 copy of A_g,
+// in pieces of 64 rows x 16 columns as gather_cols_kernel; the padding's identity
+// is not prescaled.
+template <int FMT, int NW>
+__global__ __launch_bounds__(256)
+void words_from_f64_kernel(const int2 *__restrict__ chunks, const GroupDesc *__restrict__ groups,
+                           const double *__restrict__ x, const unsigned long long *__restrict__ scale_bits,
+                           unsigned short *__restrict__ dst)
+{
+    constexpr int NB = 16;
+    const int2 ch = chunks[blockIdx.x];
+    const GroupDesc gd = groups[ch.x];
+    const int r = ch.y + (int)threadIdx.x, c0 = NB * (int)blockIdx.y, ld = gd.npad;
+    if (r >= ld || c0 >= ld) return;
+    const double s = __longlong_as_double((long long)scale_bits[ch.x]);
+    const double a = s > 0.0 ? 1.0 / s : 0.0;
+    const double *src = x + gd.off + r + (int64_t)c0 * ld;
+    double v[NB];
+#pragma unroll
+    for (int u = 0; u < NB; u++) v[u] = src[(int64_t)u * ld];
+#pragma unroll
+    for (int u = 0; u < NB; u++) {
+        const int c = c0 + u;
+        const bool pad = r >= gd.n || c >= gd.n;
+        if constexpr (FMT == 2) {
+            reinterpret_cast<float *>(dst)[gd.off + r + (int64_t)c * ld] = pad ? (float)v[u] : (float)(a * v[u]);
+        } else {
+            unsigned short w[NW];
+            split_words<FMT, NW>(pad ? v[u] * word_scale<FMT>() : a * v[u] * word_scale<FMT>(), w);
+            unsigned short *p = dst + NW * gd.off + word_pos(NW, ld, r, c);
+#pragma unroll
+            for (int q = 0; q < NW; q++) p[32 * q] = w[q];
+        }
+    }
+}
+
 // fp64 copy of the bulk result X_kfinal (sum of its words).
 template <int FMT, int NW>
 __global__ __launch_bounds__(256)
@@ -1321,6 +1357,24 @@ hipError_t launch_gather_words(hipStream_t st, int fmt, int nw, int nchunks, con
     else return hipErrorInvalidValue;
 #undef SMX_GW
     return hipGetLastError();
+}
+
+hipError_t launch_words_from_f64(hipStream_t st, int fmt, int nw, int nchunks, const int2 *chunks, int max_npad,
+                                 const GroupDesc *groups, const double *a, const unsigned long long *scale_bits,
+                                 unsigned short *dst)
+{
+    if (nchunks <= 0) return hipSuccess;
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nchunks, (unsigned)((max_npad + 15) / 16)), dim3(256), 0, st, chunks, groups, a,
+                           scale_bits, dst);
+        return hipGetLastError();
+    };
+    if (fmt == 2) return go(words_from_f64_kernel<2, 1>);
+    if (fmt == 0 && nw == 1) return go(words_from_f64_kernel<0, 1>);
+    if (fmt == 0 && nw == 2) return go(words_from_f64_kernel<0, 2>);
+    if (fmt == 1 && nw == 1) return go(words_from_f64_kernel<1, 1>);
+    if (fmt == 1 && nw == 3) return go(words_from_f64_kernel<1, 3>);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_from_words(hipStream_t st, int fmt, int nw, int g0, int ngroups, int max_npad, const GroupDesc *groups,
