@@ -21,6 +21,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace smx;
@@ -230,7 +231,15 @@ struct smx_context {
     DevBuf<unsigned long long> d_scale, d_resid;
     DevBuf<int32_t> d_done, d_kfinal, d_flags, d_ndone;
     DevBuf<double> d_pe, d_pn, d_ne, d_check;
-    DevBuf<int32_t> d_fsum;                 // flag counts of a static-scratch evaluation
+    // pinned host memory the device writes: N, E and flag counts of the last
+    // evaluation, maxima of the value check, progress word of the iteration
+    struct Pinned {
+        HostResult res;
+        double check[2];
+        unsigned long long poll;
+    };
+    Pinned *h = nullptr;
+    uint32_t poll_tag = 0;                  // tags given to steps so far (each wave's follow on)
     DevBuf<int32_t> d_own;
     DevBuf<double> d_tdiag, d_tau_hist;
     // frozen iteration (derivatives, mu search): step counts and scales of a previous evaluation
@@ -255,7 +264,10 @@ struct smx_context {
     int32_t *h_ndone = nullptr;
     int32_t h_ndone_cap = 0;
     std::vector<hipEvent_t> ev_poll;
-    std::vector<hipEvent_t> ev_launch;   // two per product launch (before, after)
+    std::vector<hipEvent_t> ev_launch;   // around the product launches: one event ends a launch and begins the next
+                                         // (timing only: without the system fence a record costs about 2 us less)
+    int32_t n_ev = 0;                    // events of ev_launch the last evaluation recorded
+    std::vector<int32_t> launch_ev;      // index of each launch's first event; its second follows
     std::vector<int32_t> launch_step;    // step k of each product launch
     std::vector<int32_t> launch_kind;    // 0/1 FP64 square/update, 2/3 word square/update (128 x 128
                                          // tiles), 4/5 polish, 6 tangent, 7/8 word square/update (256 x 256)
@@ -838,13 +850,12 @@ int32_t ensure_plan(smx_ctx c)
 
 int32_t validate_values(smx_ctx c)
 {
-    HIP_TRY(c, c->d_check.ensure(2));
-    HIP_TRY(c, hipMemsetAsync(c->d_check.p, 0, 2 * sizeof(double), c->stream));
+    HIP_TRY(c, c->d_check.ensure(2 * kCheckParts));
+    c->h->check[0] = c->h->check[1] = 0.0;
     HIP_TRY(c, launch_check_values(c->stream, c->nnzb, c->d_valoff.p, c->d_brow.p, c->d_bcol.p,
-                                   c->d_mirror.p, c->d_k.p, c->nvals, c->d_check.p));
-    double h[2] = {0, 0};
-    HIP_TRY(c, hipMemcpyAsync(h, c->d_check.p, sizeof h, hipMemcpyDeviceToHost, c->stream));
+                                   c->d_mirror.p, c->d_k.p, c->nvals, c->d_check.p, c->h->check));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const double *h = c->h->check;
     if (!std::isfinite(h[1])) return fail(c, SMX_E_NONFINITE, "K holds NaN or Inf values");
     if (h[0] > 1e-12 * h[1]) {
         char buf[160];
@@ -996,10 +1007,11 @@ int32_t smx_create(int32_t device, smx_ctx *out)
     c->device = device;
     c->uid = ++g_ctx_uid;
     e = hipSetDevice(device);
-    if (e == hipSuccess) e = hipEventCreate(&c->ev_t0);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_t0, hipEventDisableSystemFence);
     if (e == hipSuccess) e = hipEventCreate(&c->ev_t3);
     if (e == hipSuccess) e = c->d_ne.ensure(2);
-    if (e == hipSuccess) e = c->d_fsum.ensure(2);
+    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&c->h), sizeof *c->h);
+    if (e == hipSuccess) std::memset(static_cast<void *>(c->h), 0, sizeof *c->h);
     if (e == hipSuccess && device < kMaxDevices) {
         // the static scratch array's address on this device (once per device)
         std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -1028,7 +1040,7 @@ int32_t smx_destroy(smx_ctx c)
     (void)hipStreamSynchronize(c->stream);
     for (auto *b : {&c->d_k, &c->d_d, &c->d_arena, &c->d_pe, &c->d_pn, &c->d_ne, &c->d_check})
         b->release();
-    c->d_fsum.release();
+    if (c->h) (void)hipHostFree(c->h);
     c->d_xidx.release();
     c->d_xout.release();
     c->d_plist.release();
@@ -1422,7 +1434,7 @@ int32_t eval_prepare(smx_ctx c, const EvalMode &m)
     }
     while ((int32_t)c->ev_wave.size() < 4 * P.nwaves()) {
         hipEvent_t ev;
-        HIP_TRY(c, hipEventCreate(&ev));
+        HIP_TRY(c, hipEventCreateWithFlags(&ev, hipEventDisableSystemFence));
         c->ev_wave.push_back(ev);
     }
     if (c->use_sfix) HIP_TRY(c, c->d_scale_scratch.ensure((size_t)std::max(ng, 1)));
@@ -1613,6 +1625,33 @@ hipError_t gather_slab(smx_ctx c, const Plan &P, const DevView &V, int nch, cons
                          scale);
 }
 
+// Wait until the square of the step with this tag has started (every earlier
+// step is then done) and read the finished-group count it published.  The word
+// sits in host memory; the stream is asked now and then, so that an error on it
+// ends the wait.
+int32_t poll_step(smx_ctx c, uint32_t tag, const int32_t *ndone, int32_t *out)
+{
+    for (uint32_t spin = 1;; spin++) {
+        const unsigned long long v = __atomic_load_n(&c->h->poll, __ATOMIC_ACQUIRE);
+        if ((int32_t)((uint32_t)(v >> 32) - tag) >= 0) {
+            *out = (int32_t)(uint32_t)v;
+            return SMX_OK;
+        }
+        if (spin % 64 == 0) std::this_thread::yield();
+        if (spin % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(c->stream);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();
+                continue;
+            }
+            HIP_TRY(c, e);
+            // idle: the word is as it will stay
+            HIP_TRY(c, hipMemcpy(out, ndone, sizeof *out, hipMemcpyDeviceToHost));
+            return SMX_OK;
+        }
+    }
+}
+
 // Enqueue one evaluation on the context's stream.  `arena` holds the largest
 // wave's three slabs (or the words of three iterates from byte 8E), `pool`
 // the own-column blocks of the polish (2 n_polish + 1 of them).  With
@@ -1640,33 +1679,39 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
     it.tdiag = V.tdiag;
     it.tau_hist = V.tau_hist;
     it.resid_stride = stride;
+    it.poll = nullptr;
+    it.poll_tag = 0;
     if (c->use_sfix) it.scale_bits = c->d_sfix.p;           // the kernels read the frozen scales
     unsigned long long *gather_scale = c->use_sfix ? c->d_scale_scratch.p : it.scale_bits;
     TraceScope tr;
     if (events) HIP_TRY(c, hipEventRecord(c->ev_t0, st));
-    HIP_TRY(c, hipMemsetAsync(gather_scale, 0, sizeof(unsigned long long) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(it.resid_bits, 0, sizeof(unsigned long long) * (size_t)ng * stride, st));
-    HIP_TRY(c, hipMemsetAsync(it.done, 0, sizeof(int32_t) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(it.kfinal, 0, sizeof(int32_t) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(it.flags, 0, sizeof(int32_t) * ng, st));
+    HIP_TRY(c, launch_clear_state(st, ng, gather_scale, (int64_t)ng * stride, it.resid_bits, ng, it.done, it.kfinal,
+                                  it.flags, it.ndone));
 
     c->launch_step.clear();
+    c->launch_ev.clear();
+    c->n_ev = 0;
     c->launch_kind.clear();
     c->launch_wave.clear();
     c->launch_subset.clear();
     int32_t wave = 0;
     int32_t subset = 0;
-    auto timed = [&](int kind, int k, auto &&launch) -> hipError_t {
-        const size_t idx = c->launch_step.size();
-        while (c->ev_launch.size() < 2 * (idx + 1)) {
+    bool chained = false;               // the last recorded event is still the last thing on the stream
+    auto mark = [&]() -> hipError_t {
+        if ((size_t)c->n_ev == c->ev_launch.size()) {
             hipEvent_t ev;
-            hipError_t e = hipEventCreate(&ev);
+            hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableSystemFence);
             if (e != hipSuccess) return e;
             c->ev_launch.push_back(ev);
         }
-        hipError_t e = hipEventRecord(c->ev_launch[2 * idx], st);
+        return hipEventRecord(c->ev_launch[(size_t)c->n_ev++], st);
+    };
+    auto timed = [&](int kind, int k, auto &&launch) -> hipError_t {
+        hipError_t e = chained ? hipSuccess : mark();
+        c->launch_ev.push_back(c->n_ev - 1);
         if (e == hipSuccess) e = launch();
-        if (e == hipSuccess) e = hipEventRecord(c->ev_launch[2 * idx + 1], st);
+        if (e == hipSuccess) e = mark();
+        chained = true;
         c->launch_step.push_back(k);
         c->launch_kind.push_back(kind);
         c->launch_wave.push_back(wave);
@@ -1733,7 +1778,7 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const TileDesc *tls = V.tiles_s + P.tiles_s_beg[wave], *tlb = V.tiles_b + P.tiles_b_beg[wave];
         tr.push("smx gather");
         if (events) HIP_TRY(c, hipEventRecord(c->ev_wave[4 * wave], st));
-        HIP_TRY(c, hipMemsetAsync(it.ndone, 0, sizeof(int32_t), st));
+        if (wave > 0) HIP_TRY(c, launch_clear_state(st, 0, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, it.ndone));
         if (persistent)                         // the step launches (or their graphs) take fresh counters
             HIP_TRY(c, hipMemsetAsync(c->d_tq.p, 0, sizeof(int32_t) * (size_t)(kmax + 1) * 16, st));
         const int nch = (int)(P.chunk_beg[wave + 1] - P.chunk_beg[wave]);
@@ -1836,6 +1881,9 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         // enqueued and finished groups skip on the device
         const int32_t S = use_graphs ? c->graph_steps : 1;
         const int32_t nchunk = kmax / S + 1;
+        chained = false;
+        it.poll = poll && !use_graphs ? &c->h->poll : nullptr;
+        it.poll_tag = c->poll_tag + 1;
         for (int32_t ch = 0; ch < nchunk; ch++) {
             const int32_t k0 = ch * S, k1 = std::min(k0 + S - 1, kmax);
             if (use_graphs) {
@@ -1858,7 +1906,13 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                 HIP_TRY(c, step(st, k0, timing));
             }
             launched = std::max(launched, k1 + 1);
-            if (poll) {
+            if (it.poll) {
+                if (ch >= 1) {
+                    int32_t nd = 0;
+                    if (int32_t e = poll_step(c, it.poll_tag + (uint32_t)ch, it.ndone, &nd)) return e;
+                    if (nd >= wng) break;
+                }
+            } else if (poll) {
                 HIP_TRY(c, hipMemcpyAsync(c->h_ndone + ch, it.ndone, sizeof(int32_t), hipMemcpyDeviceToHost, st));
                 HIP_TRY(c, hipEventRecord(c->ev_poll[ch], st));
                 if (ch >= 1) {
@@ -1867,6 +1921,7 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                 }
             }
         }
+        if (it.poll) c->poll_tag += (uint32_t)kmax + 1;
         if (mixed) {
             // FP64 polish on the own columns: X_{k+p} E from the bulk result X,
             // read from its words (converted exactly on the fly)
@@ -1893,6 +1948,7 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         tr.pop();
     }
     HIP_TRY(c, launch_reduce(st, c->nnzb, V.pe, V.pn, V.ne));
+    HIP_TRY(c, launch_publish(st, ng, V.flags, V.ne, &c->h->res));
     if (tangent) HIP_TRY(c, launch_reduce(st, ng, c->d_dnp.p, c->d_dnp.p, c->d_dn.p));
     c->have_tangent = tangent;
     c->last_sfix = c->use_sfix;
@@ -1938,15 +1994,15 @@ int32_t eig_decompose_wave(smx_ctx c, const Plan &P, const DevView &V, double *a
     if (after_gather) HIP_TRY(c, hipEventRecord(after_gather, st));
     {
         // the Householder reduction dominates the path: timed like the product launches
-        const size_t idx = c->launch_step.size();
-        while (c->ev_launch.size() < 2 * (idx + 1)) {
+        while (c->ev_launch.size() < (size_t)c->n_ev + 2) {
             hipEvent_t evt;
-            HIP_TRY(c, hipEventCreate(&evt));
+            HIP_TRY(c, hipEventCreateWithFlags(&evt, hipEventDisableSystemFence));
             c->ev_launch.push_back(evt);
         }
-        HIP_TRY(c, hipEventRecord(c->ev_launch[2 * idx], st));
+        c->launch_ev.push_back(c->n_ev);
+        HIP_TRY(c, hipEventRecord(c->ev_launch[(size_t)c->n_ev++], st));
         HIP_TRY(c, launch_eig_tridiag(st, g0, wng, P.max_npad, V.gd, a, s, ev));     // s is free until the eigenvectors
-        HIP_TRY(c, hipEventRecord(c->ev_launch[2 * idx + 1], st));
+        HIP_TRY(c, hipEventRecord(c->ev_launch[(size_t)c->n_ev++], st));
         c->launch_step.push_back(0);
         c->launch_kind.push_back(12);
         c->launch_wave.push_back(wave);
@@ -1991,12 +2047,11 @@ int32_t eig_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView &
     hipStream_t st = c->stream;
     const int32_t ng = P.ngroups;
     HIP_TRY(c, hipEventRecord(c->ev_t0, st));
-    HIP_TRY(c, hipMemsetAsync(V.scale, 0, sizeof(unsigned long long) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(V.resid, 0, sizeof(unsigned long long) * (size_t)ng * m.stride, st));
-    HIP_TRY(c, hipMemsetAsync(V.done, 0, sizeof(int32_t) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(V.kfinal, 0, sizeof(int32_t) * ng, st));
-    HIP_TRY(c, hipMemsetAsync(V.flags, 0, sizeof(int32_t) * ng, st));
+    HIP_TRY(c, launch_clear_state(st, ng, V.scale, (int64_t)ng * m.stride, V.resid, ng, V.done, V.kfinal, V.flags,
+                                  nullptr));
     c->launch_step.clear();
+    c->launch_ev.clear();
+    c->n_ev = 0;
     c->launch_kind.clear();
     c->launch_wave.clear();
     c->launch_subset.clear();
@@ -2010,6 +2065,7 @@ int32_t eig_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView &
         HIP_TRY(c, hipEventRecord(c->ev_wave[4 * wave + 3], st));
     }
     HIP_TRY(c, launch_reduce(st, c->nnzb, V.pe, V.pn, V.ne));
+    HIP_TRY(c, launch_publish(st, ng, V.flags, V.ne, &c->h->res));
     HIP_TRY(c, hipEventRecord(c->ev_t3, st));
     c->have_tangent = false;
     c->last_sfix = false;
@@ -2223,7 +2279,6 @@ int32_t smx_evaluate_static(smx_ctx c)
     if (int32_t e = eval_enqueue(c, m, P, V, reinterpret_cast<double *>(base + L.arena),
                                  reinterpret_cast<double *>(base + L.pool), false, false, false, false))
         return e;
-    HIP_TRY(c, launch_count_flags(st, P.ngroups, V.flags, c->d_fsum.p));
     c->eval_static = true;
     return SMX_OK;
 }
@@ -2233,20 +2288,7 @@ int32_t smx_wait(smx_ctx c)
     if (!c) return SMX_E_INVALID;
     if (int32_t st = need_sync_results(c)) return st;
     if (int32_t st = check_guards(c)) return st;
-    int nc = 0, nf = 0;
-    if (c->eval_static) {
-        int32_t cnt[2] = {0, 0};
-        HIP_TRY(c, hipMemcpy(cnt, c->d_fsum.p, sizeof cnt, hipMemcpyDeviceToHost));
-        nc = cnt[0];
-        nf = cnt[1];
-    } else {
-        std::vector<int32_t> fl((size_t)c->plan.ngroups);
-        HIP_TRY(c, hipMemcpy(fl.data(), c->d_flags.p, fl.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-        for (int32_t f : fl) {
-            nc += (f & 1) != 0;
-            nf += (f & 2) != 0;
-        }
-    }
+    const int nc = c->h->res.nflag[0], nf = c->h->res.nflag[1];
     if (nf) return fail(c, SMX_E_NONFINITE, std::to_string(nf) + " group(s) produced non-finite iterates");
     if (nc)
         return fail(c, SMX_E_NOT_CONVERGED,
@@ -2301,7 +2343,8 @@ int32_t smx_get_d_expanded(smx_ctx c, const int64_t *index, int64_t n_out, doubl
 static int32_t read_ne(smx_ctx c, double *ne)
 {
     if (int32_t st = need_sync_results(c)) return st;
-    HIP_TRY(c, hipMemcpy(ne, c->d_ne.p, 2 * sizeof(double), hipMemcpyDeviceToHost));
+    ne[0] = c->h->res.ne[0];
+    ne[1] = c->h->res.ne[1];
     return SMX_OK;
 }
 
@@ -2460,7 +2503,8 @@ int32_t smx_get_launch_profile(smx_ctx c, int32_t cap, float *ms, double *algo_f
         if (kind) kind[l] = kd;
         if (ms) {
             float t = 0;
-            HIP_TRY(c, hipEventElapsedTime(&t, c->ev_launch[2 * l], c->ev_launch[2 * l + 1]));
+            const size_t q = (size_t)c->launch_ev[(size_t)l];
+            HIP_TRY(c, hipEventElapsedTime(&t, c->ev_launch[q], c->ev_launch[q + 1]));
             ms[l] = t;
         }
         if (algo_flops) {
@@ -2886,7 +2930,7 @@ int32_t smx_find_mu_eig(smx_ctx c, double n_target, double tol, int32_t max_step
     double *arena = arena_base(c), *pool = pool_base(c);
     // 1. every group's eigenvalues and Algorithm 1's weights, at mu0
     const double mu0 = c->mu;
-    HIP_TRY(c, hipMemsetAsync(V.scale, 0, sizeof(unsigned long long) * ng, st));
+    HIP_TRY(c, launch_clear_state(st, ng, V.scale, 0, nullptr, 0, nullptr, nullptr, nullptr, nullptr));
     for (int32_t wave = 0; wave < P.nwaves(); wave++)
         if (int32_t e = eig_decompose_wave(c, P, V, arena, pool, wave)) return e;
     // 2. multisection on N(mu) = sum_g sum_l w_gl f(lambda_gl - mu), monotone in
@@ -2937,9 +2981,8 @@ int32_t smx_find_mu_eig(smx_ctx c, double n_target, double tol, int32_t max_step
         const double mu_dec = c->mu;
         c->mu = mu0;                                  // the decomposition's shift
         HIP_TRY(c, hipEventRecord(c->ev_t0, st));
-        HIP_TRY(c, hipMemsetAsync(V.kfinal, 0, sizeof(int32_t) * ng, st));
-        HIP_TRY(c, hipMemsetAsync(V.flags, 0, sizeof(int32_t) * ng, st));
-        HIP_TRY(c, hipMemsetAsync(V.resid, 0, sizeof(unsigned long long) * (size_t)ng * m.stride, st));
+        HIP_TRY(c, launch_clear_state(st, 0, nullptr, (int64_t)ng * m.stride, V.resid, ng, nullptr, V.kfinal, V.flags,
+                                      nullptr));
         HIP_TRY(c, hipEventRecord(c->ev_wave[0], st));
         HIP_TRY(c, hipEventRecord(c->ev_wave[1], st));
         HIP_TRY(c, hipEventRecord(c->ev_wave[2], st));
@@ -2948,8 +2991,11 @@ int32_t smx_find_mu_eig(smx_ctx c, double n_target, double tol, int32_t max_step
         if (e) return e;
         HIP_TRY(c, hipEventRecord(c->ev_wave[3], st));
         HIP_TRY(c, launch_reduce(st, c->nnzb, V.pe, V.pn, V.ne));
+        HIP_TRY(c, launch_publish(st, ng, V.flags, V.ne, &c->h->res));
         HIP_TRY(c, hipEventRecord(c->ev_t3, st));
         c->launch_step.clear();
+        c->launch_ev.clear();
+        c->n_ev = 0;
         c->launch_kind.clear();
         c->launch_wave.clear();
         c->launch_subset.clear();
@@ -3085,6 +3131,8 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     it.tdiag = c->d_tdiag.p;
     it.tau_hist = c->d_tau_hist.p;
     it.resid_stride = c->last_stride;
+    it.poll = nullptr;
+    it.poll_tag = 0;
     const int scratch_slot = c->last_max_iter + 1;    // residual slot the adjoint squares may use
     const int nt = (int)P.tiles_d.size();
     const TileDesc *tl = c->d_tiles_d.p;

@@ -57,7 +57,23 @@ struct IterState {
                                       // at GroupDesc::rinfo_off + i (reduced-precision bulk)
     double *tau_hist;                 // [ngroups * resid_stride] Tr(I - X_k^2) per step
     int32_t resid_stride;             // steps 0..max_iter, then one slot per polish step
+    // progress word in host memory (nullptr: none): the square of step k writes
+    // (poll_tag + k) << 32 | *ndone when it starts, i.e. with every earlier step done
+    unsigned long long *poll;
+    uint32_t poll_tag;
 };
+
+// The host follows the iteration by this word instead of by a copy and an event
+// per step: back-to-back kernels have no gap, an event record costs about 5 us and
+// a 4-byte copy 4 us and another gap, against kernels of 6-25 us on small batches.
+__device__ inline void publish_step(const IterState &it, int k)
+{
+    if (it.poll && blockIdx.x == 0 && threadIdx.x == 0) {
+        const unsigned int nd = (unsigned int)__hip_atomic_load(it.ndone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(it.poll, (unsigned long long)(it.poll_tag + (uint32_t)k) << 32 | nd, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
 
 // Row r of A_g = K[R(g), R(g)] - mu I over the columns c < n_g (Sec. III-A
 // step 1), block column by block column: emit(c, v) for every column, zero
@@ -269,8 +285,17 @@ hipError_t launch_polish_flags(hipStream_t st, int g0, int ngroups, const IterSt
 
 hipError_t launch_reduce(hipStream_t st, int64_t n, const double *part_e, const double *part_n,
                          double *out2);
-// out2[0] / out2[1] = number of groups with flag bit 0 / bit 1 set.
-hipError_t launch_count_flags(hipStream_t st, int ngroups, const int32_t *flags, int32_t *out2);
+// What the host reads of an evaluation, in pinned host memory: N and E, the number
+// of groups with flag bit 0 / bit 1 set.
+struct HostResult {
+    double ne[2];
+    int32_t nflag[2];
+};
+hipError_t launch_publish(hipStream_t st, int ngroups, const int32_t *flags, const double *ne, HostResult *res);
+// The per-evaluation state cleared in one launch (any pointer may be null).
+hipError_t launch_clear_state(hipStream_t st, int64_t nscale, unsigned long long *scale, int64_t nresid,
+                              unsigned long long *resid, int64_t ngroups, int32_t *done, int32_t *kfinal,
+                              int32_t *flags, int32_t *ndone);
 // dst[0 .. n_dst) = 0, then dst[idx[q]] = src[q] for q < n_src (idx checked on the host).
 hipError_t launch_expand_values(hipStream_t st, int64_t n_src, const int64_t *idx, const double *src, int64_t n_dst,
                                 double *dst);
@@ -286,7 +311,9 @@ hipError_t launch_own_trace(hipStream_t st, int g0, int ngroups, const GroupDesc
 
 hipError_t launch_check_values(hipStream_t st, int64_t nblocks, const int64_t *valoff,
                                const int32_t *blk_rows, const int32_t *blk_cols,
-                               const int64_t *mirror, const double *kvals, int64_t nvals, double *out2);
+                               const int64_t *mirror, const double *kvals, int64_t nvals, double *part, double *res);
+// Pairs of partial maxima launch_check_values writes to part (res: the two maxima, host memory).
+constexpr int kCheckParts = 1024;
 
 // ---- batched symmetric eigensolver (finite temperature, Algorithm 1) --------
 // Largest submatrix dimension of the eigensolver path (its workgroups keep

@@ -616,7 +616,7 @@ void polish_flags_kernel(int ngroups, IterState it, int slot, double tol, int g0
 // out2[0] = groups with flag bit 0 (not converged), out2[1] = groups with bit 1
 // (non-finite), over flags[0 .. ngroups-1]; one workgroup, no atomics.
 __global__ __launch_bounds__(1024)
-void count_flags_kernel(int ngroups, const int32_t *__restrict__ flags, int32_t *__restrict__ out2)
+void publish_kernel(int ngroups, const int32_t *__restrict__ flags, const double *__restrict__ ne, HostResult *res)
 {
     __shared__ int s0[16], s1[16];
     const int t = threadIdx.x;
@@ -640,9 +640,29 @@ void count_flags_kernel(int ngroups, const int32_t *__restrict__ flags, int32_t 
             a0 += s0[w];
             a1 += s1[w];
         }
-        out2[0] = a0;
-        out2[1] = a1;
+        res->nflag[0] = a0;
+        res->nflag[1] = a1;
+        res->ne[0] = ne[0];
+        res->ne[1] = ne[1];
     }
+}
+
+__global__ __launch_bounds__(256)
+void clear_state_kernel(int64_t nscale, unsigned long long *__restrict__ scale, int64_t nresid,
+                        unsigned long long *__restrict__ resid, int64_t ngroups, int32_t *__restrict__ done,
+                        int32_t *__restrict__ kfinal, int32_t *__restrict__ flags, int32_t *__restrict__ ndone)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    if (scale)
+        for (int64_t i = i0; i < nscale; i += step) scale[i] = 0;
+    if (resid)
+        for (int64_t i = i0; i < nresid; i += step) resid[i] = 0;
+    for (int64_t i = i0; i < ngroups; i += step) {
+        if (done) done[i] = 0;
+        if (kfinal) kfinal[i] = 0;
+        if (flags) flags[i] = 0;
+    }
+    if (ndone && i0 == 0) *ndone = 0;
 }
 
 // Fixed-order sum of the per-block partials (one workgroup): deterministic.
@@ -681,7 +701,7 @@ void reduce_kernel(int64_t n, const double *__restrict__ pe, const double *__res
 // Validation of K's values: max|K_IJ - K_JI^T| and max|K| (NaN/Inf -> +Inf).
 // Bound by HBM (K is read once; the mirrored block mostly comes from a cache).
 // A fixed grid walks the stored blocks, L lanes per block, and every workgroup
-// ends with one atomic pair: one pair per stored block serialised on the two
+// writes one pair of maxima: an atomic pair per stored block serialised on the two
 // result words (about 20 ns each: 6.2 ms for water1024's 330,000 blocks, 27 ms
 // for the 1.2 million one-element blocks of the split water256e, against
 // 0.10 ms and 0.04 ms this way).  Maxima do not depend on the order.
@@ -690,7 +710,7 @@ __global__ __launch_bounds__(256)
 void check_values_kernel(int64_t nblocks, const int64_t *__restrict__ valoff,
                          const int32_t *__restrict__ brow, const int32_t *__restrict__ bcol,
                          const int64_t *__restrict__ mirror, const double *__restrict__ kv,
-                         unsigned long long *__restrict__ out2)
+                         double *__restrict__ part)
 {
     __shared__ double sm[2][4];
     const int sub = threadIdx.x & (L - 1);
@@ -720,7 +740,30 @@ void check_values_kernel(int64_t nblocks, const int64_t *__restrict__ valoff,
     __syncthreads();
     if (threadIdx.x < 2) {
         const double *s = sm[threadIdx.x];
-        atomic_max_nonneg(out2 + threadIdx.x, fmax(fmax(s[0], s[1]), fmax(s[2], s[3])));
+        part[2 * blockIdx.x + threadIdx.x] = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
+    }
+}
+
+// The maxima over the workgroups' partial maxima, to host memory.
+__global__ __launch_bounds__(256)
+void check_max_kernel(int nparts, const double *__restrict__ part, double *res)
+{
+    __shared__ double sm[2][4];
+    double m0 = 0.0, m1 = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += 256) {
+        m0 = fmax(m0, part[2 * i]);
+        m1 = fmax(m1, part[2 * i + 1]);
+    }
+    m0 = wave_max(m0);
+    m1 = wave_max(m1);
+    if ((threadIdx.x & 63) == 0) {
+        sm[0][threadIdx.x >> 6] = m0;
+        sm[1][threadIdx.x >> 6] = m1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const double *s = sm[threadIdx.x];
+        res[threadIdx.x] = fmax(fmax(s[0], s[1]), fmax(s[2], s[3]));
     }
 }
 
@@ -955,9 +998,19 @@ void clear_values_kernel(int64_t n, double *__restrict__ dst)
         dst[q] = 0.0;
 }
 
-hipError_t launch_count_flags(hipStream_t st, int ngroups, const int32_t *flags, int32_t *out2)
+hipError_t launch_publish(hipStream_t st, int ngroups, const int32_t *flags, const double *ne, HostResult *res)
 {
-    hipLaunchKernelGGL(count_flags_kernel, dim3(1), dim3(1024), 0, st, ngroups, flags, out2);
+    hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(1024), 0, st, ngroups, flags, ne, res);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear_state(hipStream_t st, int64_t nscale, unsigned long long *scale, int64_t nresid,
+                              unsigned long long *resid, int64_t ngroups, int32_t *done, int32_t *kfinal,
+                              int32_t *flags, int32_t *ndone)
+{
+    const int64_t n = std::max<int64_t>({nscale, nresid, ngroups, 1});
+    hipLaunchKernelGGL(clear_state_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, st,
+                       nscale, scale, nresid, resid, ngroups, done, kfinal, flags, ndone);
     return hipGetLastError();
 }
 
@@ -970,25 +1023,31 @@ hipError_t launch_reduce(hipStream_t st, int64_t n, const double *part_e, const 
 
 hipError_t launch_check_values(hipStream_t st, int64_t nblocks, const int64_t *valoff,
                                const int32_t *blk_rows, const int32_t *blk_cols,
-                               const int64_t *mirror, const double *kvals, int64_t nvals, double *out2)
+                               const int64_t *mirror, const double *kvals, int64_t nvals, double *part,
+                               double *res)
 {
     if (nblocks <= 0) return hipSuccess;
     // Lanes per block by the mean block: more lanes than elements idle (the
     // one-element blocks of the split water256e: 0.42 ms with 64 lanes, 0.04 ms
     // with one), and a wave that spans several blocks has more of the dependent
     // index loads in flight (water1024, mean 47 elements: 0.13 ms with 64 lanes,
-    // 0.10 ms with 8); from 512 elements on, 64 lanes have eight loads each.
+    // 0.10 ms with 8); from 512 elements on, 64 lanes have eight loads each.  Few
+    // blocks leave the chip idle with less (75 of 190: 36 us with 8 lanes, 7 us
+    // with 64).
     // Four workgroups per CU.
-    unsigned long long *o = reinterpret_cast<unsigned long long *>(out2);
+    int64_t grid = 0;
     const auto go = [&](auto kernel, int lanes) {
-        const int64_t grid = std::min<int64_t>((nblocks * lanes + 255) / 256, 1024);
+        grid = std::min<int64_t>((nblocks * lanes + 255) / 256, kCheckParts);
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), 0, st, nblocks, valoff, blk_rows, blk_cols, mirror,
-                           kvals, o);
+                           kvals, part);
     };
     const int64_t mean = nvals / nblocks;
-    if (mean >= 512) go(check_values_kernel<64>, 64);
+    if (mean >= 512 || (mean >= 4 && nblocks * 64 <= 256 * kCheckParts)) go(check_values_kernel<64>, 64);
     else if (mean >= 4) go(check_values_kernel<8>, 8);
     else go(check_values_kernel<1>, 1);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(check_max_kernel, dim3(1), dim3(256), 0, st, (int)grid, part, res);
     return hipGetLastError();
 }
 

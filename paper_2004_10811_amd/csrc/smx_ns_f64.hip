@@ -73,6 +73,7 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ double As[2][BM][SK];
     __shared__ double Bs[2][BM][SK];
 
+    if (MODE == 0 || MODE == 5) publish_step(it, k);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                            // idle slot of the launch order

@@ -639,6 +639,7 @@ void ns_words_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__rest
                      unsigned short *__restrict__ out, IterState it, int k,
                      double switch_tol, int kmax)
 {
+    if (MODE == 0 || MODE == 2) publish_step(it, k);
     ns_words_tile<FMT, NW, MODE, RP>(tiles[blockIdx.x], groups, xin, bin, out, it, k, switch_tol, kmax);
 }
 
@@ -658,6 +659,7 @@ void ns_words_persistent(const TileDesc *__restrict__ tiles_x, const int32_t *__
                          unsigned short *__restrict__ out, IterState it, int k, double switch_tol, int kmax)
 {
     __shared__ int s_q;
+    if (MODE == 0) publish_step(it, k);
     // s_getreg of HW_REG_XCC_ID (id 20, bits 3:0)
     const int x0 = (int)(__builtin_amdgcn_s_getreg((3 << 11) | (0 << 6) | 20) & 7);
     for (int d = 0; d < 8; d++) {
@@ -710,6 +712,7 @@ void ns_words256_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__r
     unsigned short *Ls = reinterpret_cast<unsigned short *>(smem);   // [stage][2 operands][NW][BM2][BK]
     float *Cs = reinterpret_cast<float *>(smem);                     // staging after the K loop
 
+    if (MODE == 0 || MODE == 2) publish_step(it, k);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
@@ -957,6 +960,7 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ float As[2][TE][SF];
     __shared__ float Bs[2][TE][SF];
 
+    if (MODE == 0 || MODE == 2) publish_step(it, k);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
