@@ -1772,7 +1772,10 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const int ntd = (int)(P.tiles_d_beg[wave + 1] - P.tiles_d_beg[wave]);
         const TileDesc *tld = V.tiles_d + P.tiles_d_beg[wave];
         // one- and two-word products: the size buckets (128 x 128 and 256 x 256 tiles)
-        const bool buckets = mixed && fmt != 2 && nw <= 2;
+        // few tiles: all groups on 32 x 32 tiles, unless the caller chose a tile
+        // shape or operand stream
+        const bool words32 = mixed && fmt != 2 && P.edge_d == 32 && c->big_min_npad == 0 && c->kernel_variant == 0;
+        const bool buckets = mixed && fmt != 2 && nw <= 2 && !words32;
         const int nts = (int)(P.tiles_s_beg[wave + 1] - P.tiles_s_beg[wave]);
         const int ntb = (int)(P.tiles_b_beg[wave + 1] - P.tiles_b_beg[wave]);
         const TileDesc *tls = V.tiles_s + P.tiles_s_beg[wave], *tlb = V.tiles_b + P.tiles_b_beg[wave];
@@ -1848,6 +1851,9 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                     else if (fmt == 2)
                         r = run(kind128, [&] { return launch_ns_f32(s, mode, P.edge_d, ntd, tld, V.gd, x, y, o, it, k,
                                                                     c->switch_tol, kmax); });
+                    else if (words32)
+                        r = run(kind128, [&] { return launch_ns_words32(s, fmt, nw, mode, ntd, tld, V.gd, x, y, o, it, k,
+                                                                        c->switch_tol, kmax); });
                     else if (persistent && mode <= 1)
                         r = run(kind128, [&] {
                             return launch_ns_words_persistent(s, fmt, nw, mode, pers_nwg, V.tiles_sx + P.sx_wbeg[wave],

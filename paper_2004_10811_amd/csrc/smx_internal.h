@@ -213,6 +213,10 @@ int words_persistent_blocks_per_cu(int fmt, int nw);
 hipError_t launch_ns_words(hipStream_t st, int fmt, int nw, int mode, int variant, int ntiles, const TileDesc *tiles,
                            const GroupDesc *groups, const unsigned short *x, const unsigned short *b,
                            unsigned short *out, const IterState &it, int k, double switch_tol, int kmax);
+// The same on the lower 32 x 32 tiles of a small batch.
+hipError_t launch_ns_words32(hipStream_t st, int fmt, int nw, int mode, int ntiles, const TileDesc *tiles,
+                             const GroupDesc *groups, const unsigned short *x, const unsigned short *b,
+                             unsigned short *out, const IterState &it, int k, double switch_tol, int kmax);
 // The same for FP32 values (one per element, column-major like the FP64 slabs), on
 // the lower tiles of the FP64 products (edge 32 or 64).
 hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles, const GroupDesc *groups,

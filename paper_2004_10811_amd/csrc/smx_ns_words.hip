@@ -936,6 +936,163 @@ void ns_words256_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__r
     }
 }
 
+// The word products on 32 x 32 output tiles, for batches whose 128 x 128 tiles
+// leave most CUs idle: four waves of one 16 x 16 block each, K steps of 32
+// through double-buffered LDS with the loads two steps ahead in two register
+// sets (the FP32 kernel's stream), stores straight from the accumulators.  The
+// order of an element's products is that of the other tiles: bitwise the same.
+// What bounds it: the latency of a K step.  16 groups of n ~ 270, square / update
+// per launch: 128 x 128 tiles (96 of them) 23 / 18 us, this @W32S@ / @W32U@ us.
+template <int FMT, int NW, int MODE>
+__global__ __launch_bounds__(256)
+void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
+                       const unsigned short *__restrict__ xin, const unsigned short *__restrict__ bin,
+                       unsigned short *__restrict__ out, IterState it, int k, double switch_tol, int kmax)
+{
+    constexpr int TE = 32;
+    constexpr int CH = 4 * NW;          // 16-B chunks of a column and K step (word w: chunks 4 w .. 4 w + 3)
+    constexpr int NCH = TE * CH;        // chunks of an operand's K step
+    constexpr int NQ = (NCH + 255) / 256;
+    constexpr int SH = 32 * NW + 8;     // LDS column stride in halves (breaks bank aliasing)
+    __shared__ __attribute__((aligned(16))) unsigned short As[2][TE][SH];
+    __shared__ __attribute__((aligned(16))) unsigned short Bs[2][TE][SH];
+
+    if (MODE == 0 || MODE == 2) publish_step(it, k);
+    const TileDesc td = tiles[blockIdx.x];
+    const int g = td.x;
+    if (g < 0) return;                  // idle slot of the launch order
+    if (it.done[g]) return;
+    const int ti = td.y >> 16, tj = td.y & 0xffff;
+    const GroupDesc gd = groups[g];
+    const int ld = gd.npad;
+    if (MODE == 1 && bulk_stop(it, gd, g, k, ti == 0 && tj == 0 && threadIdx.x == 0, threadIdx.x & 63, switch_tol,
+                               kmax, NW > 1))
+        return;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int wr = wave >> 1, wc = wave & 1;
+    const int li = lane & 15;
+    const int lg = lane >> 4;
+
+    // chunk q*256 + tid of an operand's K step: column id / CH, chunk id % CH
+    // (lanes past the last chunk repeat it; n_pad is a multiple of 32, so the
+    // tile's columns all exist)
+    const unsigned short *pa[NQ], *pb[NQ];
+    int dst[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        const int id = min(q * 256 + tid, NCH - 1), cl = id / CH, ch = id % CH;
+        pa[q] = xin + NW * gd.off + (int64_t)(ti * TE + cl) * ld * NW + 8 * ch;
+        pb[q] = bin + NW * gd.off + (int64_t)(tj * TE + cl) * ld * NW + 8 * ch;
+        dst[q] = cl * SH + 8 * ch;
+    }
+    const bool wave_live = !(ti == tj && wr < wc);
+
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int nk = ld / BK;
+    u16x8 r0[2 * NQ], r1[2 * NQ];
+    auto gload = [&](int kt, u16x8 (&r)[2 * NQ]) {
+        const int kk = min(kt, nk - 1) * (BK * NW);
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            r[q] = *reinterpret_cast<const u16x8 *>(pa[q] + kk);
+            r[NQ + q] = *reinterpret_cast<const u16x8 *>(pb[q] + kk);
+        }
+    };
+    auto sstore = [&](int buf, const u16x8 (&r)[2 * NQ]) {
+#pragma unroll
+        for (int q = 0; q < NQ; q++) {
+            *reinterpret_cast<u16x8 *>(&As[buf][0][0] + dst[q]) = r[q];
+            *reinterpret_cast<u16x8 *>(&Bs[buf][0][0] + dst[q]) = r[NQ + q];
+        }
+    };
+    auto products = [&](int buf) {
+        if (!wave_live) return;
+        u16x8 av[NW], bv[NW];
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            av[w] = *reinterpret_cast<const u16x8 *>(&As[buf][wr * 16 + li][32 * w + 8 * lg]);
+            bv[w] = *reinterpret_cast<const u16x8 *>(&Bs[buf][wc * 16 + li][32 * w + 8 * lg]);
+        }
+#pragma unroll
+        for (int pr = npairs<NW>() - 1; pr >= 0; pr--)      // least significant products first
+            acc = mfma16<FMT>(av[pair_p(pr)], bv[pair_q(pr)], acc);
+    };
+    gload(0, r0);
+    gload(1, r1);
+    sstore(0, r0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {
+        gload(kt + 2, r0);
+        products(0);
+        sstore(1, r1);
+        __syncthreads();
+        if (kt + 1 >= nk) break;
+        gload(kt + 3, r1);
+        products(1);
+        sstore(0, r0);
+        __syncthreads();
+    }
+    if (!wave_live) return;
+
+    // lane l, register v: row 4 (l / 16) + v, column l % 16 of the wave's block
+    constexpr float inv_s2 = (float)(1.0 / (word_scale<FMT>() * word_scale<FMT>()));
+    constexpr float sc = (float)word_scale<FMT>();
+    const int n = gd.n;
+    const int c = tj * TE + wc * 16 + li, ra = ti * TE + wr * 16 + 4 * lg;
+    unsigned short *og = out + NW * gd.off;
+    float rmax = 0.f;
+    unsigned short wv[NW][4];
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+        const int r = ra + v;
+        const float t = acc[v] * inv_s2;
+        if ((MODE == 0 || MODE == 2) && r < n && c < n && r >= c) {
+            float d = fabsf(t - (r == c ? 1.f : 0.f));
+            if (!(d <= 3.4e38f)) d = __builtin_huge_valf();
+            rmax = fmaxf(rmax, d);
+            if (r == c) it.tdiag[gd.rinfo_off + r] = 1.0 - (double)t;
+        }
+        float tv = 0.f;
+        if constexpr (MODE == 3) {      // T at this position: the sum of its words, as load8_words
+            const unsigned short *p = xin + NW * gd.off + word_pos(NW, ld, r, c);
+            float s = 0.f;
+#pragma unroll
+            for (int w = NW - 1; w >= 0; w--) s += from_word_f<FMT>(p[32 * w]);
+            tv = s * (float)(1.0 / word_scale<FMT>());
+        }
+        float rem = out_value<MODE>(t, tv, r, c) * sc;
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            wv[w][v] = to_word_f<FMT>(rem);
+            rem -= from_word_f<FMT>(wv[w][v]);
+        }
+    }
+    typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+        unsigned short *p = og + word_pos(NW, ld, ra, c) + 32 * w;     // rows ra .. ra + 3 of a 32-row block
+        if (ra >= c) {
+            *reinterpret_cast<u16x4 *>(p) = u16x4{wv[w][0], wv[w][1], wv[w][2], wv[w][3]};
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+                if (ra + v >= c) p[v] = wv[w][v];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; v++)
+            if (ra + v > c) og[word_pos(NW, ld, c, ra + v) + 32 * w] = wv[w][v];
+    }
+    if (MODE == 0 || MODE == 2) {
+        double rm = (double)rmax;
+        rm = wave_max(rm);
+        if (lane == 0)
+            atomicMax(it.resid_bits + (int64_t)g * it.resid_stride + k, (unsigned long long)__double_as_longlong(rm));
+    }
+}
+
 // FP32 products (v_mfma_f32_16x16x4_f32, FP32 accumulation): the iterate is
 // held as one FP32 value per element.  Stopping rule as the word products;
 // tiles, operand stream and stores as the FP64 products: 2 x 2 waves of WB x WB
@@ -1257,6 +1414,31 @@ hipError_t launch_ns_words(hipStream_t st, int fmt, int nw, int mode, int varian
     if (fmt == 0 && nw == 2) return launch_words_t<0, 2>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     if (fmt == 1 && nw == 1) return launch_words_t<1, 1>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
     if (fmt == 1 && nw == 3) return launch_words_t<1, 3>(st, mode, variant, ntiles, tiles, groups, x, b, out, it, k, switch_tol, kmax);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_ns_words32(hipStream_t st, int fmt, int nw, int mode, int ntiles, const TileDesc *tiles,
+                             const GroupDesc *groups, const unsigned short *x, const unsigned short *b,
+                             unsigned short *out, const IterState &it, int k, double switch_tol, int kmax)
+{
+    if (ntiles <= 0) return hipSuccess;
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(256), 0, st, tiles, groups, x, b, out, it, k, switch_tol, kmax);
+        return hipGetLastError();
+    };
+#define SMX_W32(F, N)                                     \
+    switch (mode) {                                       \
+    case 0: return go(ns_words32_kernel<F, N, 0>);        \
+    case 1: return go(ns_words32_kernel<F, N, 1>);        \
+    case 2: return go(ns_words32_kernel<F, N, 2>);        \
+    case 3: return go(ns_words32_kernel<F, N, 3>);        \
+    default: return hipErrorInvalidValue;                 \
+    }
+    if (fmt == 0 && nw == 1) { SMX_W32(0, 1) }
+    if (fmt == 0 && nw == 2) { SMX_W32(0, 2) }
+    if (fmt == 1 && nw == 1) { SMX_W32(1, 1) }
+    if (fmt == 1 && nw == 3) { SMX_W32(1, 3) }
+#undef SMX_W32
     return hipErrorInvalidValue;
 }
 
