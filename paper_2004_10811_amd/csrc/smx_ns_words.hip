@@ -942,7 +942,10 @@ void ns_words256_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__r
 // sets (the FP32 kernel's stream), stores straight from the accumulators.  The
 // order of an element's products is that of the other tiles: bitwise the same.
 // What bounds it: the latency of a K step.  16 groups of n ~ 270, square / update
-// per launch: 128 x 128 tiles (96 of them) 23 / 18 us, this @W32S@ / @W32U@ us.
+// per launch: 128 x 128 tiles (96 of them) 23 / 18 us, this 9.4 / 8.2 us.
+// The same stream on larger tiles loses to the 128 x 128 kernel where those fill
+// the chip (water1024, 2.41 ms a launch): edge 64 3.1 ms (twice the operand bytes),
+// 96 2.9 ms, 128 2.6 ms (2.5 ms with its epilogue through LDS; two workgroups per CU).
 template <int FMT, int NW, int MODE>
 __global__ __launch_bounds__(256)
 void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
