@@ -100,7 +100,10 @@ struct Plan {
     std::vector<TileDesc> tiles;
     std::vector<int2> chunks;
     std::vector<RowInfo> rinfo;
-    std::vector<int32_t> bmap;
+    std::vector<int32_t> rows;        // block rows of the groups, ascending; group g's start at boff_off - g
+    int64_t n_map = 0;                // entries of the block maps
+    int32_t max_m = 0;
+    std::vector<int32_t> bmap;        // the block maps on the host, once build_map has run
     std::vector<int32_t> boffs;
     std::vector<ScatterDesc> scat;
     std::vector<int32_t> own_list;    // own columns of every group (submatrix column indices)
@@ -214,7 +217,8 @@ struct smx_context {
     DevBuf<int32_t> d_xbeg, d_tq;           // per-XCD list offsets, counters of the persistent word products
     DevBuf<int2> d_chunks;
     DevBuf<RowInfo> d_rinfo;
-    DevBuf<int32_t> d_bmap, d_boffs;
+    DevBuf<int32_t> d_bmap, d_boffs, d_rows, d_rowidx;
+    DevBuf<int64_t> d_colptr;
     DevBuf<ScatterDesc> d_scat;
     // device: work
     DevBuf<double> d_arena;                 // one wave's slabs (see kArenaBytesPerElem), when no
@@ -410,22 +414,21 @@ int32_t build_plan(smx_ctx c, Plan &P)
     std::vector<int32_t> pos(nblk, -1);
     std::vector<char> mark(nblk, 0);
     P.scat.assign((size_t)c->nnzb, ScatterDesc{-1, 0, 0, 0});
-    std::vector<int32_t> rows;
-    rows.reserve(1024);
     for (int32_t g = 0; g < ng; g++) {
-        rows.clear();
+        const size_t r0 = P.rows.size();
         for (int32_t q = c->grp_ptr[g]; q < c->grp_ptr[g + 1]; q++) {
             const int32_t j = c->grp_blocks[q];
             for (int64_t p = c->col_ptr[j]; p < c->col_ptr[j + 1]; p++) {
                 const int32_t i = c->row_idx[p];
                 if (!mark[i]) {
                     mark[i] = 1;
-                    rows.push_back(i);
+                    P.rows.push_back(i);
                 }
             }
         }
-        std::sort(rows.begin(), rows.end());
-        const int32_t m = (int32_t)rows.size();
+        std::sort(P.rows.begin() + r0, P.rows.end());
+        const int32_t *rows = P.rows.data() + r0;
+        const int32_t m = (int32_t)(P.rows.size() - r0);
         GroupDesc d{};
         d.m = m;
         d.boff_off = (int32_t)P.boffs.size();
@@ -447,15 +450,9 @@ int32_t build_plan(smx_ctx c, Plan &P)
             for (int32_t rr = 0; rr < b; rr++) P.rinfo.push_back(RowInfo{t, rr | (b << 16)});
         }
         for (int32_t r = d.n; r < d.npad; r++) P.rinfo.push_back(RowInfo{0, 0});
-        d.map_off = (int64_t)P.bmap.size();
-        P.bmap.resize(P.bmap.size() + (size_t)m * m, -1);
-        for (int32_t tb = 0; tb < m; tb++) {
-            const int32_t j = rows[tb];
-            for (int64_t p = c->col_ptr[j]; p < c->col_ptr[j + 1]; p++) {
-                const int32_t a = pos[c->row_idx[p]];
-                if (a >= 0) P.bmap[(size_t)d.map_off + a + (size_t)m * tb] = (int32_t)p;
-            }
-        }
+        d.map_off = P.n_map;
+        P.n_map += (int64_t)m * m;
+        P.max_m = std::max(P.max_m, m);
         d.own_off = (int32_t)P.own_list.size();
         int32_t ocol = 0;
         for (int32_t q = c->grp_ptr[g]; q < c->grp_ptr[g + 1]; q++) {
@@ -504,6 +501,29 @@ int32_t build_plan(smx_ctx c, Plan &P)
     for (int64_t p = 0; p < c->nnzb; p++)
         if (P.scat[p].g < 0) return fail(c, SMX_E_INVALID, "internal: stored block without a group");
     return SMX_OK;
+}
+
+// The block maps on the host, for what needs them there: the tables of a static
+// evaluation, the adjoint's contribution lists and the debug checks.  An ordinary
+// evaluation's come from block_map_kernel.
+void build_map(smx_ctx c, Plan &P)
+{
+    if ((int64_t)P.bmap.size() == P.n_map) return;
+    std::vector<int32_t> pos(c->nblk, -1);
+    P.bmap.assign((size_t)P.n_map, -1);
+    for (int32_t g = 0; g < P.ngroups; g++) {
+        const GroupDesc &d = P.gd[g];
+        const int32_t *rows = P.rows.data() + (d.boff_off - g);
+        for (int32_t t = 0; t < d.m; t++) pos[rows[t]] = t;
+        for (int32_t tb = 0; tb < d.m; tb++) {
+            const int32_t j = rows[tb];
+            for (int64_t p = c->col_ptr[j]; p < c->col_ptr[j + 1]; p++) {
+                const int32_t a = pos[c->row_idx[p]];
+                if (a >= 0) P.bmap[(size_t)d.map_off + a + (size_t)d.m * tb] = (int32_t)p;
+            }
+        }
+        for (int32_t t = 0; t < d.m; t++) pos[rows[t]] = -1;
+    }
 }
 
 // Device bytes one group adds to a wave: its share of the arena and of the
@@ -745,12 +765,17 @@ int32_t check_plan(smx_ctx c, const Plan &P)
         if (d.npad % 16 || d.npad < d.n || d.off < 0 || d.off + (int64_t)d.npad * d.npad > P.work_elems)
             return fail(c, SMX_E_INVALID, "internal: group extent");
         if (d.rinfo_off + d.npad > (int64_t)P.rinfo.size() ||
-            d.map_off + (int64_t)d.m * d.m > (int64_t)P.bmap.size() ||
+            d.map_off + (int64_t)d.m * d.m > P.n_map ||
+            d.boff_off - (&d - P.gd.data()) + d.m > (int64_t)P.rows.size() ||
             d.boff_off + d.m + 1 > (int64_t)P.boffs.size() || P.boffs[d.boff_off + d.m] != d.n)
             return fail(c, SMX_E_INVALID, "internal: group tables");
     }
-    for (size_t q = 0; q < P.bmap.size(); q++)
-        if (P.bmap[q] < -1 || P.bmap[q] >= c->nnzb) return fail(c, SMX_E_INVALID, "internal: block map");
+    int32_t map_lo = 0, map_hi = -1;
+    for (const int32_t q : P.bmap) {    // no early exit: the compiler vectorises it
+        map_lo = std::min(map_lo, q);
+        map_hi = std::max(map_hi, q);
+    }
+    if (map_lo < -1 || map_hi >= c->nnzb) return fail(c, SMX_E_INVALID, "internal: block map");
     for (const RowInfo &r : P.rinfo)
         if (r.x < 0 || (r.y & 0xffff) >= (r.y >> 16 ? (r.y >> 16) : 1)) return fail(c, SMX_E_INVALID, "internal: row table");
     for (int64_t p = 0; p < c->nnzb; p++) {
@@ -799,8 +824,9 @@ int32_t ensure_plan(smx_ctx c)
             const int64_t ntd = (d.npad + 63) / 64;     // more than 1536 such tiles, or the estimate is small anyway
             tiles_est += nt * nt + ntd * ntd;
         }
-        const int64_t tables = (int64_t)(vbytes(P.gd) + vbytes(P.chunks) + vbytes(P.rinfo) + vbytes(P.bmap) +
-                                         vbytes(P.boffs) + vbytes(P.scat) + vbytes(P.own_list)) +
+        const int64_t tables = (int64_t)(vbytes(P.gd) + vbytes(P.chunks) + vbytes(P.rinfo) +
+                                         (size_t)P.n_map * sizeof(int32_t) + vbytes(P.rows) + vbytes(c->col_ptr) +
+                                         vbytes(c->row_idx) + vbytes(P.boffs) + vbytes(P.scat) + vbytes(P.own_list)) +
                                (int64_t)sizeof(TileDesc) * 2 * tiles_est + 8 * c->nnzb + 64 * (int64_t)P.ngroups;
         // at most 3/4 of the device in one allocation
         budget = std::min<int64_t>((int64_t)fr - tables - (int64_t)(1ll << 30), (int64_t)(tot / 4 * 3));
@@ -829,7 +855,12 @@ int32_t ensure_plan(smx_ctx c)
     c->contrib_ready = false;
     HIP_TRY(c, upload(c->d_chunks, P.chunks, c->stream));
     HIP_TRY(c, upload(c->d_rinfo, P.rinfo, c->stream));
-    HIP_TRY(c, upload(c->d_bmap, P.bmap, c->stream));
+    HIP_TRY(c, upload(c->d_rows, P.rows, c->stream));
+    HIP_TRY(c, upload(c->d_colptr, c->col_ptr, c->stream));
+    HIP_TRY(c, upload(c->d_rowidx, c->row_idx, c->stream));
+    HIP_TRY(c, c->d_bmap.ensure((size_t)P.n_map));
+    HIP_TRY(c, launch_block_map(c->stream, P.ngroups, P.max_m, c->d_gd.p, c->d_rows.p, c->d_colptr.p, c->d_rowidx.p,
+                                c->d_bmap.p));
     HIP_TRY(c, upload(c->d_boffs, P.boffs, c->stream));
     HIP_TRY(c, upload(c->d_scat, P.scat, c->stream));
     HIP_TRY(c, upload(c->d_own, P.own_list, c->stream));
@@ -1059,6 +1090,9 @@ int32_t smx_destroy(smx_ctx c)
     c->d_chunks.release();
     c->d_rinfo.release();
     c->d_bmap.release();
+    c->d_rows.release();
+    c->d_rowidx.release();
+    c->d_colptr.release();
     c->d_boffs.release();
     c->d_scat.release();
     c->d_scale.release();
@@ -1541,6 +1575,7 @@ int32_t arm_guards(smx_ctx c, bool pool)
     c->guards_armed = false;
     if (!c->debug_checks) return SMX_OK;
     std::string why;
+    build_map(c, c->plan);
     if (!plan_tables_valid(c->plan, c->nnzb, kTile2, why)) return fail(c, SMX_E_INVALID, "debug check: plan table: " + why);
     HIP_TRY(c, c->d_d.ensure((size_t)std::max<int64_t>(c->nvals, 1) + kGuardElems));
     HIP_TRY(c, hipMemsetAsync(c->d_d.p + c->nvals, kGuardByte, kGuardElems * 8, c->stream));
@@ -2125,7 +2160,7 @@ StaticLayout static_layout(smx_ctx c, const Plan &P, int32_t stride)
     L.tiles_d = take(vbytes(P.tiles_d));
     L.chunks = take(vbytes(P.chunks));
     L.rinfo = take(vbytes(P.rinfo));
-    L.bmap = take(vbytes(P.bmap));
+    L.bmap = take((int64_t)sizeof(int32_t) * P.n_map);
     L.boffs = take(vbytes(P.boffs));
     L.scat = take(vbytes(P.scat));
     L.own = take(vbytes(P.own_list));
@@ -2171,6 +2206,7 @@ int32_t static_plan(smx_ctx c, int32_t stride)
         if (static_layout(c, P, stride).end <= cap) break;
         budget = budget * 15 / 16;
     }
+    build_map(c, P);
     if (int32_t st = check_plan(c, P)) return st;
     c->splan_gen++;
     c->splan_stride = stride;
@@ -3050,6 +3086,7 @@ static int32_t ensure_contrib(smx_ctx c)
 {
     if (c->contrib_ready) return SMX_OK;
     Plan &P = c->plan;
+    build_map(c, P);
     std::vector<int64_t> cnt((size_t)c->nnzb + 1, 0);
     for (int32_t g = 0; g < P.ngroups; g++) {
         const GroupDesc &d = P.gd[g];

@@ -129,6 +129,11 @@ __device__ inline double gather_row(const GroupDesc &gd, int r, const RowInfo *_
 
 // ---- launchers (stream-ordered, no synchronisation) -----------------------
 
+// Block maps of all groups: entry (a, b) of group g's is the storage position of
+// block (rows[a], rows[b]), -1 where it is not stored.
+hipError_t launch_block_map(hipStream_t st, int ngroups, int max_m, const GroupDesc *groups, const int32_t *rows,
+                            const int64_t *col_ptr, const int32_t *row_idx, int32_t *bmap);
+
 hipError_t launch_gather(hipStream_t st, int nchunks, const int2 *chunks, const GroupDesc *groups,
                          const RowInfo *rinfo, const int32_t *bmap, const int32_t *boffs,
                          const int64_t *valoff, const double *kvals, double mu, double *x0,
