@@ -63,6 +63,14 @@ struct IterState {
     uint32_t poll_tag;
 };
 
+// Both values are in scalar registers here, so that loads written above are issued
+// together and waited for once, not each where it is first used.
+template <typename A, typename B>
+__device__ inline void loaded(A a, B b)
+{
+    asm volatile("" ::"s"(a), "s"(b));
+}
+
 // The host follows the iteration by this word instead of by a copy and an event
 // per step: back-to-back kernels have no gap, an event record costs about 5 us and
 // a 4-byte copy 4 us and another gap, against kernels of 6-25 us on small batches.

@@ -74,40 +74,36 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ double Bs[2][BM][SK];
 
     if (MODE == 0 || MODE == 5) publish_step(it, k);
+    loaded(groups, it.done);
+    loaded(it.resid_bits, it.scale_bits);
+    loaded(xin, bin);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                            // idle slot of the launch order
-    if (it.kact >= 0 && it.kfix && it.kact >= it.kfix[g]) return;   // group not in this adjoint step
-    if (!polish && (MODE <= 2 || MODE >= 5) && it.done[g]) return;  // finished at an earlier step
-    const int ti = td.y >> 16, tj = td.y & 0xffff;
+    // The group's state and extent in one wait, and the first operand loads before
+    // the stopping test: each of these is a trip to memory that no cache holds
+    // right after the previous launch, and small batches are short of other work.
+    // An evaluation of 100 groups of n ~ 503 9.2 -> 8.8 ms, 12 of ~ 90 327 -> 311 us.
     const GroupDesc gd = groups[g];
+    constexpr bool reads_x0 = MODE < 2 || MODE == 5;
+    const int dn = MODE <= 2 || MODE >= 5 ? it.done[g] : 0;
+    const unsigned long long sb = reads_x0 ? it.scale_bits[g] : 0;
+    const unsigned long long rb = MODE == 1 ? it.resid_bits[(int64_t)g * it.resid_stride + k] : 0;
+    loaded(gd.off, gd.npad);
+    loaded(gd.n, dn);
+    loaded(sb, rb);
+    if (it.kact >= 0 && it.kfix && it.kact >= it.kfix[g]) return;   // group not in this adjoint step
+    if (!polish && (MODE <= 2 || MODE >= 5) && dn) return;  // finished at an earlier step
+    const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
 
     // the prescaling enters the products that read X_0: squares and the update
-    constexpr bool reads_x0 = MODE < 2 || MODE == 5;
     double a = 1.0;
     if (k == 0 && !polish && reads_x0) {
-        const double s = __longlong_as_double((long long)it.scale_bits[g]);
+        const double s = __longlong_as_double((long long)sb);
         a = s > 0.0 ? 1.0 / s : 0.0;
     }
-    if (MODE == 2 && it.done[g]) return;          // tangent only while the group iterates
-    if (MODE == 1 && !polish) {
-        const double rk = __longlong_as_double((long long)it.resid_bits[(int64_t)g * it.resid_stride + k]);
-        const bool finite = rk <= 1.7976931348623157e308;
-        const bool stop = it.kfix ? (k >= it.kfix[g]) : (rk <= tol || k >= max_iter);
-        if (stop || !finite) {
-            if (ti == 0 && tj == 0 && threadIdx.x == 0) {
-                it.done[g] = 1;
-                it.kfinal[g] = k;
-                int fl = 0;
-                if (!it.kfix && !(rk <= tol)) fl |= 1;
-                if (!finite) fl |= 2;
-                it.flags[g] = fl;
-                atomicAdd(it.ndone, 1);
-            }
-            return;
-        }
-    }
+    if (MODE == 2 && dn) return;                  // tangent only while the group iterates
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -191,6 +187,23 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     // LDS, and step kt + 1 (loaded one step earlier) is stored for the next
     gload(0, r0);
     gload(1, r1);
+    if (MODE == 1 && !polish) {
+        const double rk = __longlong_as_double((long long)rb);
+        const bool finite = rk <= 1.7976931348623157e308;
+        const bool stop = it.kfix ? (k >= it.kfix[g]) : (rk <= tol || k >= max_iter);
+        if (stop || !finite) {
+            if (ti == 0 && tj == 0 && threadIdx.x == 0) {
+                it.done[g] = 1;
+                it.kfinal[g] = k;
+                int fl = 0;
+                if (!it.kfix && !(rk <= tol)) fl |= 1;
+                if (!finite) fl |= 2;
+                it.flags[g] = fl;
+                atomicAdd(it.ndone, 1);
+            }
+            return;
+        }
+    }
     sstore(0, r0);
     __syncthreads();
     for (int kt = 0; kt < nk; kt += 2) {

@@ -961,16 +961,18 @@ void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__re
     __shared__ __attribute__((aligned(16))) unsigned short Bs[2][TE][SH];
 
     if (MODE == 0 || MODE == 2) publish_step(it, k);
+    loaded(groups, it.done);
+    loaded(xin, bin);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
-    if (it.done[g]) return;
-    const int ti = td.y >> 16, tj = td.y & 0xffff;
     const GroupDesc gd = groups[g];
+    const int dn = it.done[g];
+    loaded(gd.off, gd.npad);
+    loaded(gd.n, dn);
+    if (dn) return;
+    const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
-    if (MODE == 1 && bulk_stop(it, gd, g, k, ti == 0 && tj == 0 && threadIdx.x == 0, threadIdx.x & 63, switch_tol,
-                               kmax, NW > 1))
-        return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1025,6 +1027,10 @@ void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__re
     };
     gload(0, r0);
     gload(1, r1);
+    // the first loads are in flight meanwhile: a trip to memory each
+    if (MODE == 1 && bulk_stop(it, gd, g, k, ti == 0 && tj == 0 && threadIdx.x == 0, threadIdx.x & 63, switch_tol,
+                               kmax, NW > 1))
+        return;
     sstore(0, r0);
     __syncthreads();
     for (int kt = 0; kt < nk; kt += 2) {
@@ -1121,17 +1127,18 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ float Bs[2][TE][SF];
 
     if (MODE == 0 || MODE == 2) publish_step(it, k);
+    loaded(groups, it.done);
+    loaded(xin, bin);
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
-    if (it.done[g]) return;
-    const int ti = td.y >> 16, tj = td.y & 0xffff;
     const GroupDesc gd = groups[g];
+    const int dn = it.done[g];
+    loaded(gd.off, gd.npad);
+    loaded(gd.n, dn);
+    if (dn) return;
+    const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
-
-    if (MODE == 1 && bulk_stop(it, gd, g, k, ti == 0 && tj == 0 && threadIdx.x == 0, threadIdx.x & 63, switch_tol,
-                               kmax, true))
-        return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1197,6 +1204,10 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     };
     gload(0, r0);
     gload(1, r1);
+    // the first loads are in flight meanwhile: a trip to memory each
+    if (MODE == 1 && bulk_stop(it, gd, g, k, ti == 0 && tj == 0 && threadIdx.x == 0, threadIdx.x & 63, switch_tol,
+                               kmax, true))
+        return;
     sstore(0, r0);
     __syncthreads();
     for (int kt = 0; kt < nk; kt += 2) {
