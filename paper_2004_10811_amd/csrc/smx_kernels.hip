@@ -1,6 +1,8 @@
 // Memory-bound kernels of the submatrix path: gather + shift + Gershgorin
 // bound, scatter of the own columns of D with the energy/trace partials, the
 // fixed-order final reduction, and validation of K's values.
+#include <type_traits>
+
 #include "smx_internal.h"
 
 #include <algorithm>
@@ -325,9 +327,15 @@ void own_gather_kernel(const GroupDesc *__restrict__ groups, const int32_t *__re
     if (r >= gd.npad) return;
     const void *xb = x_base<K>(xs, gd, g);
     const int64_t rp = x_row<K>(r), cs = x_col_stride<K>(gd.npad);
-    for (int c = 0; c < gd.m_own; c++) {
-        const d2v v = x_pair<K>(xb, rp + (int64_t)own_list[gd.own_off + c] * cs);
-        *reinterpret_cast<d2v *>(o + gd.thin_off + r + (int64_t)c * gd.npad) = v;
+    constexpr int NB = 8;                             // columns in flight
+    for (int c0 = 0; c0 < gd.m_own; c0 += NB) {
+        d2v v[NB];
+#pragma unroll
+        for (int u = 0; u < NB; u++)
+            v[u] = x_pair<K>(xb, rp + (int64_t)own_list[gd.own_off + min(c0 + u, gd.m_own - 1)] * cs);
+#pragma unroll
+        for (int u = 0; u < NB; u++)
+            if (c0 + u < gd.m_own) *reinterpret_cast<d2v *>(o + gd.thin_off + r + (int64_t)(c0 + u) * gd.npad) = v[u];
     }
 }
 
@@ -422,28 +430,33 @@ void thin_mul_kernel(const GroupDesc *__restrict__ groups, XSource xs,
 // its column r, whose K-consecutive entries are contiguous: a lane reads 8
 // consecutive rows of one column per word (one 16-B load each; eight values
 // per 16 B for FP32 reads two) and the wave's output rows need no LDS for
-// X.  Wave w of a workgroup owns output rows 32 w .. + 31 of the workgroup's
-// 128 (two 16-row blocks b) and 16 CB output columns per pass (CB 16-column
-// blocks: one when every group owns at most 16 columns, else two).  Per K step of 32: lane l supplies, for
-// product t (0 .. 7), A[i][kk] = X[r0 + 16 b + l % 16, k0 + 8 kk + t] with
+// X.  Wave w of a workgroup owns output rows 16 w .. + 15 of the workgroup's
+// 64 and 16 CB output columns per pass.  Per K step of 32: lane l supplies, for
+// product t (0 .. 7), A[i][kk] = X[r0 + l % 16, k0 + 8 kk + t] with
 // kk = l / 16 and B[kk][j] = Z[k0 + 8 kk + t, 16 cb + l % 16] from LDS, so the
-// eight products of a block cover its 32 K values once.  Z goes to LDS 128
-// rows at a time with the storage's power-of-two word scale on it (every
-// product unchanged, the words are read unscaled).  The next K step's words
-// are loaded while the matrix cores work on the current one.  Rows of Z at
-// or beyond n are zero (X's padding never contributes); output rows at or
-// beyond n come out exactly zero (identity padding times zero rows of Z).
+// eight products of a block cover its 32 K values once.  Z goes to LDS 64
+// rows at a time, double-buffered, with the storage's power-of-two word scale on
+// it (every product unchanged, the words are read unscaled).  The next K step's
+// words and the next stage of Z are loaded while the matrix cores work on the
+// current one.  Rows of Z at or beyond n are zero (X's padding never contributes);
+// output rows at or beyond n come out exactly zero (identity padding times zero
+// rows of Z).
+//
+// Bound by the FP64 matrix cores (23 own columns fill 72% of two column blocks) and
+// the latency of the words, at four waves per SIMD.  256 groups of n ~ 855: 297 us a
+// product with two row blocks per wave, 128-row stages of Z loaded between barriers
+// and the words summed in FP64, at three waves per SIMD (two blocks spill at four); 279
+// now, 40 TFLOP/s on real columns.  100 groups: 154 / 137 us.
 template <int K>
 __device__ constexpr int tm_loads() { return K == X_F32 ? 2 : x_nw<K>(); }
-// 16-row blocks per wave: two keep the kernel at three waves per SIMD (four
-// took two waves per SIMD and ran 0.9% slower per D on water1024; one, at four
-// waves per SIMD, 5% slower per launch)
-constexpr int kThinRB = 2;
-constexpr int kThinRows = 64 * kThinRB;                // output rows per workgroup
+constexpr int kThinWide = 1024;    // workgroups from which one takes both column blocks (launch_thin_mul)
 
 // Element t (0 .. 7) of the 8 consecutive rows a lane loaded, as the unscaled
-// FP64 sum of its words (exact).
-template <int K>
+// sum of its words (exact).  The words of an iterate come from a product's FP32
+// output: a multiple of its unit in the last place that its rounding cannot carry
+// beyond the next power of two, so that FP32 holds the sum (F32).  The words of
+// X_0 come from FP64 and are summed there.
+template <int K, bool F32>
 __device__ inline double tm_value(const u4 *raw, int t)
 {
     if constexpr (K == X_F32) {
@@ -451,15 +464,19 @@ __device__ inline double tm_value(const u4 *raw, int t)
         return (double)__builtin_bit_cast(float, u);
     } else {
         constexpr int NW = x_nw<K>();
-        double v = 0.0;
+        typename std::conditional<F32, float, double>::type v = 0;
 #pragma unroll
         for (int w = NW - 1; w >= 0; w--) {
             const unsigned int u = raw[w][t >> 1];
             const unsigned short h = (t & 1) ? (unsigned short)(u >> 16) : (unsigned short)(u & 0xffffu);
-            const double a = K == X_F16x2 ? f16w(h) : bf16w(h);
-            v = (w == NW - 1) ? a : v + a;
+            const float a = K == X_F16x2 ? (float)__builtin_bit_cast(_Float16, h)
+                                         : __builtin_bit_cast(float, ((unsigned int)h) << 16);
+            if (w == NW - 1)
+                v = a;
+            else
+                v += a;
         }
-        return v;
+        return (double)v;
     }
 }
 
@@ -468,32 +485,35 @@ __device__ inline double tm_value(const u4 *raw, int t)
 // L takes item (L % 8) * (grid / 8) + L / 8, so that each XCD works through
 // one contiguous range of items and the row blocks of a group share the XCD's
 // L2 for their reads of the group's Z.
+// With gc > 1 column blocks in the grid as well, a row block's items take every
+// gc-th block of 16 CB columns.
+// three BF16 words on two column blocks spill at four waves per SIMD
 template <int MODE, int K, int CB>
-__global__ __launch_bounds__(256, 3)
+__global__ __launch_bounds__(256, K == X_BF16x3 && CB == 2 ? 3 : 4)
 void thin_mfma_kernel(const GroupDesc *__restrict__ groups, XSource xs, const double *__restrict__ z,
-                      const double *__restrict__ o, double *__restrict__ y, int g0, int gx, int nwork)
+                      const double *__restrict__ o, double *__restrict__ y, int g0, int gx, int gc, int nwork)
 {
-    constexpr int KC = 128;                           // rows of Z per LDS stage
-    constexpr int ZS = 33;                            // LDS row stride of the staged Z (doubles)
+    constexpr int KC = 64;                            // rows of Z per LDS stage: two K steps
+    constexpr int ZS = 16 * CB + 2;                   // LDS row stride of the staged Z (doubles): reads free of conflicts
+    constexpr int ZU = KC * 16 * CB / 256;            // values of a stage per lane
     constexpr int NL = tm_loads<K>();
-    constexpr int RB = kThinRB;
-    __shared__ double zs[KC * ZS];
+    __shared__ double zs[2][KC * ZS];
     const int item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
     if (item >= nwork) return;                        // padding of the grid to a multiple of 8
-    const int g = g0 + item / gx;
+    const int g = g0 + item / (gx * gc);
     const GroupDesc gd = groups[g];
     const int npad = gd.npad;
-    const int row0 = (item % gx) * (64 * RB);
+    const int row0 = (item / gc % gx) * 64;
     if (row0 >= npad) return;                         // whole workgroup beyond this group
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rw = row0 + 16 * RB * wave;             // first output row of this wave
+    const int rw = row0 + 16 * wave;                  // first output row of this wave
     const bool live = rw < npad;                      // wave-uniform
     const int li = lane & 15, q = lane >> 4;
     const void *xg = x_base<K>(xs, gd, g);
     // word layout: column c starts at c * npad * NW halves, K step s at s * 32 * NW, word w at + 32 w
-    auto src = [&](int b, int k0, int w) -> const u4 * {
-        const int c = min(rw + 16 * b + li, npad - 1);    // rows beyond n_pad are never stored
+    auto src = [&](int k0, int w) -> const u4 * {
+        const int c = min(rw + li, npad - 1);    // rows beyond n_pad are never stored
         if constexpr (K == X_F32)
             return reinterpret_cast<const u4 *>(reinterpret_cast<const float *>(xg) + (int64_t)c * npad + k0 + 8 * q +
                                                 4 * w);
@@ -503,53 +523,34 @@ void thin_mfma_kernel(const GroupDesc *__restrict__ groups, XSource xs, const do
     };
     constexpr double zscale = x_word_scale<K>();
     const int nk = npad / 32;
-    for (int c0 = 0; c0 < gd.m_own; c0 += 16 * CB) {
-        f64x4 acc[RB][CB];
+    for (int c0 = 16 * CB * (item % gc); c0 < gd.m_own; c0 += 16 * CB * gc) {
+        f64x4 acc[CB];
 #pragma unroll
-        for (int b = 0; b < RB; b++)
-#pragma unroll
-            for (int cb = 0; cb < CB; cb++) acc[b][cb] = f64x4{0.0, 0.0, 0.0, 0.0};
-        u4 ra[RB][NL], rb[RB][NL];
+        for (int cb = 0; cb < CB; cb++) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
+        u4 ra[NL], rb[NL];
         if (live) {
 #pragma unroll
-            for (int b = 0; b < RB; b++)
-#pragma unroll
-                for (int w = 0; w < NL; w++) ra[b][w] = *src(b, 0, w);
+            for (int w = 0; w < NL; w++) ra[w] = *src(0, w);
         }
+        // Stages of Z.  Consecutive lanes take consecutive rows of one column
+        // (coalesced reads); a lane keeps row kk and takes columns tid / KC + 4 m.
+        // Every lane loads: rows and columns outside Z read its last row or column,
+        // and the value is replaced by zero.
+        const int kk = tid & (KC - 1), zc = tid / KC;
+        double zv[ZU];
+        auto zload = [&](int s) {
+            const double *zr = z + gd.thin_off + min(s * KC + kk, gd.n - 1);
+#pragma unroll
+            for (int m = 0; m < ZU; m++) zv[m] = zr[(int64_t)min(c0 + zc + 4 * m, gd.m_own - 1) * npad];
+        };
+        auto zstore = [&](int s) {
+            const bool in = s * KC + kk < gd.n;
+            double *zd = zs[s & 1] + kk * ZS + zc;
+#pragma unroll
+            for (int m = 0; m < ZU; m++) zd[4 * m] = in && c0 + zc + 4 * m < gd.m_own ? zv[m] * zscale : 0.0;
+        };
         // one K step with the words in rc, the next step's loaded into rn
-        auto kstep = [&](int kt, u4 (&rc)[RB][NL], u4 (&rn)[RB][NL]) {
-            if (kt % (KC / 32) == 0) {
-                const int ks = kt * 32;
-                __syncthreads();                      // every wave is done with the previous stage
-                // consecutive lanes take consecutive rows of one column of Z
-                // (coalesced reads; the LDS writes, 33 doubles apart, are at
-                // most two-way bank conflicted).  A lane keeps one row kk of Z
-                // and takes columns tid / KC + 2 m; its loads go out ZB at a time,
-                // all in flight before their LDS writes (every lane loads: rows
-                // and columns outside Z read its last row or column, and the
-                // value is replaced by zero afterwards)
-                static_assert(256 == 2 * KC, "a lane's row kk = tid % KC, its first column tid / KC in {0, 1}");
-                constexpr int ZU = KC * 32 / 256, ZB = 8;
-                const int kk = tid & (KC - 1), kr = ks + kk;
-                const double *zr = z + gd.thin_off + min(kr, gd.n - 1);
-#pragma unroll
-                for (int m0 = 0; m0 < ZU; m0 += ZB) {
-                    double zv[ZB];
-#pragma unroll
-                    for (int m = 0; m < ZB; m++) {
-                        const int col = c0 + tid / KC + 2 * (m0 + m);
-                        zv[m] = zr[(int64_t)min(col, gd.m_own - 1) * npad];
-                    }
-#pragma unroll
-                    for (int m = 0; m < ZB; m++) {
-                        const int col = c0 + tid / KC + 2 * (m0 + m);
-                        if (!(kr < gd.n && col < gd.m_own)) zv[m] = 0.0;
-                    }
-#pragma unroll
-                    for (int m = 0; m < ZB; m++) zs[kk * ZS + tid / KC + 2 * (m0 + m)] = zv[m] * zscale;
-                }
-                __syncthreads();
-            }
+        auto kstep = [&](auto f32, int kt, u4 (&rc)[NL], u4 (&rn)[NL]) {
             if (!live) return;
             // the next step's words (unconditionally: the last step reloads its
             // own, so that no load sits under a branch, where the compiler would
@@ -557,47 +558,54 @@ void thin_mfma_kernel(const GroupDesc *__restrict__ groups, XSource xs, const do
             {
                 const int kn = min(kt + 1, nk - 1) * 32;
 #pragma unroll
-                for (int b = 0; b < RB; b++)
-#pragma unroll
-                    for (int w = 0; w < NL; w++) rn[b][w] = *src(b, kn, w);
+                for (int w = 0; w < NL; w++) rn[w] = *src(kn, w);
             }
-            const double *zr = zs + ((kt % (KC / 32)) * 32 + 8 * q) * ZS + li;
+            const double *zr = zs[(kt >> 1) & 1] + ((kt & 1) * 32 + 8 * q) * ZS + li;
 #pragma unroll
             for (int t = 0; t < 8; t++) {
                 double bz[CB];
 #pragma unroll
                 for (int cb = 0; cb < CB; cb++) bz[cb] = zr[t * ZS + 16 * cb];
+                const double a = tm_value<K, decltype(f32)::value>(rc, t);
 #pragma unroll
-                for (int b = 0; b < RB; b++) {
-                    const double a = tm_value<K>(rc[b], t);
-#pragma unroll
-                    for (int cb = 0; cb < CB; cb++)
-                        acc[b][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bz[cb], acc[b][cb], 0, 0, 0);
-                }
+                for (int cb = 0; cb < CB; cb++)
+                    acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bz[cb], acc[cb], 0, 0, 0);
             }
         };
-        for (int kt = 0; kt < nk; kt += 2) {
-            kstep(kt, ra, rb);
-            if (kt + 1 < nk) kstep(kt + 1, rb, ra);
-        }
+        // stage s + 1's loads are in flight during stage s's products, then go to
+        // the other buffer
+        zload(0);
+        zstore(0);
+        __syncthreads();
+        auto stages = [&](auto f32) {
+            for (int kt = 0; kt < nk; kt += 2) {
+                zload((kt >> 1) + 1);
+                kstep(f32, kt, ra, rb);
+                if (kt + 1 < nk) kstep(f32, kt + 1, rb, ra);
+                zstore((kt >> 1) + 1);
+                __syncthreads();
+            }
+        };
+        if (NL > 1 && K != X_F32 && xs.kfinal[g] == 0)
+            stages(std::false_type{});
+        else
+            stages(std::true_type{});
         if (live) {
-            // lane l, register v of block (b, cb): row 16 b + l / 16 + 4 v, column 16 cb + l % 16
+            // lane l, register v of block cb: row l / 16 + 4 v, column 16 cb + l % 16
 #pragma unroll
-            for (int b = 0; b < RB; b++)
+            for (int cb = 0; cb < CB; cb++) {
+                const int col = c0 + 16 * cb + li;
+                if (col >= gd.m_own) continue;
 #pragma unroll
-                for (int cb = 0; cb < CB; cb++) {
-                    const int col = c0 + 16 * cb + li;
-                    if (col >= gd.m_own) continue;
-#pragma unroll
-                    for (int v = 0; v < 4; v++) {
-                        const int r = rw + 16 * b + q + 4 * v;
-                        if (r >= npad) continue;
-                        const int64_t idx = gd.thin_off + r + (int64_t)col * npad;
-                        double val = acc[b][cb][v];
-                        if (MODE == 1) val = 1.5 * o[idx] - 0.5 * val;
-                        y[idx] = val;
-                    }
+                for (int v = 0; v < 4; v++) {
+                    const int r = rw + q + 4 * v;
+                    if (r >= npad) continue;
+                    const int64_t idx = gd.thin_off + r + (int64_t)col * npad;
+                    double val = acc[cb][v];
+                    if (MODE == 1) val = 1.5 * o[idx] - 0.5 * val;
+                    y[idx] = val;
                 }
+            }
         }
     }
 }
@@ -966,26 +974,36 @@ hipError_t launch_thin_mul(hipStream_t st, int mode, int g0, int ngroups, int ma
     if (ngroups <= 0 || max_own <= 0) return hipSuccess;
     const dim3 grid((unsigned)((max_npad + 511) / 512), (unsigned)ngroups);
     const int mw = max_own <= 8 ? 8 : (max_own <= 16 ? 16 : (max_own <= 24 ? 24 : 32));
-    // the bulk's words (or FP32 values) go through the matrix cores; an FP64
-    // slab through the vector units
-    const int gx = (max_npad + kThinRows - 1) / kThinRows;
-    const int nwork = gx * ngroups;
+    // The bulk's words (or FP32 values) go through the matrix cores; an FP64
+    // slab through the vector units.
+    //
+    // A workgroup takes 64 rows and two column blocks, which read the words once, when
+    // there are four workgroups for every CU.  Fewer leave CUs idle and each wave a long
+    // chain of products: then one column block per workgroup (the same sums in the same
+    // order).  One product, two blocks / one: 80 workgroups (16 groups of n ~ 270, 23
+    // own columns) 18 / 9.1 us, 240 (40 of ~ 374) 22.6 / 19.4, 1400 (100 of ~ 855)
+    // 137 / 137, 3584 (256 of ~ 855) 279 / 318.
+    const int gx = (max_npad + 63) / 64;
+    const bool wide = (int64_t)gx * ngroups >= kThinWide;
+    const int gc = wide ? 1 : (max_own + 15) / 16;
+    const int64_t nwork = (int64_t)gx * gc * ngroups;
     const dim3 grid_m((unsigned)((nwork + 7) / 8 * 8));
-    // one 16-column block per pass when every group owns at most 16 columns
+#define SMX_TMM_CB(KK, CBB)                                                                                     \
+    do {                                                                                                        \
+        if (mode == 0)                                                                                          \
+            hipLaunchKernelGGL((thin_mfma_kernel<0, KK, CBB>), grid_m, dim3(256), 0, st, groups, xs, z, o, y,   \
+                               g0, gx, gc, (int)nwork);                                                         \
+        else                                                                                                    \
+            hipLaunchKernelGGL((thin_mfma_kernel<1, KK, CBB>), grid_m, dim3(256), 0, st, groups, xs, z, o, y,   \
+                               g0, gx, gc, (int)nwork);                                                         \
+        return hipGetLastError();                                                                               \
+    } while (0)
 #define SMX_TMM(KK)                                                                                             \
     do {                                                                                                        \
-        if (max_own <= 16) {                                                                                    \
-            if (mode == 0)                                                                                      \
-                hipLaunchKernelGGL((thin_mfma_kernel<0, KK, 1>), grid_m, dim3(256), 0, st, groups, xs, z, o, y, g0, gx, nwork); \
-            else                                                                                                \
-                hipLaunchKernelGGL((thin_mfma_kernel<1, KK, 1>), grid_m, dim3(256), 0, st, groups, xs, z, o, y, g0, gx, nwork); \
-        } else {                                                                                                \
-            if (mode == 0)                                                                                      \
-                hipLaunchKernelGGL((thin_mfma_kernel<0, KK, 2>), grid_m, dim3(256), 0, st, groups, xs, z, o, y, g0, gx, nwork); \
-            else                                                                                                \
-                hipLaunchKernelGGL((thin_mfma_kernel<1, KK, 2>), grid_m, dim3(256), 0, st, groups, xs, z, o, y, g0, gx, nwork); \
-        }                                                                                                       \
-        return hipGetLastError();                                                                               \
+        if (wide && max_own > 16)                                                                               \
+            SMX_TMM_CB(KK, 2);                                                                                  \
+        else                                                                                                    \
+            SMX_TMM_CB(KK, 1);                                                                                  \
     } while (0)
     switch (x_kind(xs)) {
     case X_F64: return thin_mul_k<X_F64>(st, mode, mw, grid, g0, groups, xs, z, o, y);
@@ -996,6 +1014,7 @@ hipError_t launch_thin_mul(hipStream_t st, int mode, int g0, int ngroups, int ma
     default: return hipErrorInvalidValue;
     }
 #undef SMX_TMM
+#undef SMX_TMM_CB
 }
 
 hipError_t launch_thin_combine(hipStream_t st, int g0, int ngroups, int max_npad, int max_own,
