@@ -240,7 +240,8 @@ int32_t smx_set_tile_order(smx_ctx ctx, int32_t order);
  * 128 x 128 bucket persistently: as many workgroups as the CUs hold, taking
  * tiles from one work list per XCD through atomic counters (each starts with
  * its own XCD's list, read from the hardware, then takes what the others left).
- * Results are bitwise the same.
+ * With 0, a small batch (no size bucket, at most 1536 lower tiles of 64 x 64)
+ * takes 32 x 32 tiles, loaded two K steps ahead.  Results are bitwise the same.
  */
 int32_t smx_set_kernel_variant(smx_ctx ctx, int32_t variant);
 
@@ -265,9 +266,10 @@ int32_t smx_set_debug_checks(smx_ctx ctx, int32_t on);
  * dimension n_pad is at least big_min_npad run on 256 x 256 output tiles
  * (one 512-lane workgroup per CU, operands double-buffered in LDS), the
  * others on 128 x 128 tiles; each bucket is one launch per product.
- * big_min_npad = 0 puts every group on 128 x 128 tiles.  Results are bitwise
- * the same for every choice.  Takes effect at the next plan build; other
- * precision modes always use 128 x 128 tiles.
+ * big_min_npad = 0 puts every group on 128 x 128 tiles (32 x 32 for a small
+ * batch, see smx_set_kernel_variant).  Results are bitwise the same for every
+ * choice.  Takes effect at the next plan build; 3-word BF16 is not bucketed, and
+ * the FP64 and FP32 products take 64 x 64 tiles, or 32 x 32 for a small batch.
  */
 int32_t smx_set_tile_shape(smx_ctx ctx, int32_t big_min_npad);
 
@@ -333,10 +335,11 @@ int32_t smx_workspace_size(smx_ctx ctx, size_t *bytes);
 int32_t smx_set_workspace(smx_ctx ctx, void *dptr, size_t bytes);
 
 /*
- * Host polling.  on = 1 (default): smx_evaluate reads the finished-group
- * counter one step (or one step graph) behind the device and stops enqueueing
- * steps once every group is done, which synchronises the host with the stream
- * during the call.  on = 0: smx_evaluate enqueues every step up to the cap
+ * Host polling.  on = 1 (default): smx_evaluate follows the finished-group
+ * counter one step (or one step graph) behind the device, through a word that the
+ * products write to pinned host memory (a copy per replay with step graphs), and
+ * stops enqueueing steps once every group is done, which synchronises the host
+ * with the stream during the call.  on = 0: smx_evaluate enqueues every step up to the cap
  * (max_iter, or max_iter - n_polish bulk steps) without waiting on the
  * device; finished groups skip on the device, so results are bitwise the
  * same, at the cost of the launches past convergence.  With smx_set_graph the
@@ -347,7 +350,7 @@ int32_t smx_set_host_poll(smx_ctx ctx, int32_t on);
 /*
  * Evaluate D, N and E for the current K, groups and mu.  The work is
  * enqueued on the context's stream; the call returns after enqueueing it
- * (with host polling on, the host only polls a small counter to stop the
+ * (with host polling on, the host only reads a small counter to stop the
  * iteration when every group has converged).  D stays resident on the device.
  */
 int32_t smx_evaluate(smx_ctx ctx);
@@ -593,11 +596,11 @@ int32_t smx_get_sizes(smx_ctx ctx, int32_t *ngroups, int64_t *nvalues);
 
 /*
  * Per-launch profile of the matrix-core product kernels of the last
- * evaluation, in launch order: device time in ms measured with HIP events on
- * the context's stream, the algorithmic flops of the launch (2 n_g^3 for
+ * evaluation, in launch order: device time in ms between the HIP events before and
+ * after the launch on the context's stream (one event between two launches), the algorithmic flops of the launch (2 n_g^3 for
  * every group the launch works on, i.e. one dense n_g x n_g product), and
  * its kind: 0/1 FP64 square/update, 2/3 reduced-precision square/update on
- * 128 x 128 tiles, 4/5 FP64 polish square/update, 6 mu tangent, 7/8
+ * 128 x 128 tiles (32 x 32 for a small batch; FP32 64 x 64 or 32 x 32), 4/5 FP64 polish square/update, 6 mu tangent, 7/8
  * reduced-precision square/update on 256 x 256 tiles, 9/10 reduced-precision
  * Pade combine on 128 x 128 / 256 x 256 tiles, 11 FP64 Pade combine (the Pade
  * square shares the square's kind), 12 Householder reduction of the

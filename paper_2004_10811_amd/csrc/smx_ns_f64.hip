@@ -74,24 +74,30 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ double Bs[2][BM][SK];
 
     if (MODE == 0 || MODE == 5) publish_step(it, k);
-    loaded(groups, it.done);
-    loaded(it.resid_bits, it.scale_bits);
-    loaded(xin, bin);
+    if (WB == 1) {
+        loaded(groups, it.done);
+        loaded(it.resid_bits, it.scale_bits);
+        loaded(xin, bin);
+    }
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                            // idle slot of the launch order
     // The group's state and extent in one wait, and the first operand loads before
     // the stopping test: each of these is a trip to memory that no cache holds
     // right after the previous launch, and small batches are short of other work.
-    // An evaluation of 100 groups of n ~ 503 9.2 -> 8.8 ms, 12 of ~ 90 327 -> 311 us.
+    // An evaluation of 12 groups of n ~ 90 324 -> 317 us, 100 of ~ 503 unchanged (8.95 ms);
+    // the larger tiles leave the order of the loads to the compiler (1024 groups of ~ 847
+    // 364.3 ms with it forced, 362.5 without).
     const GroupDesc gd = groups[g];
     constexpr bool reads_x0 = MODE < 2 || MODE == 5;
     const int dn = MODE <= 2 || MODE >= 5 ? it.done[g] : 0;
     const unsigned long long sb = reads_x0 ? it.scale_bits[g] : 0;
     const unsigned long long rb = MODE == 1 ? it.resid_bits[(int64_t)g * it.resid_stride + k] : 0;
-    loaded(gd.off, gd.npad);
-    loaded(gd.n, dn);
-    loaded(sb, rb);
+    if (WB == 1) {
+        loaded(gd.off, gd.npad);
+        loaded(gd.n, dn);
+        loaded(sb, rb);
+    }
     if (it.kact >= 0 && it.kfix && it.kact >= it.kfix[g]) return;   // group not in this adjoint step
     if (!polish && (MODE <= 2 || MODE >= 5) && dn) return;  // finished at an earlier step
     const int ti = td.y >> 16, tj = td.y & 0xffff;

@@ -1127,15 +1127,19 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     __shared__ float Bs[2][TE][SF];
 
     if (MODE == 0 || MODE == 2) publish_step(it, k);
-    loaded(groups, it.done);
-    loaded(xin, bin);
+    if (WB == 1) {
+        loaded(groups, it.done);
+        loaded(xin, bin);
+    }
     const TileDesc td = tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
     const GroupDesc gd = groups[g];
     const int dn = it.done[g];
-    loaded(gd.off, gd.npad);
-    loaded(gd.n, dn);
+    if (WB == 1) {
+        loaded(gd.off, gd.npad);
+        loaded(gd.n, dn);
+    }
     if (dn) return;
     const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
