@@ -658,6 +658,7 @@ void bisect_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev)
 // z_r = 1, z_i = -L+_i z_{i+1} (i < r), z_{i+1} = -U-_i z_i (i >= r).
 // S[i * n_pad + l] holds component i of eigenvector l (U-_i is parked there
 // at row i + 1 until z overwrites it); lbuf holds D- and then L+.
+template <int NR>
 __global__ __launch_bounds__(256)
 void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, double *__restrict__ sbase,
                  double *__restrict__ lbase)
@@ -666,6 +667,13 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
     const GroupDesc gd = groups[g];
     const int l = blockIdx.x * 256 + threadIdx.x;
     const int ld = gd.npad;
+    __shared__ double d[NR], e[NR];
+    if ((int)blockIdx.x * 256 >= ld) return;          // whole workgroup beyond this group
+    for (int i = threadIdx.x; i < gd.n; i += 256) {
+        d[i] = ev.d[gd.rinfo_off + i];
+        e[i] = ev.e[gd.rinfo_off + i];
+    }
+    __syncthreads();
     if (l >= ld) return;
     double *S = sbase + gd.off;
     double *Lb = lbase + gd.off;
@@ -673,7 +681,6 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
         for (int i = 0; i < ld; i++) S[(int64_t)i * ld + l] = (i == l) ? 1.0 : 0.0;
         return;
     }
-    const double *d = ev.d + gd.rinfo_off, *e = ev.e + gd.rinfo_off;
     const int s = ev.bs[gd.rinfo_off + l], t = ev.be[gd.rinfo_off + l];
     const double lam = ev.lam[gd.rinfo_off + l];
     double emax = 0.0;
@@ -697,8 +704,11 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
     }
     // stationary (top-down): gamma at every row, L+ replaces D- in lbuf.  Here
     // and below eight rows are loaded at a time, all in flight before their use
-    // (rows beyond the block read its last one and are not used): 8.7 ms on
-    // water256 against 10.3 ms one at a time.
+    // (rows beyond the block read its last one and are not used; a break out of the
+    // unrolled rows kept the compiler from that).  d and e are in LDS: a load from
+    // memory waits for the stores issued before it.  256 groups of n ~ 855: 10.3 ms one
+    // row at a time, 8.7 with eight, 7.9 with d and e in LDS and no breaks; 32 of ~ 390
+    // 0.75, 0.66, 0.43 ms.
     double dp = guard(d[s] - lam);
     int r = s;
     double gbest = 1.7976931348623157e308;
@@ -709,9 +719,8 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
 #pragma unroll
         for (int u = 0; u < 8; u++) {
             const int i = i0 + u;
-            if (i >= t) break;
-            const double gam = dp + dmi[u] - (d[i] - lam);
-            if (fabs(gam) < gbest) {
+            const double gam = dp + dmi[u] - (d[min(i, t - 1)] - lam);
+            if (i < t && fabs(gam) < gbest) {
                 gbest = fabs(gam);
                 r = i;
             }
@@ -731,10 +740,11 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
         for (int u = 0; u < 8; u++) lp[u] = Lb[(int64_t)max(i0 - u, s) * ld + l];
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            if (i0 - u < s) break;
-            z = -lp[u] * z;
-            S[(int64_t)(i0 - u) * ld + l] = z;
-            nrm += z * z;
+            if (i0 - u >= s) {
+                z = -lp[u] * z;
+                S[(int64_t)(i0 - u) * ld + l] = z;
+                nrm += z * z;
+            }
         }
     }
     z = 1.0;
@@ -744,10 +754,11 @@ void tvec_kernel(const GroupDesc *__restrict__ groups, int g0, EigVecs ev, doubl
         for (int u = 0; u < 8; u++) un[u] = S[(int64_t)min(i0 + u + 1, t - 1) * ld + l];
 #pragma unroll
         for (int u = 0; u < 8; u++) {
-            if (i0 + u + 1 >= t) break;
-            z = -un[u] * z;
-            S[(int64_t)(i0 + u + 1) * ld + l] = z;
-            nrm += z * z;
+            if (i0 + u + 1 < t) {
+                z = -un[u] * z;
+                S[(int64_t)(i0 + u + 1) * ld + l] = z;
+                nrm += z * z;
+            }
         }
     }
     const double inv = 1.0 / sqrt(nrm);
@@ -1227,7 +1238,10 @@ hipError_t launch_eig_values_vectors(hipStream_t st, int g0, int ngroups, int ma
     hipLaunchKernelGGL(bisect_kernel, grid, dim3(256), 0, st, groups, g0, ev);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(tvec_kernel, grid, dim3(256), 0, st, groups, g0, ev, s, scratch);
+    if (max_npad <= kHalfMaxN)
+        hipLaunchKernelGGL(tvec_kernel<kHalfMaxN>, grid, dim3(256), 0, st, groups, g0, ev, s, scratch);
+    else
+        hipLaunchKernelGGL(tvec_kernel<kEigMaxN>, grid, dim3(256), 0, st, groups, g0, ev, s, scratch);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cluster_kernel, grid, dim3(256), 0, st, groups, g0, ev, s, scratch);
