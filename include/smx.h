@@ -33,7 +33,8 @@
  *     device memory and frees it in smx_destroy().
  *   - Device work is enqueued on the stream given to smx_set_stream() (the
  *     null stream by default), e.g. the current PyTorch stream.  Functions
- *     that return host scalars synchronise that stream.
+ *     that return host scalars synchronise that stream, and wait for the last
+ *     evaluation also where another stream was set after it.
  *
  * Block-sparse layout (BSC, "block compressed sparse column"):
  *   nblk block rows/columns with sizes blk_size[0..nblk-1] (1..1024);

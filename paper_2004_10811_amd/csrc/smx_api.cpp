@@ -282,6 +282,7 @@ struct smx_context {
 
     // results of the last evaluation
     bool evaluated = false;
+    bool end_recorded = false;              // ev_t3 marks the end of the last evaluation
     int32_t steps_launched = 0;
     int32_t last_precision = SMX_FP64;
     int32_t last_iteration = SMX_ITER_NS2;
@@ -916,7 +917,31 @@ int32_t set_device(smx_ctx c)
 int32_t need_sync_results(smx_ctx c)
 {
     if (!c->evaluated) return fail(c, SMX_E_STATE, "no evaluation has been run");
+    if (c->end_recorded) HIP_TRY(c, hipEventSynchronize(c->ev_t3));    // on whatever stream it ran
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return SMX_OK;
+}
+
+// Before the host reads what the device wrote to pinned memory (N, E, flag
+// counts): no copy orders that read behind the evaluation.  The event covers an
+// evaluation whose stream is not the context's any more; the null stream covers one
+// that no event marks, a captured one replayed there or on another blocking stream.
+int32_t need_published(smx_ctx c)
+{
+    if (int32_t st = need_sync_results(c)) return st;
+    if (c->stream) HIP_TRY(c, hipStreamSynchronize(nullptr));
+    return SMX_OK;
+}
+
+// The event at the end of an evaluation; inside a capture it marks nothing that
+// the host could wait for.
+int32_t record_end(smx_ctx c)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(c->stream, &cs);
+    if (e != hipSuccess) (void)hipGetLastError();
+    c->end_recorded = e == hipSuccess && cs == hipStreamCaptureStatusNone;
+    HIP_TRY(c, hipEventRecord(c->ev_t3, c->stream));
     return SMX_OK;
 }
 
@@ -1993,7 +2018,9 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
     if (tangent) HIP_TRY(c, launch_reduce(st, ng, c->d_dnp.p, c->d_dnp.p, c->d_dn.p));
     c->have_tangent = tangent;
     c->last_sfix = c->use_sfix;
-    if (events) HIP_TRY(c, hipEventRecord(c->ev_t3, st));
+    c->end_recorded = false;
+    if (events)
+        if (int32_t e = record_end(c)) return e;
     c->steps_launched = launched;
     c->last_precision = c->precision;
     c->last_iteration = c->iteration;
@@ -2107,7 +2134,7 @@ int32_t eig_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView &
     }
     HIP_TRY(c, launch_reduce(st, c->nnzb, V.pe, V.pn, V.ne));
     HIP_TRY(c, launch_publish(st, ng, V.flags, V.ne, &c->h->res));
-    HIP_TRY(c, hipEventRecord(c->ev_t3, st));
+    if (int32_t e = record_end(c)) return e;
     c->have_tangent = false;
     c->last_sfix = false;
     c->steps_launched = 0;
@@ -2328,7 +2355,7 @@ int32_t smx_evaluate_static(smx_ctx c)
 int32_t smx_wait(smx_ctx c)
 {
     if (!c) return SMX_E_INVALID;
-    if (int32_t st = need_sync_results(c)) return st;
+    if (int32_t st = need_published(c)) return st;
     if (int32_t st = check_guards(c)) return st;
     const int nc = c->h->res.nflag[0], nf = c->h->res.nflag[1];
     if (nf) return fail(c, SMX_E_NONFINITE, std::to_string(nf) + " group(s) produced non-finite iterates");
@@ -2384,7 +2411,7 @@ int32_t smx_get_d_expanded(smx_ctx c, const int64_t *index, int64_t n_out, doubl
 
 static int32_t read_ne(smx_ctx c, double *ne)
 {
-    if (int32_t st = need_sync_results(c)) return st;
+    if (int32_t st = need_published(c)) return st;
     ne[0] = c->h->res.ne[0];
     ne[1] = c->h->res.ne[1];
     return SMX_OK;
@@ -3034,7 +3061,7 @@ int32_t smx_find_mu_eig(smx_ctx c, double n_target, double tol, int32_t max_step
         HIP_TRY(c, hipEventRecord(c->ev_wave[3], st));
         HIP_TRY(c, launch_reduce(st, c->nnzb, V.pe, V.pn, V.ne));
         HIP_TRY(c, launch_publish(st, ng, V.flags, V.ne, &c->h->res));
-        HIP_TRY(c, hipEventRecord(c->ev_t3, st));
+        if (int32_t e2 = record_end(c)) return e2;
         c->launch_step.clear();
         c->launch_ev.clear();
         c->n_ev = 0;
