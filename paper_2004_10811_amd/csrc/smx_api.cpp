@@ -1949,7 +1949,10 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const int32_t nchunk = kmax / S + 1;
         chained = false;
         it.poll = poll && !use_graphs ? &c->h->poll : nullptr;
+        // the tags are this loop's from here on, so that words left by one that ends in an
+        // error are never taken for a later one's
         it.poll_tag = c->poll_tag + 1;
+        if (it.poll) c->poll_tag += (uint32_t)kmax + 1;
         for (int32_t ch = 0; ch < nchunk; ch++) {
             const int32_t k0 = ch * S, k1 = std::min(k0 + S - 1, kmax);
             if (use_graphs) {
@@ -1987,7 +1990,6 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                 }
             }
         }
-        if (it.poll) c->poll_tag += (uint32_t)kmax + 1;
         if (mixed) {
             // FP64 polish on the own columns: X_{k+p} E from the bulk result X,
             // read from its words (converted exactly on the fly)
