@@ -108,10 +108,15 @@ struct Plan {
     std::vector<ScatterDesc> scat;
     std::vector<int32_t> own_list;    // own columns of every group (submatrix column indices)
     std::vector<double> wtiles;       // live 64 x 64 wave tiles of one product, per group
-    // lower tiles of the FP64 and FP32 products and their edge; per wave like tile_beg
+    // lower tiles of the FP64 products and their edge; per wave like tile_beg
     int32_t edge_d = kTile;
     std::vector<TileDesc> tiles_d;
     std::vector<int64_t> tiles_d_beg;
+    // the FP32 products' edge, and their own list where it is another (else empty)
+    int32_t edge_f = kTile;
+    std::vector<TileDesc> tiles_f;
+    std::vector<int64_t> tiles_f_beg;
+    int64_t busy32 = 0;                // 32 x 32 tiles of the busiest XCD (edge_d = 32 only)
     bool by_cols = false;              // gather in pieces of 16 columns (gather_by_cols)
     std::vector<int64_t> cptr;        // per stored block: its contributions from the groups (adjoint)
     std::vector<int4> contrib;        // (group, row offset, column offset, 0), ascending group per block
@@ -146,7 +151,8 @@ struct Plan {
 // context's own buffers, or places in the static scratch array.
 struct DevView {
     const GroupDesc *gd = nullptr;
-    const TileDesc *tiles = nullptr, *tiles_s = nullptr, *tiles_b = nullptr, *tiles_d = nullptr;
+    const TileDesc *tiles = nullptr, *tiles_s = nullptr, *tiles_b = nullptr, *tiles_d = nullptr,
+                   *tiles_f = nullptr;
     const TileDesc *tiles_sx = nullptr;     // per-XCD lists of the persistent word products (context buffers only)
     const int32_t *xbeg = nullptr;
     const int2 *chunks = nullptr;
@@ -213,7 +219,7 @@ struct smx_context {
     DevBuf<int32_t> d_brow, d_bcol;
     // device: plan
     DevBuf<GroupDesc> d_gd;
-    DevBuf<TileDesc> d_tiles, d_tiles_s, d_tiles_b, d_tiles_sx, d_tiles_d;
+    DevBuf<TileDesc> d_tiles, d_tiles_s, d_tiles_b, d_tiles_sx, d_tiles_d, d_tiles_f;
     DevBuf<int32_t> d_xbeg, d_tq;           // per-XCD list offsets, counters of the persistent word products
     DevBuf<int2> d_chunks;
     DevBuf<RowInfo> d_rinfo;
@@ -534,12 +540,14 @@ int64_t group_bytes(const GroupDesc &d)
     return kArenaBytesPerElem * (int64_t)d.npad * d.npad + (2 * kMaxPolishMixed + 1) * 8 * (int64_t)d.npad * d.m_own;
 }
 
-// Tile edge of the FP64 and FP32 products (bitwise the same results).  Edge 64 once its
+// Tile edge of the FP64 products (bitwise the same results).  Edge 64 once its
 // tiles fill the chip: four workgroups on each of the 256 CUs are 1024 tiles.
-// With fewer, edge 32 spreads the same products over more waves.  Square per
-// launch, edge 32 / 64: 36 tiles of 64 (12 groups of n ~ 90) 6.3 / 11.0 us, 240
-// (16 of 271) 17.0 / 20.3, 920 (40 of 374) 55 / 61, 2476 (60 of 518) 187 / 191,
-// 3025 (40 of 724) 320 / 293, 3600 (100 of 503) 284 / 272.
+// With fewer, edge 32 spreads the same products over more waves.  Product per
+// launch, edge 32 / 64: 48 tiles of 64 (16 groups of n = 100) 7 / 13 us, 528 (8 of
+// 700) 64 / 80, 1320 (20 of 700) 162 / 169, 1128 (one of 3000) 3315 / 3310, 1440 (40 of
+// 500) 122 / 119; 2112 (32 of 700) 231 / 224, 2880 (80 of 500) 241 / 220, 4512 (four
+// of 3000) 3778 / 3251.  Near the line the two are within 8% either way, the groups'
+// sizes deciding (one of 1500 440 / 473, four 494 / 464; 240 of 200, 2400 tiles, 77 / 97).
 int32_t f64_edge(const Plan &P)
 {
     int64_t tiles64 = 0;
@@ -548,6 +556,33 @@ int32_t f64_edge(const Plan &P)
         tiles64 += nt * (nt + 1) / 2;
     }
     return tiles64 <= 1536 ? 32 : 64;
+}
+
+// The same for the FP32 products, whose operand stream from L2 is the larger part of
+// their time: edge 32 loads twice the bytes of edge 64, which larger groups do not hide.
+// Edge 32 / 64: 8 groups of n = 300 11.1 / 14.9 us, 8 of 700 41 / 46, 8 of 1000 108 / 108;
+// one of 1500 302 / 266, one of 2000 702 / 588, one of 3000 2278 / 1796.
+int32_t f32_edge(const Plan &P)
+{
+    return f64_edge(P) == 32 && P.max_npad <= 1024 ? 32 : 64;
+}
+
+// Whether the word products take 32 x 32 tiles instead of 128 x 128 ones (bitwise the
+// same results).  A group's tiles all run on one XCD, where a 32 x 32 tile loads four
+// times the operand bytes: they win while the XCD's 32 CUs have few of them, and the
+// 128 x 128 tiles of the same groups leave most of its CUs idle.  The line is the
+// number of 32 x 32 tiles on the busiest XCD.  Product per launch, 32 / 128:
+//   two FP16 words: 28 (200 x 4 groups) 7.0 / 23 us, 190 (600 x 8) 23 / 36, 272 (500 x 16)
+//     27 / 34, 378 (850 x 8) 46 / 47, 380 (600 x 16) 37 / 38, 506 (700 x 16) 52 / 46, 528 (one
+//     of 1000) 64 / 54, one of 2000 413 / 192, one of 3000 1329 / 535;
+//   three BF16 words: 190 32 / 52, 272 39 / 48, 378 73 / 67, 380 54 / 54, 528 110 / 80;
+//   one BF16 word, half the bytes and a third of the products: 136 (500 x 8) 17 / 22, 190
+//     20 / 23, 253 (700 x 8) 24.7 / 23.9, 272 22.5 / 21.1.
+// Spread over all XCDs (the caller's tile order 1), large groups miss the L2s: one of 1000
+// (66 tiles an XCD) 31 / 50 us, one of 2000 (252) 101 / 90.
+bool word_tiles32(const Plan &P, int32_t nw)
+{
+    return P.edge_d == 32 && P.max_npad <= 1536 && P.busy32 <= (nw == 1 ? 200 : nw == 2 ? 384 : 320);
 }
 
 // Whether an evaluation gathers A_g in pieces of 64 rows x 16 columns and takes
@@ -613,6 +648,10 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     P.by_cols = gather_by_cols(P);
     P.tiles_d.clear();
     P.tiles_d_beg.assign(1, 0);
+    P.edge_f = f32_edge(P);
+    P.tiles_f.clear();
+    P.tiles_f_beg.assign(1, 0);
+    P.busy32 = 0;
     P.tiles_sx.clear();
     P.sx_wbeg.assign(1, 0);
     P.xbeg.clear();
@@ -624,7 +663,7 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
     size_t ch = 0;
     for (int32_t w = 0; w < nw; w++) {
         int64_t e = 0, t = 0;
-        std::vector<TileDesc> tl, ts, tb, td;
+        std::vector<TileDesc> tl, ts, tb, td, tf;
         for (int32_t g = P.wave_g[w]; g < P.wave_g[w + 1]; g++) {
             GroupDesc &d = P.gd[g];
             d.off = e;
@@ -634,9 +673,13 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
             const int32_t nt = (d.npad + kTile - 1) / kTile;
             for (int32_t ti = 0; ti < nt; ti++)
                 for (int32_t tj = 0; tj <= ti; tj++) tl.push_back(TileDesc{g, (ti << 16) | tj});
-            const int32_t ntd = (d.npad + P.edge_d - 1) / P.edge_d;
-            for (int32_t ti = 0; ti < ntd; ti++)
-                for (int32_t tj = 0; tj <= ti; tj++) td.push_back(TileDesc{g, (ti << 16) | tj});
+            const auto lower = [&](int32_t edge, std::vector<TileDesc> &out) {
+                const int32_t nte = (d.npad + edge - 1) / edge;
+                for (int32_t ti = 0; ti < nte; ti++)
+                    for (int32_t tj = 0; tj <= ti; tj++) out.push_back(TileDesc{g, (ti << 16) | tj});
+            };
+            lower(P.edge_d, td);
+            if (P.edge_f != P.edge_d) lower(P.edge_f, tf);
             if (P.big[g]) {
                 const int32_t nt2 = (d.npad + kTile2 - 1) / kTile2;
                 for (int32_t ti = 0; ti < nt2; ti++)
@@ -664,7 +707,10 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
             if (!ts.empty()) xcd_order(P, P.wave_g[w], P.wave_g[w + 1], ts);
             if (!tb.empty()) xcd_order(P, P.wave_g[w], P.wave_g[w + 1], tb);
             xcd_order(P, P.wave_g[w], P.wave_g[w + 1], td);
+            if (!tf.empty()) xcd_order(P, P.wave_g[w], P.wave_g[w + 1], tf);
         }
+        // the XCDs take the launch's workgroups in turn (idle slots end the shorter lists)
+        if (P.edge_d == 32) P.busy32 = std::max<int64_t>(P.busy32, ((int64_t)td.size() + 7) / 8);
         P.tiles.insert(P.tiles.end(), tl.begin(), tl.end());
         P.tile_beg.push_back((int64_t)P.tiles.size());
         P.tiles_s.insert(P.tiles_s.end(), ts.begin(), ts.end());
@@ -673,6 +719,8 @@ int32_t partition_waves(smx_ctx c, Plan &P, int64_t budget)
         P.tiles_b_beg.push_back((int64_t)P.tiles_b.size());
         P.tiles_d.insert(P.tiles_d.end(), td.begin(), td.end());
         P.tiles_d_beg.push_back((int64_t)P.tiles_d.size());
+        P.tiles_f.insert(P.tiles_f.end(), tf.begin(), tf.end());
+        P.tiles_f_beg.push_back((int64_t)P.tiles_f.size());
         while (ch < P.chunks.size() && P.chunks[ch].x < P.wave_g[w + 1]) ch++;
         P.chunk_beg.push_back((int64_t)ch);
     }
@@ -705,24 +753,30 @@ int32_t check_plan(smx_ctx c, const Plan &P)
             const int ti = t.y >> 16, tj = t.y & 0xffff;
             if (tj > ti || ti * kTile >= d.npad) return fail(c, SMX_E_INVALID, "internal: tile index");
         }
-        // lower tiles of the FP64 products: every tile of every group of the wave
-        if ((int32_t)P.tiles_d_beg.size() != nw + 1 || P.tiles_d_beg[nw] != (int64_t)P.tiles_d.size() ||
-            (P.edge_d != 32 && P.edge_d != 64))
-            return fail(c, SMX_E_INVALID, "internal: FP64 tile tables");
-        int64_t nd = 0;
-        for (int64_t q = P.tiles_d_beg[w]; q < P.tiles_d_beg[w + 1]; q++) {
-            const TileDesc &t = P.tiles_d[(size_t)q];
-            if (t.x == -1) continue;
-            if (t.x < P.wave_g[w] || t.x >= P.wave_g[w + 1]) return fail(c, SMX_E_INVALID, "internal: FP64 tile group");
-            const int ti = t.y >> 16, tj = t.y & 0xffff;
-            if (tj > ti || ti * P.edge_d >= P.gd[t.x].npad) return fail(c, SMX_E_INVALID, "internal: FP64 tile index");
-            nd++;
+        // lower tiles of the FP64 and FP32 products: every tile of every group of the wave
+        for (int pass = 0; pass < 2; pass++) {
+            const std::vector<TileDesc> &L = pass ? P.tiles_f : P.tiles_d;
+            const std::vector<int64_t> &B = pass ? P.tiles_f_beg : P.tiles_d_beg;
+            const int32_t edge = pass ? P.edge_f : P.edge_d;
+            if ((int32_t)B.size() != nw + 1 || B[nw] != (int64_t)L.size() || (edge != 32 && edge != 64))
+                return fail(c, SMX_E_INVALID, "internal: FP64 tile tables");
+            if (pass && P.edge_f == P.edge_d && L.empty()) continue;
+            int64_t nd = 0;
+            for (int64_t q = B[w]; q < B[w + 1]; q++) {
+                const TileDesc &t = L[(size_t)q];
+                if (t.x == -1) continue;
+                if (t.x < P.wave_g[w] || t.x >= P.wave_g[w + 1])
+                    return fail(c, SMX_E_INVALID, "internal: FP64 tile group");
+                const int ti = t.y >> 16, tj = t.y & 0xffff;
+                if (tj > ti || ti * edge >= P.gd[t.x].npad) return fail(c, SMX_E_INVALID, "internal: FP64 tile index");
+                nd++;
+            }
+            for (int32_t g = P.wave_g[w]; g < P.wave_g[w + 1]; g++) {
+                const int64_t nt = (P.gd[g].npad + edge - 1) / edge;
+                nd -= nt * (nt + 1) / 2;
+            }
+            if (nd != 0) return fail(c, SMX_E_INVALID, "internal: FP64 tile count");
         }
-        for (int32_t g = P.wave_g[w]; g < P.wave_g[w + 1]; g++) {
-            const int64_t nt = (P.gd[g].npad + P.edge_d - 1) / P.edge_d;
-            nd -= nt * (nt + 1) / 2;
-        }
-        if (nd != 0) return fail(c, SMX_E_INVALID, "internal: FP64 tile count");
         // size-bucket lists: every group of the wave in exactly one of them,
         // with its full set of lower tiles of that shape
         if ((int32_t)P.tiles_s_beg.size() != nw + 1 || (int32_t)P.tiles_b_beg.size() != nw + 1 ||
@@ -852,6 +906,7 @@ int32_t ensure_plan(smx_ctx c)
     HIP_TRY(c, upload(c->d_tiles_sx, P.tiles_sx, c->stream));
     HIP_TRY(c, upload(c->d_xbeg, P.xbeg, c->stream));
     HIP_TRY(c, upload(c->d_tiles_d, P.tiles_d, c->stream));
+    HIP_TRY(c, upload(c->d_tiles_f, P.tiles_f, c->stream));
     HIP_TRY(c, upload(c->d_plist, P.plist, c->stream));
     c->contrib_ready = false;
     HIP_TRY(c, upload(c->d_chunks, P.chunks, c->stream));
@@ -1107,6 +1162,7 @@ int32_t smx_destroy(smx_ctx c)
     c->d_gd.release();
     c->d_tiles.release();
     c->d_tiles_d.release();
+    c->d_tiles_f.release();
     c->d_tiles_s.release();
     c->d_tiles_sx.release();
     c->d_xbeg.release();
@@ -1577,6 +1633,7 @@ bool plan_tables_valid(const Plan &P, int64_t nnzb, int32_t big_tile, std::strin
         return true;
     };
     if (!tiles_ok(P.tiles, kTile, "tiles") || !tiles_ok(P.tiles_d, P.edge_d, "FP64 tiles") ||
+        !tiles_ok(P.tiles_f, P.edge_f, "FP32 tiles") ||
         !tiles_ok(P.tiles_s, kTile, "128-tiles") ||
         !tiles_ok(P.tiles_b, big_tile, "256-tiles"))
         return false;
@@ -1650,6 +1707,7 @@ DevView ctx_view(smx_ctx c)
     v.tiles_s = c->d_tiles_s.p;
     v.tiles_b = c->d_tiles_b.p;
     v.tiles_d = c->d_tiles_d.p;
+    v.tiles_f = c->d_tiles_f.p;
     v.tiles_sx = c->d_tiles_sx.p;
     v.xbeg = c->d_xbeg.p;
     v.chunks = c->d_chunks.p;
@@ -1831,10 +1889,13 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const TileDesc *tl = V.tiles + P.tile_beg[wave];
         const int ntd = (int)(P.tiles_d_beg[wave + 1] - P.tiles_d_beg[wave]);
         const TileDesc *tld = V.tiles_d + P.tiles_d_beg[wave];
+        const bool own_f = P.edge_f != P.edge_d;      // the FP32 products have a list of their own
+        const int ntf = own_f ? (int)(P.tiles_f_beg[wave + 1] - P.tiles_f_beg[wave]) : ntd;
+        const TileDesc *tlf = own_f ? V.tiles_f + P.tiles_f_beg[wave] : tld;
         // one- and two-word products: the size buckets (128 x 128 and 256 x 256 tiles)
         // few tiles: all groups on 32 x 32 tiles, unless the caller chose a tile
         // shape or operand stream
-        const bool words32 = mixed && fmt != 2 && P.edge_d == 32 && c->big_min_npad == 0 && c->kernel_variant == 0;
+        const bool words32 = mixed && fmt != 2 && word_tiles32(P, nw) && c->big_min_npad == 0 && c->kernel_variant == 0;
         const bool buckets = mixed && fmt != 2 && nw <= 2 && !words32;
         const int nts = (int)(P.tiles_s_beg[wave + 1] - P.tiles_s_beg[wave]);
         const int ntb = (int)(P.tiles_b_beg[wave + 1] - P.tiles_b_beg[wave]);
@@ -1909,7 +1970,7 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                         r = run(kind256, [&] { return launch_ns_words256(s, fmt, nw, mode, b.n, b.tl, V.gd, x, y, o, it,
                                                                          k, c->switch_tol, kmax); });
                     else if (fmt == 2)
-                        r = run(kind128, [&] { return launch_ns_f32(s, mode, P.edge_d, ntd, tld, V.gd, x, y, o, it, k,
+                        r = run(kind128, [&] { return launch_ns_f32(s, mode, P.edge_f, ntf, tlf, V.gd, x, y, o, it, k,
                                                                     c->switch_tol, kmax); });
                     else if (words32)
                         r = run(kind128, [&] { return launch_ns_words32(s, fmt, nw, mode, ntd, tld, V.gd, x, y, o, it, k,
@@ -2164,7 +2225,7 @@ int32_t eig_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView &
 // context memory allocated by earlier calls.
 struct StaticLayout {
     int64_t gd = 0, tiles = 0, chunks = 0, rinfo = 0, bmap = 0, boffs = 0, scat = 0, own = 0, plist = 0;
-    int64_t tiles_s = 0, tiles_b = 0, tiles_d = 0;
+    int64_t tiles_s = 0, tiles_b = 0, tiles_d = 0, tiles_f = 0;
     int64_t scale = 0, resid = 0, done = 0, kfinal = 0, flags = 0, ndone = 0, tdiag = 0, tau_hist = 0;
     int64_t pe = 0, pn = 0, arena = 0, pool = 0, end = 0;
 };
@@ -2187,6 +2248,7 @@ StaticLayout static_layout(smx_ctx c, const Plan &P, int32_t stride)
     L.tiles_s = take(vbytes(P.tiles_s));
     L.tiles_b = take(vbytes(P.tiles_b));
     L.tiles_d = take(vbytes(P.tiles_d));
+    L.tiles_f = take(vbytes(P.tiles_f));
     L.chunks = take(vbytes(P.chunks));
     L.rinfo = take(vbytes(P.rinfo));
     L.bmap = take((int64_t)sizeof(int32_t) * P.n_map);
@@ -2309,6 +2371,7 @@ int32_t smx_evaluate_static(smx_ctx c)
             HIP_TRY(c, upload_to(base, L.tiles_s, P.tiles_s, st));
             HIP_TRY(c, upload_to(base, L.tiles_b, P.tiles_b, st));
             HIP_TRY(c, upload_to(base, L.tiles_d, P.tiles_d, st));
+            HIP_TRY(c, upload_to(base, L.tiles_f, P.tiles_f, st));
             HIP_TRY(c, upload_to(base, L.chunks, P.chunks, st));
             HIP_TRY(c, upload_to(base, L.rinfo, P.rinfo, st));
             HIP_TRY(c, upload_to(base, L.bmap, P.bmap, st));
@@ -2326,6 +2389,7 @@ int32_t smx_evaluate_static(smx_ctx c)
     V.tiles_s = reinterpret_cast<const TileDesc *>(base + L.tiles_s);
     V.tiles_b = reinterpret_cast<const TileDesc *>(base + L.tiles_b);
     V.tiles_d = reinterpret_cast<const TileDesc *>(base + L.tiles_d);
+    V.tiles_f = reinterpret_cast<const TileDesc *>(base + L.tiles_f);
     V.chunks = reinterpret_cast<const int2 *>(base + L.chunks);
     V.rinfo = reinterpret_cast<const RowInfo *>(base + L.rinfo);
     V.bmap = reinterpret_cast<const int32_t *>(base + L.bmap);
@@ -2553,7 +2617,7 @@ int32_t smx_get_stats(smx_ctx c, smx_stats *out)
     double ws = 0;
     for (size_t b : {c->d_k.bytes(), c->d_d.bytes(), c->d_arena.bytes(), c->d_tpool.bytes(), c->d_tx0.bytes(), c->d_tx1.bytes(), c->d_adj.bytes(), c->d_bmap.bytes(),
                      c->d_rinfo.bytes(), c->d_scat.bytes(), c->d_resid.bytes(), c->d_tiles.bytes(), c->d_tiles_d.bytes(),
-                     c->d_plist.bytes(), c->ws_ptr ? c->ws_bytes : (size_t)0})
+                     c->d_tiles_f.bytes(), c->d_plist.bytes(), c->ws_ptr ? c->ws_bytes : (size_t)0})
         ws += (double)b;
     s.workspace_bytes = ws;
     *out = s;
