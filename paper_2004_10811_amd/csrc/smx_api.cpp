@@ -285,6 +285,7 @@ struct smx_context {
     std::vector<int32_t> launch_subset;  // groups of the launch: 0 all, 1 the 128-tile bucket, 2 the 256-tile bucket
     std::vector<hipEvent_t> ev_wave;     // four per wave: start, iterate, scatter, end
     hipEvent_t ev_t0 = nullptr, ev_t3 = nullptr;
+    SideStream side;                     // created with the first plan that needs it (eval_prepare)
 
     // results of the last evaluation
     bool evaluated = false;
@@ -1149,6 +1150,7 @@ int32_t smx_destroy(smx_ctx c)
     if (!c) return SMX_E_INVALID;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
+    if (c->side.stream) (void)hipStreamSynchronize(c->side.stream);
     for (auto *b : {&c->d_k, &c->d_d, &c->d_arena, &c->d_pe, &c->d_pn, &c->d_ne, &c->d_check})
         b->release();
     if (c->h) (void)hipHostFree(c->h);
@@ -1205,6 +1207,9 @@ int32_t smx_destroy(smx_ctx c)
     c->d_ebe.release();
     drop_graphs(c);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    if (c->side.stream) (void)hipStreamDestroy(c->side.stream);
+    for (hipEvent_t ev : {c->side.fork, c->side.join})
+        if (ev) (void)hipEventDestroy(ev);
     if (c->h_ndone) (void)hipHostFree(c->h_ndone);
     for (hipEvent_t ev : c->ev_poll) (void)hipEventDestroy(ev);
     for (hipEvent_t ev : c->ev_launch) (void)hipEventDestroy(ev);
@@ -1557,6 +1562,12 @@ int32_t eval_prepare(smx_ctx c, const EvalMode &m)
         if (P.max_npad > kEigMaxN)
             return fail(c, SMX_E_UNSUPPORTED, "the diagonalisation path takes submatrices up to n = " +
                                                   std::to_string(kEigMaxN));
+        if (P.max_npad > kEigHalfMaxN && !c->side.join) {
+            // not a blocking stream: work on the null stream must not wait for it, nor it for that
+            if (!c->side.stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->side.stream, hipStreamNonBlocking));
+            if (!c->side.fork) HIP_TRY(c, hipEventCreateWithFlags(&c->side.fork, hipEventDisableTiming));
+            HIP_TRY(c, hipEventCreateWithFlags(&c->side.join, hipEventDisableTiming));
+        }
         const size_t nr = std::max<size_t>(P.rinfo.size(), 1);
         for (auto *b : {&c->d_ed, &c->d_ee, &c->d_etau, &c->d_elam, &c->d_elabs, &c->d_ew}) HIP_TRY(c, b->ensure(nr));
         HIP_TRY(c, c->d_ebs.ensure(nr));
@@ -2132,7 +2143,12 @@ int32_t eig_decompose_wave(smx_ctx c, const Plan &P, const DevView &V, double *a
         }
         c->launch_ev.push_back(c->n_ev);
         HIP_TRY(c, hipEventRecord(c->ev_launch[(size_t)c->n_ev++], st));
-        HIP_TRY(c, launch_eig_tridiag(st, g0, wng, P.max_npad, V.gd, a, s, ev));     // s is free until the eigenvectors
+        int32_t lo = P.gd[g0].npad, hi = lo;
+        for (int32_t g = g0; g < g0 + wng; g++) {
+            lo = std::min(lo, P.gd[g].npad);
+            hi = std::max(hi, P.gd[g].npad);
+        }
+        HIP_TRY(c, launch_eig_tridiag(st, c->side, g0, wng, lo, hi, V.gd, a, s, ev));     // s is free until the eigenvectors
         HIP_TRY(c, hipEventRecord(c->ev_launch[(size_t)c->n_ev++], st));
         c->launch_step.push_back(0);
         c->launch_kind.push_back(12);

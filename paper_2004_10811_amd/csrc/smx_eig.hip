@@ -278,11 +278,12 @@ __device__ inline double panel_row(const double *__restrict__ V, const double *_
     return s;
 }
 
-constexpr int kHalfMaxN = 1280;     // largest n whose eight per-wave sums fit the LDS beside the rest
+constexpr int kHalfMaxN = kEigHalfMaxN;
 
 // HALF: the trailing block is read and kept up to date in its lower triangle
 // only, n <= kHalfMaxN; otherwise in full, larger n.  A launch covers all groups
-// and returns at once from those of the other kind.
+// and returns at once from those of the other kind; where a wave has both kinds, the
+// two launches run side by side (launch_eig_tridiag).
 //
 // What bounds it: HBM.  With one group per CU the trailing blocks (5.8 MB each
 // at n = 850) stay in no cache, and A_s v reads them once per step.  water256 at
@@ -1214,18 +1215,33 @@ void n_reduce_kernel(int ng, int nmu, const double *__restrict__ part, double *_
 
 }  // namespace
 
-hipError_t launch_eig_tridiag(hipStream_t st, int g0, int ngroups, int max_npad, const GroupDesc *groups, double *a,
-                              double *wpanel, const EigVecs &ev)
+hipError_t launch_eig_tridiag(hipStream_t st, const SideStream &side, int g0, int ngroups, int min_npad, int max_npad,
+                              const GroupDesc *groups, double *a, double *wpanel, const EigVecs &ev)
 {
     if (ngroups <= 0) return hipSuccess;
-    hipLaunchKernelGGL(tridiag_kernel<true>, dim3((unsigned)ngroups), dim3(kEigBlock), 0, st, groups, g0, a, wpanel, ev);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (max_npad > kHalfMaxN) {
-        hipLaunchKernelGGL(tridiag_kernel<false>, dim3((unsigned)ngroups), dim3(kEigBlock), 0, st, groups, g0, a, wpanel, ev);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    const auto go = [&](auto kernel, hipStream_t on) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ngroups), dim3(kEigBlock), 0, on, groups, g0, a, wpanel, ev);
+        return hipGetLastError();
+    };
+    hipError_t e = hipSuccess;
+    // A workgroup holds its CU to itself for its group's whole reduction.  Groups of
+    // both kinds reduced one kind after the other leave the CUs of the second kind
+    // idle during the first: 256 groups of n 583-1395 348 ms, in full and all at once
+    // 316 ms, side by side on two streams 304 ms.  (Both bodies in one kernel lost
+    // their loads in flight: 926 ms.)
+    if (max_npad <= kEigHalfMaxN) {
+        e = go(tridiag_kernel<true>, st);
+    } else if (min_npad > kEigHalfMaxN) {
+        e = go(tridiag_kernel<false>, st);
+    } else {
+        e = hipEventRecord(side.fork, st);
+        if (e == hipSuccess) e = hipStreamWaitEvent(side.stream, side.fork, 0);
+        if (e == hipSuccess) e = go(tridiag_kernel<false>, side.stream);
+        if (e == hipSuccess) e = hipEventRecord(side.join, side.stream);
+        if (e == hipSuccess) e = go(tridiag_kernel<true>, st);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, side.join, 0);
     }
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(split_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, groups, g0, ev);
     return hipGetLastError();
 }

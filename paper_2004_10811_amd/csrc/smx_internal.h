@@ -348,11 +348,21 @@ struct EigVecs {
     int32_t *bs, *be;
 };
 
+// Largest n whose reduction reads the trailing block's lower triangle only.  A multiple
+// of 32: n is at most this where n_pad is.
+constexpr int kEigHalfMaxN = 1280;
+// A stream beside the caller's, and the events that fork work to it and join it back.
+struct SideStream {
+    hipStream_t stream = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
+};
 // Householder reduction of each group's slab (A_g - mu0 I, column-major) to
 // tridiagonal form, reflectors left below the subdiagonal; then the split.
 // wpanel: a second slab (n_pad x 16 of each group's place used as panel work).
-hipError_t launch_eig_tridiag(hipStream_t st, int g0, int ngroups, int max_npad, const GroupDesc *groups, double *a,
-                              double *wpanel, const EigVecs &ev);
+// min_npad, max_npad: the smallest and largest n_pad of these groups; side is used (and
+// must be there) where kEigHalfMaxN lies between them.  All of it is done on st's order.
+hipError_t launch_eig_tridiag(hipStream_t st, const SideStream &side, int g0, int ngroups, int min_npad, int max_npad,
+                              const GroupDesc *groups, double *a, double *wpanel, const EigVecs &ev);
 // Eigenvalues (bisection) and eigenvectors (twisted factorisations, then
 // Gram-Schmidt inside tight clusters) of T: s[i * n_pad + l] = component i of
 // eigenvector l; scratch: one more slab.
