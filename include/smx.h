@@ -253,7 +253,8 @@ int32_t smx_set_kernel_variant(smx_ctx ctx, int32_t variant);
  * smx_evaluate first validates every plan table on the host against the sizes
  * it indexes (slab, own-column and row-table offsets, block maps and offsets,
  * product tiles inside each group's lower triangle, gather chunks, scatter
- * blocks inside their submatrix; SMX_E_INVALID naming the table), and writes
+ * blocks inside their submatrix, the block maps also as they lie on the device;
+ * SMX_E_INVALID naming the table), and writes
  * a 64-KB guard pattern right after the extent the evaluation may write in
  * the arena, the polish pool and D (device memory the library owns); smx_wait
  * reads the guards back and returns SMX_E_HIP naming the buffer if a byte

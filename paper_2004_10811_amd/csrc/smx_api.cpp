@@ -1670,6 +1670,17 @@ int32_t arm_guards(smx_ctx c, bool pool)
     std::string why;
     build_map(c, c->plan);
     if (!plan_tables_valid(c->plan, c->nnzb, kTile2, why)) return fail(c, SMX_E_INVALID, "debug check: plan table: " + why);
+    {
+        // the gathers index with the map block_map_kernel wrote: it has to be the host's
+        std::vector<int32_t> dev(c->plan.bmap.size());
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        HIP_TRY(c, hipMemcpy(dev.data(), c->d_bmap.p, vbytes(dev), hipMemcpyDeviceToHost));
+        const auto at = std::mismatch(dev.begin(), dev.end(), c->plan.bmap.begin());
+        if (at.first != dev.end())
+            return fail(c, SMX_E_INVALID, "debug check: plan table: block map entry " +
+                                              std::to_string(at.first - dev.begin()) + " on the device is " +
+                                              std::to_string(*at.first) + ", not " + std::to_string(*at.second));
+    }
     HIP_TRY(c, c->d_d.ensure((size_t)std::max<int64_t>(c->nvals, 1) + kGuardElems));
     HIP_TRY(c, hipMemsetAsync(c->d_d.p + c->nvals, kGuardByte, kGuardElems * 8, c->stream));
     if (!c->ws_ptr) {
