@@ -290,6 +290,7 @@ struct smx_context {
     // results of the last evaluation
     bool evaluated = false;
     bool end_recorded = false;              // ev_t3 marks the end of the last evaluation
+    bool moved = false;                     // smx_set_stream was called after it
     int32_t steps_launched = 0;
     int32_t last_precision = SMX_FP64;
     int32_t last_iteration = SMX_ITER_NS2;
@@ -973,15 +974,19 @@ int32_t set_device(smx_ctx c)
 int32_t need_sync_results(smx_ctx c)
 {
     if (!c->evaluated) return fail(c, SMX_E_STATE, "no evaluation has been run");
-    if (c->end_recorded) HIP_TRY(c, hipEventSynchronize(c->ev_t3));    // on whatever stream it ran
+    if (c->end_recorded && c->moved) {              // it ran on another stream; waiting once is enough
+        HIP_TRY(c, hipEventSynchronize(c->ev_t3));
+        c->end_recorded = false;
+    }
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return SMX_OK;
 }
 
 // Before the host reads what the device wrote to pinned memory (N, E, flag
 // counts): no copy orders that read behind the evaluation.  The event covers an
-// evaluation whose stream is not the context's any more; the null stream covers one
-// that no event marks, a captured one replayed there or on another blocking stream.
+// evaluation whose stream is not the context's any more (only then: waiting for it takes
+// some 20 us more than for the stream); the null stream covers one that no event marks, a
+// captured one replayed there or on another blocking stream.
 int32_t need_published(smx_ctx c)
 {
     if (int32_t st = need_sync_results(c)) return st;
@@ -997,6 +1002,7 @@ int32_t record_end(smx_ctx c)
     const hipError_t e = hipStreamIsCapturing(c->stream, &cs);
     if (e != hipSuccess) (void)hipGetLastError();
     c->end_recorded = e == hipSuccess && cs == hipStreamCaptureStatusNone;
+    c->moved = false;
     HIP_TRY(c, hipEventRecord(c->ev_t3, c->stream));
     return SMX_OK;
 }
@@ -1230,6 +1236,7 @@ int32_t smx_set_stream(smx_ctx c, void *hip_stream)
 {
     if (!c) return SMX_E_INVALID;
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);
+    c->moved = true;
     return SMX_OK;
 }
 
