@@ -117,6 +117,7 @@ struct Plan {
     std::vector<TileDesc> tiles_f;
     std::vector<int64_t> tiles_f_beg;
     int64_t busy32 = 0;                // 32 x 32 tiles of the busiest XCD (edge_d = 32 only)
+    bool quarters = false;             // those products take the quarters of the 128 x 128 tiles, no lists
     bool by_cols = false;              // gather in pieces of 16 columns (gather_by_cols)
     std::vector<int64_t> cptr;        // per stored block: its contributions from the groups (adjoint)
     std::vector<int4> contrib;        // (group, row offset, column offset, 0), ascending group per block
@@ -584,7 +585,7 @@ int32_t f32_edge(const Plan &P)
 // (66 tiles an XCD) 31 / 50 us, one of 2000 (252) 101 / 90.
 bool word_tiles32(const Plan &P, int32_t nw)
 {
-    return P.edge_d == 32 && P.max_npad <= 1536 && P.busy32 <= (nw == 1 ? 200 : nw == 2 ? 384 : 320);
+    return P.edge_d == 32 && !P.quarters && P.max_npad <= 1536 && P.busy32 <= (nw == 1 ? 200 : nw == 2 ? 384 : 320);
 }
 
 // Whether an evaluation gathers A_g in pieces of 64 rows x 16 columns and takes
@@ -760,6 +761,7 @@ int32_t check_plan(smx_ctx c, const Plan &P)
             const std::vector<TileDesc> &L = pass ? P.tiles_f : P.tiles_d;
             const std::vector<int64_t> &B = pass ? P.tiles_f_beg : P.tiles_d_beg;
             const int32_t edge = pass ? P.edge_f : P.edge_d;
+            if (P.quarters && L.empty()) continue;
             if ((int32_t)B.size() != nw + 1 || B[nw] != (int64_t)L.size() || (edge != 32 && edge != 64))
                 return fail(c, SMX_E_INVALID, "internal: FP64 tile tables");
             if (pass && P.edge_f == P.edge_d && L.empty()) continue;
@@ -1916,11 +1918,14 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
         const int32_t g0 = P.wave_g[wave], wng = P.wave_g[wave + 1] - g0;
         const int ntiles = (int)(P.tile_beg[wave + 1] - P.tile_beg[wave]);
         const TileDesc *tl = V.tiles + P.tile_beg[wave];
-        const int ntd = (int)(P.tiles_d_beg[wave + 1] - P.tiles_d_beg[wave]);
-        const TileDesc *tld = V.tiles_d + P.tiles_d_beg[wave];
-        const bool own_f = P.edge_f != P.edge_d;      // the FP32 products have a list of their own
-        const int ntf = own_f ? (int)(P.tiles_f_beg[wave + 1] - P.tiles_f_beg[wave]) : ntd;
-        const TileDesc *tlf = own_f ? V.tiles_f + P.tiles_f_beg[wave] : tld;
+        // the FP64 (and 32 x 32 word) and the FP32 products' tiles
+        const int32_t edge_d = P.quarters ? 64 : P.edge_d, edge_f = P.quarters ? 64 : P.edge_f;
+        TileList ltd{tl, ntiles, true}, ltf = ltd;
+        if (!P.quarters) {
+            ltd = ltf = TileList{V.tiles_d + P.tiles_d_beg[wave], (int)(P.tiles_d_beg[wave + 1] - P.tiles_d_beg[wave]), false};
+            if (edge_f != edge_d)
+                ltf = TileList{V.tiles_f + P.tiles_f_beg[wave], (int)(P.tiles_f_beg[wave + 1] - P.tiles_f_beg[wave]), false};
+        }
         // one- and two-word products: the size buckets (128 x 128 and 256 x 256 tiles)
         // few tiles: all groups on 32 x 32 tiles, unless the caller chose a tile
         // shape or operand stream
@@ -1962,21 +1967,21 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
             // (W = (15 I - 10 T + 3 T^2) / 8), update X W.
             if (!mixed) {
                 if (!pade) {
-                    e = run(0, [&] { return launch_ns_f64(s, 0, P.edge_d, ntd, tld, V.gd, xb[k & 1], xb[k & 1], wslab, it, k,
+                    e = run(0, [&] { return launch_ns_f64(s, 0, edge_d, ltd, V.gd, xb[k & 1], xb[k & 1], wslab, it, k,
                                                           c->tol, c->max_iter, 0); });
                 } else {
                     double *tt = xb[(k + 1) & 1];
-                    e = run(0, [&] { return launch_ns_f64(s, 5, P.edge_d, ntd, tld, V.gd, xb[k & 1], xb[k & 1], tt, it, k,
+                    e = run(0, [&] { return launch_ns_f64(s, 5, edge_d, ltd, V.gd, xb[k & 1], xb[k & 1], tt, it, k,
                                                           c->tol, c->max_iter, 0); });
                     if (e == hipSuccess)
-                        e = run(11, [&] { return launch_ns_f64(s, 6, P.edge_d, ntd, tld, V.gd, tt, tt, wslab, it, k, c->tol,
+                        e = run(11, [&] { return launch_ns_f64(s, 6, edge_d, ltd, V.gd, tt, tt, wslab, it, k, c->tol,
                                                                c->max_iter, 0); });
                 }
                 if (e == hipSuccess)
-                    e = run(1, [&] { return launch_ns_f64(s, 1, P.edge_d, ntd, tld, V.gd, xb[k & 1], wslab, xb[(k + 1) & 1],
+                    e = run(1, [&] { return launch_ns_f64(s, 1, edge_d, ltd, V.gd, xb[k & 1], wslab, xb[(k + 1) & 1],
                                                           it, k, c->tol, c->max_iter, 0); });
                 if (e == hipSuccess && tangent)
-                    e = run(6, [&] { return launch_ns_f64(s, 2, P.edge_d, ntd, tld, V.gd, tb[k & 1], wslab, tb[(k + 1) & 1],
+                    e = run(6, [&] { return launch_ns_f64(s, 2, edge_d, ltd, V.gd, tb[k & 1], wslab, tb[(k + 1) & 1],
                                                           it, k, c->tol, c->max_iter, 0); });
             } else {
                 // one launch per size bucket and product (one bucket of all
@@ -1999,10 +2004,10 @@ int32_t eval_enqueue(smx_ctx c, const EvalMode &m, const Plan &P, const DevView 
                         r = run(kind256, [&] { return launch_ns_words256(s, fmt, nw, mode, b.n, b.tl, V.gd, x, y, o, it,
                                                                          k, c->switch_tol, kmax); });
                     else if (fmt == 2)
-                        r = run(kind128, [&] { return launch_ns_f32(s, mode, P.edge_f, ntf, tlf, V.gd, x, y, o, it, k,
+                        r = run(kind128, [&] { return launch_ns_f32(s, mode, edge_f, ltf, V.gd, x, y, o, it, k,
                                                                     c->switch_tol, kmax); });
                     else if (words32)
-                        r = run(kind128, [&] { return launch_ns_words32(s, fmt, nw, mode, ntd, tld, V.gd, x, y, o, it, k,
+                        r = run(kind128, [&] { return launch_ns_words32(s, fmt, nw, mode, ltd.n, ltd.tiles, V.gd, x, y, o, it, k,
                                                                         c->switch_tol, kmax); });
                     else if (persistent && mode <= 1)
                         r = run(kind128, [&] {
@@ -2281,8 +2286,10 @@ StaticLayout static_layout(smx_ctx c, const Plan &P, int32_t stride)
     L.tiles = take(vbytes(P.tiles));
     L.tiles_s = take(vbytes(P.tiles_s));
     L.tiles_b = take(vbytes(P.tiles_b));
-    L.tiles_d = take(vbytes(P.tiles_d));
-    L.tiles_f = take(vbytes(P.tiles_f));
+    if (!P.quarters) {
+        L.tiles_d = take(vbytes(P.tiles_d));
+        L.tiles_f = take(vbytes(P.tiles_f));
+    }
     L.chunks = take(vbytes(P.chunks));
     L.rinfo = take(vbytes(P.rinfo));
     L.bmap = take((int64_t)sizeof(int32_t) * P.n_map);
@@ -2329,6 +2336,13 @@ int32_t static_plan(smx_ctx c, int32_t stride)
             return st;
         }
         if (static_layout(c, P, stride).end <= cap) break;
+        // without the lists of the smaller tiles, whose place may be what is missing: the
+        // FP64 and FP32 products then take the quarters of the 128 x 128 ones
+        P.quarters = true;
+        P.tiles_d.clear();
+        P.tiles_f.clear();
+        if (static_layout(c, P, stride).end <= cap) break;
+        P.quarters = false;
         budget = budget * 15 / 16;
     }
     build_map(c, P);
@@ -2422,8 +2436,10 @@ int32_t smx_evaluate_static(smx_ctx c)
     V.tiles = reinterpret_cast<const TileDesc *>(base + L.tiles);
     V.tiles_s = reinterpret_cast<const TileDesc *>(base + L.tiles_s);
     V.tiles_b = reinterpret_cast<const TileDesc *>(base + L.tiles_b);
-    V.tiles_d = reinterpret_cast<const TileDesc *>(base + L.tiles_d);
-    V.tiles_f = reinterpret_cast<const TileDesc *>(base + L.tiles_f);
+    if (!P.quarters) {
+        V.tiles_d = reinterpret_cast<const TileDesc *>(base + L.tiles_d);
+        V.tiles_f = reinterpret_cast<const TileDesc *>(base + L.tiles_f);
+    }
     V.chunks = reinterpret_cast<const int2 *>(base + L.chunks);
     V.rinfo = reinterpret_cast<const RowInfo *>(base + L.rinfo);
     V.bmap = reinterpret_cast<const int32_t *>(base + L.bmap);
@@ -3304,8 +3320,7 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     it.poll = nullptr;
     it.poll_tag = 0;
     const int scratch_slot = c->last_max_iter + 1;    // residual slot the adjoint squares may use
-    const int nt = (int)P.tiles_d.size();
-    const TileDesc *tl = c->d_tiles_d.p;
+    const TileList tl{c->d_tiles_d.p, (int)P.tiles_d.size(), false};
 
     // seed: sym(-1/2 dL/dD at the own-column stored positions)
     HIP_TRY(c, hipMemsetAsync(xb[0], 0, sizeof(double) * (size_t)E, st));
@@ -3341,15 +3356,15 @@ int32_t smx_backward(smx_ctx c, double gE, double gN, const double *gD, int32_t 
     for (int32_t k = 0; k < kmax; k++) {
         const double *xk = x[k & 1], *bk = xb[k & 1];
         it.kact = k;
-        HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, nt, tl, c->d_gd.p, xk, xk, w, it, scratch_slot, 0.0,
+        HIP_TRY(c, launch_ns_f64(st, 0, P.edge_d, tl, c->d_gd.p, xk, xk, w, it, scratch_slot, 0.0,
                                  c->last_max_iter, 1));
-        HIP_TRY(c, launch_ns_f64(st, 3, P.edge_d, nt, tl, c->d_gd.p, xk, bk, wb, it, scratch_slot, 0.0,
+        HIP_TRY(c, launch_ns_f64(st, 3, P.edge_d, tl, c->d_gd.p, xk, bk, wb, it, scratch_slot, 0.0,
                                  c->last_max_iter, 1, bk, xk));
-        HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, nt, tl, c->d_gd.p, bk, w, xb[(k + 1) & 1], it, scratch_slot, 0.0,
+        HIP_TRY(c, launch_ns_f64(st, 4, P.edge_d, tl, c->d_gd.p, bk, w, xb[(k + 1) & 1], it, scratch_slot, 0.0,
                                  c->last_max_iter, 1, xk, wb));
         it.kact = k + 1;                              // X_{k+1} for the groups that take step k + 1
         if (k + 1 < kmax)
-            HIP_TRY(c, launch_ns_f64(st, 1, P.edge_d, nt, tl, c->d_gd.p, xk, w, x[(k + 1) & 1], it, scratch_slot, 0.0,
+            HIP_TRY(c, launch_ns_f64(st, 1, P.edge_d, tl, c->d_gd.p, xk, w, x[(k + 1) & 1], it, scratch_slot, 0.0,
                                      c->last_max_iter, 1));
     }
     // dK: transposed gather of Abar = Xbar / s_g plus gE D; dL/dmu = -sum_g tr(Abar_g)

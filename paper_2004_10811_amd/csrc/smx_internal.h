@@ -135,6 +135,33 @@ __device__ inline double gather_row(const GroupDesc &gd, int r, const RowInfo *_
     return real ? rowsum : 0.0;
 }
 
+// Tiles of an FP64 or FP32 product: a list of tiles of its edge, or (quarters) a list of
+// 128 x 128 tiles of which each stands for its four 64 x 64 quarters.  The quarters above
+// the diagonal and beyond the matrix are workgroups with nothing to do (an evaluation of
+// 256 groups of n ~ 855 in FP64 117 ms, 108 from a list of 64 x 64 tiles), so this form is
+// taken only where smx_evaluate_static's array has no room for the list.
+struct TileList {
+    const TileDesc *tiles;
+    int32_t n;
+    bool quarters;
+};
+// Workgroups of a launch over the list.  A tile's quarters go to the tile's XCD
+// (workgroup b runs on XCD b % 8, entry q of the list is meant for XCD q % 8).
+inline unsigned tile_grid(const TileList &l)
+{
+    return l.quarters ? (unsigned)((l.n + 7) / 8 * 8) * 4 : (unsigned)l.n;
+}
+// This workgroup's quarter of n 128 x 128 tiles, as a 64 x 64 tile; group -1: none.  It
+// may lie beyond the matrix.
+__device__ inline TileDesc quarter_tile(const TileDesc *tiles, int n)
+{
+    const int b = (int)blockIdx.x, q = (b >> 5 << 3) + (b & 7), s = b >> 3 & 3;
+    if (q >= n) return TileDesc{-1, 0};
+    const TileDesc t = tiles[q];
+    const int ti = 2 * (t.y >> 16) + (s >> 1), tj = 2 * (t.y & 0xffff) + (s & 1);
+    return TileDesc{tj > ti ? -1 : t.x, ti << 16 | tj};
+}
+
 // ---- launchers (stream-ordered, no synchronisation) -----------------------
 
 // Block maps of all groups: entry (a, b) of group g's is the storage position of
@@ -166,10 +193,10 @@ hipError_t launch_gather_cols(hipStream_t st, int nchunks, const int2 *chunks, i
 // (All operands symmetric; the sums of the two products are symmetric too.)
 // mode 5 (Pade square): T = a^2 X X stored, residual as mode 0.
 // mode 6 (Pade combine): out = (15 I - 10 x + 3 x x) / 8 with x = b = T.
-// edge: tile edge of the list (32 or 64).
-hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
-                         const GroupDesc *groups, const double *x, const double *b, double *out,
-                         const IterState &it, int k, double tol, int max_iter, int polish,
+// edge: tile edge (32, or 64 with or without quarters).
+hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, const TileList &tiles, const GroupDesc *groups,
+                         const double *x, const double *b, double *out, const IterState &it, int k, double tol,
+                         int max_iter, int polish,
                          const double *x2 = nullptr, const double *b2 = nullptr);
 
 // ---- adjoint helpers ------------------------------------------------------
@@ -232,7 +259,7 @@ hipError_t launch_ns_words32(hipStream_t st, int fmt, int nw, int mode, int ntil
                              unsigned short *out, const IterState &it, int k, double switch_tol, int kmax);
 // The same for FP32 values (one per element, column-major like the FP64 slabs), on
 // the lower tiles of the FP64 products (edge 32 or 64).
-hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, const TileList &tiles, const GroupDesc *groups,
                          const unsigned short *x, const unsigned short *b, unsigned short *out, const IterState &it,
                          int k, double switch_tol, int kmax);
 // The same products on 256 x 256 output tiles (tiles list (group, tile row

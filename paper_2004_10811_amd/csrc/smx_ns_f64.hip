@@ -61,13 +61,15 @@ __device__ inline double wave_max(double v)
     return v;
 }
 
-template <int MODE, int WB>
+// QUARTERS (WB = 2): the list holds nlist 128 x 128 tiles, see TileList.
+template <int MODE, int WB, bool QUARTERS>
 __global__ __launch_bounds__(256, 4)
 void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
                    const double *__restrict__ xin, const double *__restrict__ bin,
                    double *__restrict__ out, IterState it, int k, double tol, int max_iter, int polish,
-                   const double *__restrict__ x2, const double *__restrict__ b2)
+                   const double *__restrict__ x2, const double *__restrict__ b2, int nlist)
 {
+    static_assert(WB == 2 || !QUARTERS, "a quarter of a 128 x 128 tile has edge 64");
     constexpr int BM = 32 * WB;        // tile edge: 2 x 2 waves of WB x WB blocks of 16 x 16
     constexpr int WE = 16 * WB;        // edge of a wave's part of the tile
     __shared__ double As[2][BM][SK];
@@ -79,7 +81,7 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
         loaded(it.resid_bits, it.scale_bits);
         loaded(xin, bin);
     }
-    const TileDesc td = tiles[blockIdx.x];
+    const TileDesc td = QUARTERS ? quarter_tile(tiles, nlist) : tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                            // idle slot of the launch order
     // The group's state and extent in one wait, and the first operand loads before
@@ -102,6 +104,7 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     if (!polish && (MODE <= 2 || MODE >= 5) && dn) return;  // finished at an earlier step
     const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
+    if (QUARTERS && ti * BM >= ld) return;        // beyond the matrix
 
     // the prescaling enters the products that read X_0: squares and the update
     double a = 1.0;
@@ -291,41 +294,46 @@ void ns_f64_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
 
 namespace {
 
-template <int WB>
-hipError_t launch_wb(hipStream_t st, int mode, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+template <int WB, bool QUARTERS>
+hipError_t launch_wb(hipStream_t st, int mode, const TileList &tiles, const GroupDesc *groups,
                      const double *x, const double *b, double *out, const IterState &it, int k, double tol,
                      int max_iter, int polish, const double *x2, const double *b2)
 {
-#define SMX_NS_LAUNCH(M)                                                                                    \
-    hipLaunchKernelGGL((ns_f64_kernel<M, WB>), dim3(ntiles), dim3(256), 0, st, tiles, groups, x, b, out, it, k, tol, \
-                       max_iter, polish, x2, b2)
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(tile_grid(tiles)), dim3(256), 0, st, tiles.tiles, groups, x, b, out, it, k, tol,
+                           max_iter, polish, x2, b2, tiles.n);
+        return hipGetLastError();
+    };
     switch (mode) {
-    case 0: SMX_NS_LAUNCH(0); break;
-    case 1: SMX_NS_LAUNCH(1); break;
-    case 2: SMX_NS_LAUNCH(2); break;
-    case 3: SMX_NS_LAUNCH(3); break;
-    case 4: SMX_NS_LAUNCH(4); break;
-    case 5: SMX_NS_LAUNCH(5); break;
-    case 6: SMX_NS_LAUNCH(6); break;
-    default: return hipErrorInvalidValue;
+    case 0: return go(ns_f64_kernel<0, WB, QUARTERS>);
+    case 1: return go(ns_f64_kernel<1, WB, QUARTERS>);
+    case 5: return go(ns_f64_kernel<5, WB, QUARTERS>);
+    case 6: return go(ns_f64_kernel<6, WB, QUARTERS>);
     }
-#undef SMX_NS_LAUNCH
-    return hipGetLastError();
+    if constexpr (!QUARTERS) {          // tangents and the adjoint are never evaluated from the fixed array
+        switch (mode) {
+        case 2: return go(ns_f64_kernel<2, WB, false>);
+        case 3: return go(ns_f64_kernel<3, WB, false>);
+        case 4: return go(ns_f64_kernel<4, WB, false>);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles,
-                         const GroupDesc *groups, const double *x, const double *b, double *out,
-                         const IterState &it, int k, double tol, int max_iter, int polish, const double *x2,
-                         const double *b2)
+hipError_t launch_ns_f64(hipStream_t st, int mode, int edge, const TileList &tiles, const GroupDesc *groups,
+                         const double *x, const double *b, double *out, const IterState &it, int k, double tol,
+                         int max_iter, int polish, const double *x2, const double *b2)
 {
-    if (ntiles <= 0) return hipSuccess;
-    switch (edge) {
-    case 32: return launch_wb<1>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
-    case 64: return launch_wb<2>(st, mode, ntiles, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
-    default: return hipErrorInvalidValue;
-    }
+    if (tiles.n <= 0) return hipSuccess;
+    if (edge == 64 && tiles.quarters)
+        return launch_wb<2, true>(st, mode, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
+    if (edge == 64)
+        return launch_wb<2, false>(st, mode, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
+    if (edge == 32 && !tiles.quarters)
+        return launch_wb<1, false>(st, mode, tiles, groups, x, b, out, it, k, tol, max_iter, polish, x2, b2);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace smx

@@ -1114,12 +1114,14 @@ void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__re
 // What bounds it: the FP32 matrix pipe (32 cycles a product).  water256 in 384
 // k-means groups (n up to ~1300), square / update per launch: 128 x 128 tiles, one
 // LDS stage, epilogue through LDS 1.79 / 1.68 ms; edge 64 1.59 / 1.51 ms.
-template <int MODE, int WB>
+// QUARTERS (WB = 2): the list holds nlist 128 x 128 tiles, see TileList.
+template <int MODE, int WB, bool QUARTERS>
 __global__ __launch_bounds__(256, 4)
 void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restrict__ groups,
                    const float *__restrict__ xin, const float *__restrict__ bin,
-                   float *__restrict__ out, IterState it, int k, double switch_tol, int kmax)
+                   float *__restrict__ out, IterState it, int k, double switch_tol, int kmax, int nlist)
 {
+    static_assert(WB == 2 || !QUARTERS, "a quarter of a 128 x 128 tile has edge 64");
     constexpr int TE = 32 * WB;         // tile edge
     constexpr int WE = 16 * WB;         // edge of a wave's part of the tile
     constexpr int SF = BK + 4;          // LDS column stride in floats (breaks bank aliasing)
@@ -1131,7 +1133,7 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
         loaded(groups, it.done);
         loaded(xin, bin);
     }
-    const TileDesc td = tiles[blockIdx.x];
+    const TileDesc td = QUARTERS ? quarter_tile(tiles, nlist) : tiles[blockIdx.x];
     const int g = td.x;
     if (g < 0) return;                  // idle slot of the launch order
     const GroupDesc gd = groups[g];
@@ -1143,6 +1145,7 @@ void ns_f32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__restri
     if (dn) return;
     const int ti = td.y >> 16, tj = td.y & 0xffff;
     const int ld = gd.npad;
+    if (QUARTERS && ti * TE >= ld) return;        // beyond the matrix
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1460,27 +1463,32 @@ hipError_t launch_ns_words32(hipStream_t st, int fmt, int nw, int mode, int ntil
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, int ntiles, const TileDesc *tiles, const GroupDesc *groups,
+hipError_t launch_ns_f32(hipStream_t st, int mode, int edge, const TileList &tiles, const GroupDesc *groups,
                          const unsigned short *x, const unsigned short *b, unsigned short *out, const IterState &it,
                          int k, double switch_tol, int kmax)
 {
-    if (ntiles <= 0) return hipSuccess;
+    if (tiles.n <= 0) return hipSuccess;
     const float *xf = reinterpret_cast<const float *>(x), *bf = reinterpret_cast<const float *>(b);
     float *of = reinterpret_cast<float *>(out);
     const auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(ntiles), dim3(256), 0, st, tiles, groups, xf, bf, of, it, k, switch_tol, kmax);
+        hipLaunchKernelGGL(kernel, dim3(tile_grid(tiles)), dim3(256), 0, st, tiles.tiles, groups, xf, bf, of, it, k,
+                           switch_tol, kmax, tiles.n);
         return hipGetLastError();
     };
-    if ((edge != 32 && edge != 64) || mode < 0 || mode > 3) return hipErrorInvalidValue;
-    switch (mode + (edge == 64 ? 4 : 0)) {
-    case 0: return go(ns_f32_kernel<0, 1>);
-    case 1: return go(ns_f32_kernel<1, 1>);
-    case 2: return go(ns_f32_kernel<2, 1>);
-    case 3: return go(ns_f32_kernel<3, 1>);
-    case 4: return go(ns_f32_kernel<0, 2>);
-    case 5: return go(ns_f32_kernel<1, 2>);
-    case 6: return go(ns_f32_kernel<2, 2>);
-    default: return go(ns_f32_kernel<3, 2>);
+    if ((edge != 64 && (edge != 32 || tiles.quarters)) || mode < 0 || mode > 3) return hipErrorInvalidValue;
+    switch (mode + (tiles.quarters ? 8 : edge == 64 ? 4 : 0)) {
+    case 0: return go(ns_f32_kernel<0, 1, false>);
+    case 1: return go(ns_f32_kernel<1, 1, false>);
+    case 2: return go(ns_f32_kernel<2, 1, false>);
+    case 3: return go(ns_f32_kernel<3, 1, false>);
+    case 4: return go(ns_f32_kernel<0, 2, false>);
+    case 5: return go(ns_f32_kernel<1, 2, false>);
+    case 6: return go(ns_f32_kernel<2, 2, false>);
+    case 7: return go(ns_f32_kernel<3, 2, false>);
+    case 8: return go(ns_f32_kernel<0, 2, true>);
+    case 9: return go(ns_f32_kernel<1, 2, true>);
+    case 10: return go(ns_f32_kernel<2, 2, true>);
+    default: return go(ns_f32_kernel<3, 2, true>);
     }
 }
 

@@ -11,8 +11,8 @@ import hipstub
 
 pytestmark = pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
 
-F64 = {32: "ns_f64_kernel<{m}, 1>", 64: "ns_f64_kernel<{m}, 2>"}
-F32 = {32: "ns_f32_kernel<{m}, 1>", 64: "ns_f32_kernel<{m}, 2>"}
+F64 = {32: "ns_f64_kernel<{m}, 1, false>", 64: "ns_f64_kernel<{m}, 2, false>"}
+F32 = {32: "ns_f32_kernel<{m}, 1, false>", 64: "ns_f32_kernel<{m}, 2, false>"}
 FORMAT = {"fp16x2": "0, 2", "bf16x3": "1, 3", "bf16": "1, 1"}
 
 
