@@ -64,3 +64,31 @@ for precision in {list(want)!r}:
     for precision, names in got.items():
         assert set(names.split("|")) == {want[precision].format(m=m) for m in (0, 1)}, (precision, names)
     assert set(got) == set(want)
+
+
+@pytest.mark.parametrize("shape,variant,names", [
+    (0, 0, {"fp16x2": "ns_words32_kernel<0, 2, {m}>", "bf16x3": "ns_words32_kernel<1, 3, {m}>",
+            "bf16": "ns_words32_kernel<1, 1, {m}>"}),
+    (1 << 20, 0, {"fp16x2": "ns_words_kernel<0, 2, {m}, 0>", "bf16x3": "ns_words_kernel<1, 3, {m}, 0>",
+                  "bf16": "ns_words_kernel<1, 1, {m}, 0>"}),
+    (32, 0, {"fp16x2": "ns_words256_kernel<0, 2, {m}>", "bf16x3": "ns_words_kernel<1, 3, {m}, 0>",
+             "bf16": "ns_words256_kernel<1, 1, {m}>"}),
+    (1 << 20, 1, {"fp16x2": "ns_words_kernel<0, 2, {m}, 1>", "bf16": "ns_words_kernel<1, 1, {m}, 1>"}),
+    (1 << 20, 2, {"fp16x2": "ns_words_persistent<0, 2, {m}>", "bf16": "ns_words_persistent<1, 1, {m}>"}),
+])
+def test_tiles_the_caller_chose(stub, shape, variant, names):
+    """A size bucket that no group reaches keeps a small batch on the 128 x 128 tiles."""
+    out = hipstub.run(stub, f"""
+ctx = smx.Context(0).load(water_config("water16"))
+smx.smx_set_tile_shape(ctx.handle, {shape})
+smx.smx_set_kernel_variant(ctx.handle, {variant})
+for precision in {list(names)!r}:
+    ctx.configure(precision=precision)
+    stub.stub_set(1, NEVER)
+    launches()
+    smx.smx_evaluate(ctx.handle)
+    print(precision, "|".join(sorted(set(k for k, g in launches("ns_")))), sep=":")
+""")
+    for line in out.splitlines():
+        precision, got = line.split(":")
+        assert set(got.split("|")) == {names[precision].format(m=m) for m in (0, 1)}, line
