@@ -392,7 +392,9 @@ def main():
         "avg_launch_ms": kms / max(kn, 1),
         "time_share": kms / sum(v[0] for v in run["prof"].values()),
         # issued matrix-core flops (word products, padding and half tiles included)
-        # over the launch time and the same peak: the matrix-core utilisation proper
+        # over the launch time and the same peak: the matrix-core utilisation proper of
+        # the word products, a bound from above for the FP64 and FP32 ones, whose smaller
+        # tiles skip part of the counted padding
         "issued_frac": (kiss / (kms * 1e-3) / 1e12 / peak) if bound == "mfma" else None,
         "issued_per_algorithmic": kiss / kfl if kfl > 0 else None,
         "issued_mfma_tflops_all_products": (stats["exec_flops"] / (stats["time_iterate_ms"] * 1e-3) / 1e12

@@ -102,8 +102,9 @@ typedef struct {
     double  resid_max;        /* max over groups of the last computed max|X^2 - I| */
     double  algo_flops;       /* sum_g 2 n_g^3 x dense products: two per Newton-
                                  Schulz step, three per Pade step                  */
-    double  exec_flops;       /* flops issued to the matrix cores (padding, half
-                                 tiles and multi-word products included)           */
+    double  exec_flops;       /* matrix-core flops, padding, half tiles and multi-word
+                                 products included, counted as by
+                                 smx_get_launch_issued                             */
     double  time_gather_ms;   /* device time of the last evaluation, per phase    */
     double  time_iterate_ms;
     double  time_scatter_ms;
@@ -601,10 +602,12 @@ int32_t smx_get_sizes(smx_ctx ctx, int32_t *ngroups, int64_t *nvalues);
 /*
  * Per-launch profile of the matrix-core product kernels of the last
  * evaluation, in launch order: device time in ms between the HIP events before and
- * after the launch on the context's stream (one event between two launches), the algorithmic flops of the launch (2 n_g^3 for
+ * after the launch on the context's stream (one event between two launches, so
+ * with the gap between them), the algorithmic flops of the launch (2 n_g^3 for
  * every group the launch works on, i.e. one dense n_g x n_g product), and
  * its kind: 0/1 FP64 square/update, 2/3 reduced-precision square/update on
- * 128 x 128 tiles (32 x 32 for a small batch; FP32 64 x 64 or 32 x 32), 4/5 FP64 polish square/update, 6 mu tangent, 7/8
+ * 128 x 128 tiles (32 x 32 for a small batch; FP32 64 x 64 or 32 x 32), 4/5
+ * FP64 polish square/update, 6 mu tangent, 7/8
  * reduced-precision square/update on 256 x 256 tiles, 9/10 reduced-precision
  * Pade combine on 128 x 128 / 256 x 256 tiles, 11 FP64 Pade combine (the Pade
  * square shares the square's kind), 12 Householder reduction of the
@@ -615,17 +618,21 @@ int32_t smx_get_launch_profile(smx_ctx ctx, int32_t cap, float *ms, double *algo
                                int32_t *kind, int32_t *count);
 
 /*
- * Issued matrix-core flops of each launch of smx_get_launch_profile, in the
- * same order: 2 x 64 x 64 x n_pad per live 64 x 64 wave tile of a 128 x 128
- * tile (2 x 16 x 16 x n_pad per live 16 x 16 block of a 256 x 256 tile),
- * times the word products per algorithmic product (3 for SMX_FP16_2W, 6 for
- * SMX_BF16_3W, else 1), padding included, for every group the launch works
- * on (the FP64 products are counted in the same 64 x 64 tiles, of which they
- * skip the 32 x 32 parts beyond the matrix or above the diagonal); kind 12 (vector units only) repeats its algorithmic flops.  Divided by
- * the launch time and the matrix-core peak of the format this is the
- * fraction of the matrix cores the launch kept busy.  Writes min(cap, count)
- * entries (issued_flops may be NULL) and the launch count to *count.
- * Synchronises.
+ * Matrix-core flops of each launch of smx_get_launch_profile on 128 x 128
+ * tiles, in the same order: 2 x 64 x 64 x n_pad per live 64 x 64 wave tile of a
+ * 128 x 128 tile (for kinds 7, 8 and 10: 2 x 16 x 16 x n_pad per live 16 x 16
+ * block of a 256 x 256 tile), times the word products per algorithmic product
+ * (3 for SMX_FP16_2W, 6 for SMX_BF16_3W, else 1), padding included, for every
+ * group the launch works on.  Word products on 128 x 128 and 256 x 256 tiles
+ * issue just that: divided by the launch time and the matrix-core peak of the
+ * format it is the fraction of the matrix cores the launch kept busy.  The
+ * smaller tiles issue less, and the count is a bound from above: FP64 and FP32
+ * products, and the word products of small batches, skip what lies beyond the
+ * matrix or above the diagonal in pieces of 32 x 32 (tiles of 64 x 64) or 16 x 16
+ * (tiles of 32 x 32): at n_pad = 864 0.90 of the count, at 384 0.89 (16 x 16), at 32
+ * 0.19.  Kind 12, whose matrix-core part is not counted, repeats its algorithmic
+ * flops.  Writes min(cap, count) entries (issued_flops may be NULL) and the
+ * launch count to *count.  Synchronises.
  */
 int32_t smx_get_launch_issued(smx_ctx ctx, int32_t cap, double *issued_flops, int32_t *count);
 

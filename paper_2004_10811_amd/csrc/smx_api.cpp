@@ -2738,7 +2738,7 @@ int32_t smx_get_launch_issued(smx_ctx c, int32_t cap, double *issued_flops, int3
             const GroupDesc &d = P.gd[g];
             if (kd == 12) {
                 const double n = d.n;
-                f += 4.0 / 3.0 * n * n * n;              // vector-unit work, no matrix cores
+                f += 4.0 / 3.0 * n * n * n;              // the algorithmic count
             } else if (active) {
                 const bool word = kd == 2 || kd == 3 || kd == 7 || kd == 8 || kd == 9 || kd == 10;
                 const double per = (kd == 7 || kd == 8 || kd == 10) ? P.wtiles2[g] * 2.0 * 16 * 16 * d.npad

@@ -156,7 +156,6 @@ __device__ inline void sym_mv(const double *__restrict__ A, int ld, int n, int k
         if (c2 >= nch) {                               // next strip of this wave
             round2++;
             s2 = k0 / 16 + round2 * NWV + ((round2 & 1) ? NWV - 1 - wave : wave);
-            if (s2 >= nst && !(round2 & 1)) s2 = nst;
             c2 = s2 >> 2;
         }
         const bool last = s2 >= nst;
@@ -894,7 +893,7 @@ void wy_t_kernel(const GroupDesc *__restrict__ groups, int g0, const double *__r
 #pragma unroll
     for (int v = 0; v < 4; v++) gs[wave][lq + 4 * v][li] = acc[v];
     __syncthreads();
-    if (threadIdx.x < 256) {
+    {
         const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
         gs[0][r][c] = ((gs[0][r][c] + gs[1][r][c]) + gs[2][r][c]) + gs[3][r][c];
     }

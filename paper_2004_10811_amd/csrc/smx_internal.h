@@ -375,8 +375,9 @@ struct EigVecs {
     int32_t *bs, *be;
 };
 
-// Largest n whose reduction reads the trailing block's lower triangle only.  A multiple
-// of 32: n is at most this where n_pad is.
+// Largest n whose reduction reads the trailing block's lower triangle only.  Its LDS
+// (80 B a row and 1 KB) would take n up to 1984; beyond 1280 it has not been measured.
+// A multiple of 32: n is at most this where n_pad is.
 constexpr int kEigHalfMaxN = 1280;
 // A stream beside the caller's, and the events that fork work to it and join it back.
 struct SideStream {

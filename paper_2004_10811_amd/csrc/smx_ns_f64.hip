@@ -40,7 +40,7 @@
 // launch: edge 128, two workgroups per CU and loads under a column condition
 // (the compiler waited for them before the products) 11.7 / 10.9 ms; edge 96
 // 10.9 / 10.4; edge 64 10.1 / 9.6 with loads one step ahead, 9.9 / 9.4 two
-// steps ahead, which is 0.9 of the matrix pipe at 2.4 GHz; edge 32 11.8 / 11.3
+// steps ahead, the matrix pipe busy for 0.75 of them by the counters; edge 32 11.8 / 11.3
 // (one block per wave: each operand value read from LDS feeds one product);
 // edge 64 with K steps of 32 12.2 / 11.0 (two workgroups per CU).
 #include "smx_internal.h"

@@ -1112,7 +1112,7 @@ void ns_words32_kernel(const TileDesc *__restrict__ tiles, const GroupDesc *__re
 // is the same for every edge.
 //
 // What bounds it: the FP32 matrix pipe (32 cycles a product).  water256 in 384
-// k-means groups (n up to ~1300), square / update per launch: 128 x 128 tiles, one
+// k-means groups (n 544-1032), square / update per launch: 128 x 128 tiles, one
 // LDS stage, epilogue through LDS 1.79 / 1.68 ms; edge 64 1.59 / 1.51 ms.
 // QUARTERS (WB = 2): the list holds nlist 128 x 128 tiles, see TileList.
 template <int MODE, int WB, bool QUARTERS>
