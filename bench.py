@@ -195,10 +195,10 @@ PEAK_BY_KERNEL = {"ns_f64_kernel": ("fp64", 78.6), "ns_words_kernel": ("fp16/bf1
 # The same runs give the matrix-core busy fraction (SQ_VALU_MFMA_BUSY_CYCLES
 # over 1024 SIMDs x 2.4 GHz x kernel time).
 TRAFFIC = {
-    ("water1024", "ns_words_kernel"): (8.175e9, ("smx_ns_words.hip", "smx_internal.h"), "0ba99e5e14a85cb8",
-                                       "profiles/ns_words_kernel_water1024_fp16x2.md", 0.301),
-    ("water1024", "ns_f64_kernel"): (29.98e9, ("smx_ns_f64.hip", "smx_internal.h"), "c6467a844e807b38",
-                                     "profiles/ns_f64_kernel_water1024_fp64.md", 0.755),
+    ("water1024", "ns_words_kernel"): (8.175e9, ("smx_ns_words.hip", "smx_internal.h"), "17063f5142c4b8b9",
+                                       "profiles/ns_words_kernel_water1024_fp16x2.md", 0.300),
+    ("water1024", "ns_f64_kernel"): (29.90e9, ("smx_ns_f64.hip", "smx_internal.h"), "a2f5fc8ca3220a93",
+                                     "profiles/ns_f64_kernel_water1024_fp64.md", 0.749),
 }
 
 
