@@ -1239,6 +1239,7 @@ hipError_t launch_eig_tridiag(hipStream_t st, const SideStream &side, int g0, in
         if (e == hipSuccess) e = hipEventRecord(side.join, side.stream);
         if (e == hipSuccess) e = go(tridiag_kernel<true>, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(st, side.join, 0);
+        if (e != hipSuccess) (void)hipStreamSynchronize(side.stream);   // nothing stays behind unjoined
     }
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(split_kernel, dim3((unsigned)ngroups), dim3(256), 0, st, groups, g0, ev);
