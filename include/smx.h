@@ -243,9 +243,9 @@ int32_t smx_set_tile_order(smx_ctx ctx, int32_t order);
  * tiles from one work list per XCD through atomic counters (each starts with
  * its own XCD's list, read from the hardware, then takes what the others left).
  * With 0, a small batch (no size bucket; at most 1536 lower tiles of 64 x 64; n_pad
- * at most 1536; on any XCD at most 384 lower tiles of 32 x 32, 320 in 3-word and 200
- * in 1-word BF16) takes 32 x 32 tiles, loaded two K steps ahead.  Results are
- * bitwise the same.
+ * at most 1536; on any XCD at most 384 lower tiles of 32 x 32, 320 in 3-word and 240
+ * in 1-word BF16, there 320 too up to n_pad = 320) takes 32 x 32 tiles, loaded two K
+ * steps ahead.  Results are bitwise the same.
  */
 int32_t smx_set_kernel_variant(smx_ctx ctx, int32_t variant);
 

@@ -580,12 +580,14 @@ int32_t f32_edge(const Plan &P)
 //     of 1000) 64 / 54, one of 2000 413 / 192, one of 3000 1329 / 535;
 //   three BF16 words: 190 32 / 52, 272 39 / 48, 378 73 / 67, 380 54 / 54, 528 110 / 80;
 //   one BF16 word, half the bytes and a third of the products: 136 (500 x 8) 17 / 22, 190
-//     20 / 23, 253 (700 x 8) 24.7 / 23.9, 272 22.5 / 21.1.
+//     20 / 23, 253 (700 x 8) 24.7 / 23.9, 272 22.5 / 21.1; the smaller the groups, the
+//     longer: 273 (400 x 24) 22.3 / 21.6, 275 (300 x 40) 19.0 / 20.3.
 // Spread over all XCDs (the caller's tile order 1), large groups miss the L2s: one of 1000
 // (66 tiles an XCD) 31 / 50 us, one of 2000 (252) 101 / 90.
 bool word_tiles32(const Plan &P, int32_t nw)
 {
-    return P.edge_d == 32 && !P.quarters && P.max_npad <= 1536 && P.busy32 <= (nw == 1 ? 200 : nw == 2 ? 384 : 320);
+    const int64_t most = nw == 2 ? 384 : nw == 3 || P.max_npad <= 320 ? 320 : 240;
+    return P.edge_d == 32 && !P.quarters && P.max_npad <= 1536 && P.busy32 <= most;
 }
 
 // Whether an evaluation gathers A_g in pieces of 64 rows x 16 columns and takes

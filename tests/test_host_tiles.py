@@ -29,7 +29,9 @@ def stub(tmp_path_factory):
 # n of a group, groups, edges of FP64, FP32, two, three and one words
 CASES = [
     (100, 16, 32, 32, 32, 32, 32),
-    (500, 16, 32, 32, 32, 32, 128),         # 272 tiles of 32 on an XCD
+    (300, 30, 32, 32, 32, 32, 32),          # 220 tiles of 32 on an XCD
+    (300, 40, 32, 32, 32, 32, 32),          # 275
+    (500, 16, 32, 32, 32, 32, 128),         # 272
     (600, 8, 32, 32, 32, 32, 32),           # 190
     (700, 8, 32, 32, 32, 32, 128),          # 253
     (850, 8, 32, 32, 32, 128, 128),         # 378
